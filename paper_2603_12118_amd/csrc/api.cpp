@@ -927,7 +927,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     GemmArgs g = {};
     g.A = A; g.lda = lda; g.W = e->ptr<bf16_t>(W); g.ldo = D; g.M = (int32_t)N; g.N = (int32_t)D;
     if (S > 1) {
-      g.ldw = K; g.K = (int32_t)(K / S); g.splits = S; g.split_stride = N * D; g.out = parts;
+      g.ldw = K; g.K = (int32_t)K; g.splits = S; g.split_stride = N * D; g.out = parts;
       if (cs_status st = launch_gemm(EPI_F32, g, stream)) return st;
       // the sums stay pending: the normalisation that reads x next adds them on its way through
       pending.parts = parts; pending.n_parts = S; pending.stride = N * D;
@@ -1051,7 +1051,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       // small batches: both GEMMs split over K like the residual ones (a few merged rows against K = 2 * 4D)
       auto split_gemm = [&](const bf16_t* A, int64_t K, size_t W, int64_t Nn, int S) {
         GemmArgs g = {};
-        g.A = A; g.lda = K; g.W = e->ptr<bf16_t>(W); g.ldw = K; g.K = (int32_t)(K / S); g.splits = S;
+        g.A = A; g.lda = K; g.W = e->ptr<bf16_t>(W); g.ldw = K; g.K = (int32_t)K; g.splits = S;
         g.split_stride = M * Nn; g.out = parts; g.ldo = Nn; g.M = (int32_t)M; g.N = (int32_t)Nn;
         return launch_gemm(EPI_F32, g, stream);
       };
@@ -1174,10 +1174,20 @@ cs_status cs_linear_bf16(const void* A, int64_t lda, const void* W, const float*
                          int64_t M, int32_t N, int32_t K, void* stream) {
   if (!A || !W || !C) return fail(CS_ERR_INVALID_ARG, "cs_linear_bf16: NULL argument");
   if (M < 0 || M > 0x7fffffff || N < 0) return fail(CS_ERR_INVALID_ARG, "cs_linear_bf16: sizes");
-  GemmArgs g = {};
-  g.A = static_cast<const bf16_t*>(A); g.lda = lda; g.W = static_cast<const bf16_t*>(W); g.bias = bias;
-  g.out = C; g.ldo = N; g.M = (int32_t)M; g.N = N; g.K = K;
-  return launch_gemm(c_dtype == CS_BF16 ? EPI_BF16 : EPI_F32, g, static_cast<hipStream_t>(stream));
+  // rows too far apart for a tile's 32-bit offsets go in several launches
+  int64_t rows = std::max<int64_t>(M, 1), cols = std::max<int64_t>(N, 1);
+  while (rows > 1 && !gemm_rows_addressable(rows, lda)) rows = std::min<int64_t>(rows, 256) / 2;
+  while (cols > 8 && !gemm_rows_addressable(cols, K)) cols = (std::min<int64_t>(cols, 256) / 2 + 7) & ~int64_t(7);
+  for (int64_t m = 0; m < M; m += rows)
+    for (int64_t n = 0; n < N; n += cols) {
+      GemmArgs g = {};
+      g.A = static_cast<const bf16_t*>(A) + m * lda; g.lda = lda; g.W = static_cast<const bf16_t*>(W) + n * K;
+      g.bias = bias ? bias + n : nullptr;
+      g.out = static_cast<unsigned char*>(C) + (m * N + n) * (c_dtype == CS_BF16 ? 2 : 4);
+      g.ldo = N; g.M = (int32_t)std::min(rows, M - m); g.N = (int32_t)std::min<int64_t>(cols, N - n); g.K = K;
+      if (cs_status st = launch_gemm(c_dtype == CS_BF16 ? EPI_BF16 : EPI_F32, g, static_cast<hipStream_t>(stream))) return st;
+    }
+  return CS_OK;
 }
 
 static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,

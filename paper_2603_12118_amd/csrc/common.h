@@ -66,8 +66,8 @@ struct GemmArgs {
   int64_t ldo;
   const int32_t* row_map;  // nullptr, or destination row per m (negative: skip)
   int32_t M, N, K;
-  // split K: workgroups with blockIdx.y = s compute columns [s*K, (s+1)*K) of A and W (K is the length of
-  // one part) and write to out + s * split_stride elements; splits <= 1: one part
+  // split K: workgroups with blockIdx.y = s take an equal share, in whole slices of 64, of the K columns of A and W
+  // and write to out + s * split_stride elements; splits <= 1: one part
   int32_t splits;
   int64_t split_stride;
   // EPI_QKV only
@@ -111,6 +111,11 @@ struct GemmArgs {
   int32_t plain_stores;
 };
 
+// The kernels address the rows of a tile (at most 256) by 32-bit byte offsets from its first row.
+inline bool gemm_rows_addressable(int64_t rows, int64_t pitch) {
+  const int64_t n = (rows < 256 ? rows : 256) - 1;
+  return n <= 0 || (pitch >= 0 && pitch <= (0xFFFFFF00ll / 2 - 64) / n);
+}
 cs_status launch_gemm(int epilogue, const GemmArgs& g, hipStream_t stream);
 // Column tiles (= partial sums of squares per row) of a residual GEMM that can fold the next RMSNorm into its
 // epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.

@@ -2,8 +2,8 @@
 //
 // One workgroup owns a BM x BN tile of C and walks K in slices of 64.  Each slice of A and W is
 // brought into LDS with 16-byte LDS-direct loads (no staging registers, no LDS store
-// instructions), double-buffered: the loads of slice k+1 are issued one by one between the MFMAs
-// of the first half of slice k and have the rest of that slice to land.
+// instructions) into two to four stage buffers: the loads of a later slice are issued one by one between the
+// MFMAs of the current one (main_loop).
 //
 // LDS layout: rows of 128 bytes (64 bf16), the 16-byte chunk at position c of row r holds chunk
 // c ^ ((r/2) % 8) of that row.  Measured on gfx950, ds_read_b128 serves 16 lanes per pass and the
@@ -13,11 +13,10 @@
 // address each lane fetches.
 //
 // Waves are laid out WGM x WGN over the tile; a wave accumulates (BM/WGM) x (BN/WGN) in fp32 with
-// v_mfma_f32_32x32x16_bf16.  The products are formed transposed (W rows as the first operand), so
-// that a lane owns one row m of C and its 16 accumulator registers of a 32x32 block walk the
+// v_mfma_f32_16x16x32_bf16.  The products are formed transposed (W rows as the first operand), so
+// that a lane owns rows m of C and its accumulator registers walk the
 // columns in groups of four consecutive n: bias, activations, rotary pairs and 8/16-byte stores
-// all work on registers of one lane.  Inside a K slice the LDS reads of k-step s+1 are issued
-// behind the first MFMAs of k-step s and scheduling barriers pin that order.
+// all work on registers of one lane.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -28,7 +27,6 @@
 namespace cs {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -36,29 +34,16 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// The MFMA shape (build-time switch for measurement: -DCS_GEMM_MFMA16=0 gives v_mfma_f32_32x32x16_bf16).
-// Both do 1024 FLOP per SIMD and clock; on random operands at the board's power limit a bare loop of
-// 16x16x32 sustains about 12 % more (see cs_mfma_ceiling and the measurement notes).
-#ifndef CS_GEMM_MFMA16
-#define CS_GEMM_MFMA16 1
-#endif
-// The 16x16x32 shape is used by the eight-wave tiles (two waves per SIMD).  With one wave per SIMD (the
-// four-wave tiles) it is slower: every other instruction of the wave delays an MFMA of 16 clocks more
-// than one of 32 (measured: down projection 67 -> 106 us).
-// (The four-wave 128 x 160 tile is launched only where two of its workgroups share a CU, which again makes two
-// waves per SIMD.)
-template <int NWAVES, int BM = 256, int BN = 256>
-constexpr bool use_mfma16() { return CS_GEMM_MFMA16 != 0 && (NWAVES >= 8 || (BM == 128 && BN == 160)); }
-
-// A wave's accumulators are kept per 32 x 32 block of C^T (or C), 16 registers per lane = 4 groups q of
-// 4 consecutive columns of one row.  Which row and columns a lane's group q holds depends on the MFMA:
-//   32x32x16: one block per MFMA;      row lane % 32,                columns 8q + 4 (lane / 32) ...
-//   16x16x32: four MFMAs per block;    row 16 (q / 2) + lane % 16,   columns 16 (q % 2) + 4 (lane / 16) ...
-// ("row" is the second operand's index, "column" the first operand's.)
-template <bool MFMA16>
-__device__ __forceinline__ int blk_row(int q, int lane) { return MFMA16 ? 16 * (q >> 1) + (lane & 15) : (lane & 31); }
-template <bool MFMA16>
-__device__ __forceinline__ int blk_col(int q, int lane) { return MFMA16 ? 16 * (q & 1) + 4 * (lane >> 4) : 8 * q + 4 * (lane >> 5); }
+// All products run on v_mfma_f32_16x16x32_bf16.  The 32x32x16 shape does the same 1024 FLOP per SIMD and clock, but on
+// random operands at the board's power limit a bare loop of 16x16x32 sustains about 12 % more (cs_mfma_ceiling).
+//
+// A wave's accumulators are kept per 32 x 32 block of C^T (or C) as 4 groups q of 4 consecutive columns of one row
+// ("row" is the second operand's index, "column" the first operand's): four MFMAs per block, group q of a lane holds
+// row 16 (q / 2) + lane % 16, columns 16 (q % 2) + 4 (lane / 16) ...
+// (Each group is a register quad of its own: kept as one 16-register vector per block, a four-wave workgroup's
+// accumulators were copied between register files around every MFMA.)
+__device__ __forceinline__ int blk_row(int q, int lane) { return 16 * (q >> 1) + (lane & 15); }
+__device__ __forceinline__ int blk_col(int q, int lane) { return 16 * (q & 1) + 4 * (lane >> 4); }
 // four floats -> four bf16 (v_cvt_pk_bf16_f32, round to nearest even), as 8 bytes
 __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d) {
   const f32x4 v = {a, b, c, d};
@@ -82,18 +67,9 @@ __device__ __forceinline__ float silu_f(float z) {
 // which the four-wave one must fit a CU twice, have 128 rows and two waves along N: 2 KB of sums.)
 constexpr int EXTRA_LDS_BYTES = 1024 + 2 * 4 * 256 * 4;
 constexpr int EXTRA_LDS_BYTES_PAIR = 1024 + 4 * 256 * 4;
-// (Build-time switch for measurement: -DCS_GEMM_NARROW_STAGES=3 gives the eight-wave 256 x 160 tile of the plain
-// residual epilogue a third stage buffer, see stages(); what is left of 160 KB then holds exactly its column
-// values and one set of sums.  Measured on one box, alternated: slower, down projection 885 -> 816 TFLOP/s, the
-// 8-image step 11.72 -> 12.02 ms, the 16 384-token step 26.35 -> 26.6 ms.)
-#ifndef CS_GEMM_NARROW_STAGES
-#define CS_GEMM_NARROW_STAGES 2
-#endif
-template <int BM, int BN, int NWAVES, int EPI>
-constexpr bool third_stage() { return CS_GEMM_NARROW_STAGES == 3 && BM == 256 && BN == 160 && NWAVES == 8 && EPI == EPI_RESADD_F32; }
 template <int BM, int BN, int NWAVES = 0, int EPI = -1>
 constexpr int extra_lds_bytes() {
-  return third_stage<BM, BN, NWAVES, EPI>() ? 1024 + 2 * 256 * 4 : BM == 128 && BN == 160 ? EXTRA_LDS_BYTES_PAIR : EXTRA_LDS_BYTES;
+  return BM == 128 && BN == 160 ? EXTRA_LDS_BYTES_PAIR : EXTRA_LDS_BYTES;
 }
 // Stage buffers of the K loop.  Two everywhere (a slice's MFMAs cover the next slice's loads where the tile is
 // large, and more would not fit) except on the eight-wave 128 x 160 tile, which runs one workgroup per CU in
@@ -104,10 +80,13 @@ constexpr int extra_lds_bytes() {
 #ifndef CS_GEMM_SMALL_STAGES
 #define CS_GEMM_SMALL_STAGES 4
 #endif
-template <int BM, int BN, int NWAVES, int EPI>
-constexpr int stages() { return BM == 128 && BN == 160 && NWAVES == 8 ? CS_GEMM_SMALL_STAGES : third_stage<BM, BN, NWAVES, EPI>() ? 3 : 2; }
-template <int BM, int BN, int NWAVES, int EPI>
-constexpr int tile_lds_bytes() { return stages<BM, BN, NWAVES, EPI>() * (BM + BN) * 128 + extra_lds_bytes<BM, BN, NWAVES, EPI>(); }
+template <int BM, int BN, int NWAVES>
+constexpr int default_stages() { return BM == 128 && BN == 160 && NWAVES == 8 ? CS_GEMM_SMALL_STAGES : 2; }
+template <int BM, int BN, int NWAVES, int EPI, int STAGES>
+constexpr int tile_lds_bytes() {   // (the epilogue chunks have room of their own where the idle stage buffers are too small for them)
+  return STAGES * (BM + BN) * 128 + extra_lds_bytes<BM, BN, NWAVES, EPI>() +
+         (NWAVES * 32 * 144 > (BM + BN) * 128 * (STAGES == 4 ? 2 : 1) ? NWAVES * 32 * 144 : 0);
+}
 constexpr int CHUNK_STRIDE = 144;               // bytes between chunk rows: 128 of data + 16 of padding
 constexpr int CHUNK_BYTES_ = 32 * CHUNK_STRIDE;
 // The 64-row tiles of a ragged last tile row run behind the full tiles, eight of them or so on an otherwise idle
@@ -146,7 +125,7 @@ struct NormFold {
   float s1acc[4];         // ... and of x_new (a LayerNorm needs the mean too)
 };
 
-template <int NB, typename T, bool ACCUM, bool MFMA16, bool SUMS = false>
+template <int NB, typename T, bool ACCUM, bool SUMS = false>
 __device__ __forceinline__ void store_block(unsigned char* chunk, const f32x4 (&v)[NB][4], T* out, int64_t ld,
                                             const int32_t* row_map, int row0, int row_end, int col0, int col_end,
                                             bool wide, bool wt, const f32x4* held = nullptr, NormFold* fold = nullptr) {
@@ -159,7 +138,7 @@ __device__ __forceinline__ void store_block(unsigned char* chunk, const f32x4 (&
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      unsigned char* p = chunk + blk_row<MFMA16>(q, lane) * CHUNK_STRIDE + (b * 32 + blk_col<MFMA16>(q, lane)) * ES;
+      unsigned char* p = chunk + blk_row(q, lane) * CHUNK_STRIDE + (b * 32 + blk_col(q, lane)) * ES;
       if constexpr (ES == 2) *reinterpret_cast<u32x2*>(p) = pack4(v[b][q][0], v[b][q][1], v[b][q][2], v[b][q][3]);
       else *reinterpret_cast<f32x4*>(p) = v[b][q];
     }
@@ -220,282 +199,265 @@ __device__ __forceinline__ void store_block(unsigned char* chunk, const f32x4 (&
 #define CS_GEMM_A_AUX 0
 #endif
 
+template <int V>
+struct int_tag { static constexpr int value = V; };
+template <bool V>
+struct bool_tag { static constexpr bool value = V; };
+
+// The operands of a tile as buffer resources: base = first row of the tile, and per load the lane's byte offset
+// from it (row and swizzled chunk).  LDS-direct loads go through buffer instructions, not global_load_lds: the
+// compiler counts the latter in both wait counters without a known order, so that every wait for an LDS read in the
+// loop became "all of them" (lgkmcnt(0)); buffer loads count in vmcnt alone and the LDS waits are exact.
+template <int A_LOADS, int B_LOADS>
+struct Operands {
+  const bf16_t* a;            // uniform
+  const bf16_t* w;
+  uint32_t a_off[A_LOADS], b_off[B_LOADS];
+};
+template <int AUX>
+__device__ __forceinline__ void load_lds16(const bf16_t* base, uint32_t byte_off, unsigned char* lds) {
+#ifdef __HIP_DEVICE_COMPILE__   // (the builtin's resource type does not exist in the host pass)
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0xFFFFFFFFu, 0x00020000),
+                                           (lds_void*)(uintptr_t)lds, 16, byte_off, 0, 0, AUX);
+#endif
+}
+
 // Issues the LDS-direct loads of one 64-wide K slice: every wave instruction moves 64 x 16 bytes
 // from the lanes' global addresses to 1 KB of LDS starting at a wave-uniform address, in lane order.
 // (A wave whose share of the W rows lies beyond the tile, where BN is not a multiple of 8 rows per wave,
 // skips that load: wave-uniform.)
-template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN>
-__device__ __forceinline__ void issue_slice(const bf16_t* const* ap, const bf16_t* const* bp, int kt,
-                                            unsigned char* stage, int wave) {
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i)
-    __builtin_amdgcn_global_load_lds(ap[i] + kt * 64, (lds_void*)(uintptr_t)(stage + (i * NWAVES + wave) * 1024), 16, 0, CS_GEMM_A_AUX);
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i)
-    if (BN % (8 * NWAVES) == 0 || (i * NWAVES + wave) * 8 < BN)
-    __builtin_amdgcn_global_load_lds(bp[i] + kt * 64, (lds_void*)(uintptr_t)(stage + BM * 128 + (i * NWAVES + wave) * 1024), 16, 0, CS_GEMM_W_AUX);
-}
-
 // One of the A_LOADS + B_LOADS loads of a slice, by index.
 template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN>
-__device__ __forceinline__ void issue_one(const bf16_t* const* ap, const bf16_t* const* bp, int l, int kt,
-                                          unsigned char* stage, int wave) {
+__device__ __forceinline__ void issue_one(const Operands<A_LOADS, B_LOADS>& op, int l, int kt, unsigned char* stage, int wave) {
   if (l < A_LOADS)
-    __builtin_amdgcn_global_load_lds(ap[l] + kt * 64, (lds_void*)(uintptr_t)(stage + (l * NWAVES + wave) * 1024), 16, 0, CS_GEMM_A_AUX);
+    load_lds16<CS_GEMM_A_AUX>(op.a + (int64_t)kt * 64, op.a_off[l], stage + (l * NWAVES + wave) * 1024);
   else if (BN % (8 * NWAVES) == 0 || ((l - A_LOADS) * NWAVES + wave) * 8 < BN)
-    __builtin_amdgcn_global_load_lds(bp[l - A_LOADS] + kt * 64,
-                                     (lds_void*)(uintptr_t)(stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024), 16, 0, CS_GEMM_W_AUX);
+    load_lds16<CS_GEMM_W_AUX>(op.w + (int64_t)kt * 64, op.b_off[l - A_LOADS], stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024);
+}
+template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN>
+__device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS>& op, int kt, unsigned char* stage, int wave) {
+#pragma unroll
+  for (int l = 0; l < A_LOADS + B_LOADS; ++l) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, l, kt, stage, wave);
 }
 
-// One 64-wide K slice of a wave's MFMAs.  PREFETCH: the loads of slice kn go out one at a time
-// between the MFMAs of the first k-steps: issued in one burst behind the barrier they queue in the
-// texture-address unit (16 clocks each, all waves at once) and every wave sits in the issue stall
-// instead of feeding the MFMA pipe.  W_FIRST: accumulate C^T blocks (lane = row m, registers =
-// columns n); otherwise C blocks (lane = column n, registers = rows m).
-template <int BM, int BN, int WGM, int WGN, bool W_FIRST, bool PREFETCH>
-__device__ __forceinline__ void k_slice(const bf16_t* const* ap, const bf16_t* const* bp, int kn,
-                                        const unsigned char* cur, unsigned char* nxt, int a_rd, int b_rd, int sw,
-                                        int lhi, int wave, f32x16 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32]) {
-  constexpr int TM = BM / WGM / 32, TN = (BN / WGN + 31) / 32;
-  constexpr int NWAVES = WGM * WGN;
-  constexpr bool MFMA16 = use_mfma16<NWAVES, BM, BN>();
-  constexpr int A_LOADS = BM / (8 * NWAVES), B_LOADS = (BN + 8 * NWAVES - 1) / (8 * NWAVES);
-  constexpr int RD_PER = 2;     // LDS reads of the next k-step issued behind each of the first MFMAs
-  constexpr int SPREAD_KS = 2;  // k-steps over which the next slice's loads are spread (2 measured best of 1..4)
-  if constexpr (MFMA16) {
-    // Two k-steps of 32 with v_mfma_f32_16x16x32_bf16; a_rd / b_rd address row lane % 16 of the wave's first
-    // 16-row fragment and sw = (lane % 16) / 2; lhi = lane / 16 is the lane's 16-byte piece of a k-step's 64
-    // bytes.  Fragment i of A pairs with fragment j of W into quarter 2 (i % 2) + j % 2 of block (i / 2, j / 2).
-    // The operand with fewer fragments per wave is held, double-buffered over the two k-steps (the second
-    // k-step's come in behind the first MFMAs); the other is streamed through a ring of four registers
-    // sets, each fragment requested three rows of MFMAs before its turn, so 48 registers hold the operands
-    // whatever the wave tile (a full double buffer of a 128 x 64 tile would take 96).
-    constexpr int TM16 = 2 * TM, TN16 = BN / WGN / 16;   // a wave's columns may end in the middle of its last 32-block
-    constexpr bool STREAM_A = TM16 >= TN16;
-    constexpr int NO = STREAM_A ? TM16 : TN16;      // streamed fragments per k-step
-    constexpr int NI = STREAM_A ? TN16 : TM16;      // held fragments per k-step
-    const int s_rd = STREAM_A ? a_rd : b_rd, h_rd = STREAM_A ? b_rd : a_rd;
-    const int coff0 = (lhi ^ sw) << 4, coff1 = ((4 + lhi) ^ sw) << 4;
-    bf16x8 hf[2][NI], sf[4];
-    auto read_streamed = [&](int r) {   // row r of the 2 * NO rows of this slice
-      return *reinterpret_cast<const bf16x8*>(cur + s_rd + (r % NO) * 16 * 128 + (r < NO ? coff0 : coff1));
-    };
-#pragma unroll
-    for (int j = 0; j < NI; ++j) hf[0][j] = *reinterpret_cast<const bf16x8*>(cur + h_rd + j * 16 * 128 + coff0);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) sf[r] = read_streamed(r);
-#pragma unroll
-    for (int r = 0; r < 2 * NO; ++r) {
-      const int ks = r / NO, o = r % NO;
-#pragma unroll
-      for (int in = 0; in < NI; ++in) {
-        const int n = o * NI + in;
-        const int i = STREAM_A ? o : in, j = STREAM_A ? in : o;
-        const int quarter = 2 * (i & 1) + (j & 1);
-        const bf16x8 fa = STREAM_A ? sf[r & 3] : hf[ks][in], fw = STREAM_A ? hf[ks][in] : sf[r & 3];
-        f32x4 c;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[e] = acc[i >> 1][j >> 1][4 * quarter + e];
-        if (W_FIRST) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fa, c, 0, 0, 0);
-        else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fw, c, 0, 0, 0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i >> 1][j >> 1][4 * quarter + e] = c[e];
-        if (PREFETCH && ks == 0) {
-          constexpr int LT = A_LOADS + B_LOADS, SLOTS = NO * NI;
-#pragma unroll
-          for (int l = 0; l < LT; ++l)
-            if (l * SLOTS / LT == n) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(ap, bp, l, kn, nxt, wave);
-        }
-        if (in == 0 && r + 3 < 2 * NO) sf[(r + 3) & 3] = read_streamed(r + 3);
-        if (ks == 0 && n < NI) hf[1][n] = *reinterpret_cast<const bf16x8*>(cur + h_rd + n * 16 * 128 + coff1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    return;
-  }
-  bf16x8 af[2][TM], bfr[2][TN];
-  {
-    const int coff = (lhi ^ sw) << 4;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[0][i] = *reinterpret_cast<const bf16x8*>(cur + a_rd + i * 32 * 128 + coff);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bfr[0][j] = *reinterpret_cast<const bf16x8*>(cur + b_rd + j * 32 * 128 + coff);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    // MFMAs of k-step ks in source order, two LDS reads of k-step ks+1 behind each of the first
-    // ones; the scheduling barriers keep the compiler from regrouping them, so the reads'
-    // latency is covered by the MFMAs that follow.
-    const int coff = (((ks + 1) * 2 + lhi) ^ sw) << 4;
-#pragma unroll
-    for (int n = 0; n < TM * TN; ++n) {
-      const int i = n / TN, j = n % TN;
-      if (W_FIRST)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
-      else
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks & 1][i], bfr[ks & 1][j], acc[i][j], 0, 0, 0);
-      if (PREFETCH && ks < SPREAD_KS) {
-        constexpr int LT = A_LOADS + B_LOADS, SLOTS = SPREAD_KS * TM * TN;
-#pragma unroll
-        for (int l = 0; l < LT; ++l)
-          if (l * SLOTS / LT == ks * TM * TN + n) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(ap, bp, l, kn, nxt, wave);
-      }
-      if (ks < 3) {
-#pragma unroll
-        for (int q = RD_PER * n; q < RD_PER * n + RD_PER && q < TM + TN; ++q) {
-          if (q == 0) af[(ks + 1) & 1][0] = *reinterpret_cast<const bf16x8*>(cur + a_rd + coff);
-          else if (q <= TN) bfr[(ks + 1) & 1][q - 1] = *reinterpret_cast<const bf16x8*>(cur + b_rd + (q - 1) * 32 * 128 + coff);
-          else af[(ks + 1) & 1][q - TN] = *reinterpret_cast<const bf16x8*>(cur + a_rd + (q - TN) * 32 * 128 + coff);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-}
-
-// The K loop.  On return the stage buffer that does not hold the last slice is idle: every wave
-// passed the last barrier after reading it and nothing was loaded into it since.
-// before_last() runs between the last barrier and the last slice's MFMAs: global loads it issues
-// are in flight while those execute.
+// The K loop, pipelined across the slices: every LDS read is issued three fragment rows of MFMAs ahead of its use,
+// also over the boundary of a slice, and a slice has one barrier, three rows before its end.  (With the barrier
+// between the slices all waves met there with nothing to multiply, then waited out the latency of the first reads
+// together: ......)
+// W_FIRST: accumulate C^T blocks (lane = row m, registers = columns n); otherwise C blocks (lane = column n,
+// registers = rows m).
+// On return the stage buffer that does not hold the last slice is idle: every wave passed the last barrier after
+// reading it and nothing was loaded into it since.
+// before_last() runs ahead of the last slice's MFMAs: global loads it issues are in flight while those execute.
+//
+// Fragment i of A (16 rows) pairs with fragment j of W into quarter 2 (i % 2) + j % 2 of block (i / 2, j / 2).  The
+// operand with fewer fragments per wave is held for a k-step of 32 (double-buffered over the two k-steps of a slice);
+// the other is streamed through a ring of registers, row r of the 2 NO rows of a slice requested at row r - 3.
+// The loads of slice s + STAGES go out one at a time between MFMAs, from the barrier of slice s (which frees that
+// slice's buffer) to the middle of the first k-step of slice s + 1: in one burst they queue in the texture-address
+// unit (16 clocks each, all waves at once) and every wave sits in the issue stall.
 template <int BM, int BN, int WGM, int WGN, bool W_FIRST, int STAGES, typename F>
 __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem, int m0, int n0,
-                                          f32x16 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32], F&& before_last) {
+                                          f32x4 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32][4], F&& before_last) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = (WN + 31) / 32;
   constexpr int STAGE_BYTES = (BM + BN) * 128;
   constexpr int NWAVES = WGM * WGN;
-  constexpr bool MFMA16 = use_mfma16<NWAVES, BM, BN>();
-  constexpr int A_LOADS = BM / (8 * NWAVES), B_LOADS = (BN + 8 * NWAVES - 1) / (8 * NWAVES);
+  constexpr int A_LOADS = BM / (8 * NWAVES), B_LOADS = (BN + 8 * NWAVES - 1) / (8 * NWAVES), LT = A_LOADS + B_LOADS;
   static_assert(BM % (8 * NWAVES) == 0 && BN % 8 == 0, "tile vs waves");
-  static_assert(WM % 32 == 0 && WN % (MFMA16 ? 16 : 32) == 0, "wave tile vs MFMA shape");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  static_assert(WM % 32 == 0 && WN % 16 == 0, "wave tile vs MFMA shape");
+  static_assert(STAGES >= 2 && STAGES <= 4 && 2 * LT < 64, "the waits below cover up to two newer slices; vmcnt is a 6-bit counter");
+  constexpr int TM16 = WM / 16, TN16 = WN / 16;   // a wave's columns may end in the middle of its last 32-block
+  constexpr bool STREAM_A = TM16 >= TN16;
+  constexpr int NO = STREAM_A ? TM16 : TN16;      // streamed fragments per k-step
+  constexpr int NI = STREAM_A ? TN16 : TM16;      // held fragments per k-step
+  constexpr int ROWS = 2 * NO, SYNC_ROW = ROWS - 3;
+  constexpr int RING = ROWS % 4 == 0 ? 4 : 5;     // divides ROWS: a row sits in the same registers in every slice
+  static_assert(ROWS % RING == 0 && SYNC_ROW >= 1, "fragment ring");
+  constexpr int HEAD_ROWS = STAGES == 2 && NO < 8 ? 0 : NO / 2, SLOTS = (3 + HEAD_ROWS) * NI;   // MFMAs over which a slice's loads are spread
+  constexpr int L0 = (3 * NI * LT + SLOTS - 1) / SLOTS;             // ... the first so many in the slice that frees the buffer
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int M = g.M, N = g.N, K = g.K;
-  // the lane's row inside an operand fragment (32 rows, or 16 for the 16x16x32 shape) and its 16-byte
-  // piece of a k-step; sw = the row's share of the LDS chunk swizzle
-  const int lrow = MFMA16 ? (lane & 15) : (lane & 31), lhi = MFMA16 ? (lane >> 4) : (lane >> 5);
+  // the lane's row inside an operand fragment and its 16-byte piece of a k-step; sw = the row's share of the LDS
+  // chunk swizzle
+  const int lrow = lane & 15, lhi = lane >> 4;
   const int a_rd = (wm * WM + lrow) * 128;
   const int b_rd = BM * 128 + (wn * WN + lrow) * 128;
   const int sw = (lrow >> 1) & 7;
+  const int s_rd = STREAM_A ? a_rd : b_rd, h_rd = STREAM_A ? b_rd : a_rd;
+  const int coff0 = (lhi ^ sw) << 4, coff1 = ((4 + lhi) ^ sw) << 4;
 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int lr = lane >> 3;  // row inside an 8-row group
-  const bf16_t* ap[A_LOADS];
-  const bf16_t* bp[B_LOADS];
+  Operands<A_LOADS, B_LOADS> op;
+  op.a = g.A + (int64_t)m0 * g.lda;
+  op.w = g.W + (int64_t)n0 * g.ldw;
 #pragma unroll
   for (int i = 0; i < A_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;  // row inside the tile
-    int r = m0 + rt;
-    r = r < M ? r : M - 1;
-    ap[i] = g.A + (int64_t)r * g.lda + (((lane & 7) ^ ((rt >> 1) & 7)) << 3);
+    const int r = m0 + rt < M ? rt : M - 1 - m0;
+    op.a_off[i] = (uint32_t)r * (uint32_t)(g.lda * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
   }
 #pragma unroll
   for (int i = 0; i < B_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;
-    int r = n0 + rt;
-    r = r < N ? r : N - 1;
-    bp[i] = g.W + (int64_t)r * g.ldw + (((lane & 7) ^ ((rt >> 1) & 7)) << 3);
+    const int r = n0 + rt < N ? rt : N - 1 - n0;
+    op.b_off[i] = (uint32_t)r * (uint32_t)(g.ldw * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
   }
   const int KT = K >> 6;
-  if constexpr (STAGES > 2) {
-    // Slices kt + 1 .. kt + STAGES - 2 stay in flight while slice kt is consumed.  A wave's loads complete in the
-    // order it issued them, so waiting until at most n * L of them are outstanding (L = its loads per slice) means
-    // everything older than the newest n slices has landed.
-    const int L = A_LOADS + (BN % (8 * NWAVES) == 0 || ((B_LOADS - 1) * NWAVES + wave) * 8 < BN ? B_LOADS : B_LOADS - 1);
-    static_assert(STAGES <= 4, "the waits below cover up to two slices in flight");
-    auto wait_newer = [&](int n) {   // n newer slices may still be in flight
-      if (n <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      else if (L == A_LOADS + B_LOADS) {
-        if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_LOADS + B_LOADS) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (A_LOADS + B_LOADS)) : "memory");
-      } else {
-        if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(A_LOADS + B_LOADS - 1) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (A_LOADS + B_LOADS - 1)) : "memory");
-      }
-    };
-    static_assert(2 * (A_LOADS + B_LOADS) < 64, "vmcnt is a 6-bit counter");
-#pragma unroll
-    for (int st = 0; st < STAGES - 1; ++st)
-      if (st < KT) issue_slice<A_LOADS, B_LOADS, NWAVES, BM, BN>(ap, bp, st, smem + st * STAGE_BYTES, wave);
-    int cur_s = 0;                     // stage of slice kt
-    for (int kt = 0; kt < KT - 1; ++kt) {
-      const int ahead = KT - 1 - kt < STAGES - 2 ? KT - 1 - kt : STAGES - 2;   // newer slices already requested
-      wait_newer(ahead);               // this wave's part of slice kt has landed
-      // ... and everyone's; slice kt-1 fully consumed, so its stage is free.  A bare barrier: __syncthreads()
-      // carries a fence that waits for every outstanding load, the newer slices' included.
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      const unsigned char* cur = smem + cur_s * STAGE_BYTES;
-      const int nxt_s = cur_s == 0 ? STAGES - 1 : cur_s - 1;   // the stage slice kt-1 was in = that of slice kt + STAGES - 1
-      if (kt + STAGES - 1 < KT)
-        k_slice<BM, BN, WGM, WGN, W_FIRST, true>(ap, bp, kt + STAGES - 1, cur, smem + nxt_s * STAGE_BYTES, a_rd, b_rd, sw, lhi, wave, acc);
-      else
-        k_slice<BM, BN, WGM, WGN, W_FIRST, false>(ap, bp, 0, cur, nullptr, a_rd, b_rd, sw, lhi, wave, acc);
-      cur_s = cur_s + 1 == STAGES ? 0 : cur_s + 1;
+
+  // A wave's loads complete in the order it issued them: at most n * L of them outstanding (L = its loads per slice)
+  // means that everything older than the newest n slices has landed.
+  const bool all_loads = BN % (8 * NWAVES) == 0 || ((B_LOADS - 1) * NWAVES + wave) * 8 < BN;
+  auto wait_newer = [&](int n) {
+    if (n <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (all_loads) {
+      if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LT) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LT) : "memory");
+    } else {
+      if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LT - 1) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (LT - 1)) : "memory");
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    before_last();
-    k_slice<BM, BN, WGM, WGN, W_FIRST, false>(ap, bp, 0, smem + ((KT - 1) % STAGES) * STAGE_BYTES, nullptr, a_rd, b_rd, sw, lhi,
-                                              wave, acc);
-    return;
+  };
+  // A bare barrier: __syncthreads() carries a fence that waits for every outstanding load, newer slices' included.
+  auto barrier = [&] {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  bf16x8 hf[2][NI], sf[RING];
+  auto read_streamed = [&](const unsigned char* stage, int r) {
+    return *reinterpret_cast<const bf16x8*>(stage + s_rd + (r % NO) * 16 * 128 + (r < NO ? coff0 : coff1));
+  };
+  // One slice in `cur`.  HEAD: it issues the rest of the loads of slice kt_head into `head`; SYNC: it waits for the
+  // next slice (in `nxt`; `newer` slices behind that one may still be in flight) and reads its first fragments;
+  // TAIL: behind that it issues the first loads of slice kt_tail into `cur`.
+  auto slice = [&](auto HEAD, auto SYNC, auto TAIL, int newer, unsigned char* cur, const unsigned char* nxt,
+                   unsigned char* head, int kt_head, int kt_tail) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      const int ks = r / NO, o = r % NO;
+      if constexpr (SYNC.value) {
+        if (r == SYNC_ROW) {
+          wait_newer(newer);   // this wave's part of the next slice has landed
+          barrier();           // ... and everyone's; nobody reads this slice's buffer any more
+        }
+      }
+#pragma unroll
+      for (int in = 0; in < NI; ++in) {
+        const int i = STREAM_A ? o : in, j = STREAM_A ? in : o;
+        const bf16x8 fa = STREAM_A ? sf[r % RING] : hf[ks][in], fw = STREAM_A ? hf[ks][in] : sf[r % RING];
+        f32x4& c = acc[i >> 1][j >> 1][2 * (i & 1) + (j & 1)];
+        if (W_FIRST) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fa, c, 0, 0, 0);
+        else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fw, c, 0, 0, 0);
+        const int slot = r >= SYNC_ROW ? (r - SYNC_ROW) * NI + in : 3 * NI + r * NI + in;
+#pragma unroll
+        for (int l = 0; l < LT; ++l) {
+          if (l * SLOTS / LT != slot) continue;
+          if constexpr (TAIL.value) {
+            if (r >= SYNC_ROW) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, l, kt_tail, cur, wave);
+          }
+          if constexpr (HEAD.value) {
+            if (r < HEAD_ROWS) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, l, kt_head, head, wave);
+          }
+        }
+        if (in == 0) {
+          if (r + 3 < ROWS) sf[(r + 3) % RING] = read_streamed(cur, r + 3);
+          else if constexpr (SYNC.value) sf[(r + 3) % RING] = read_streamed(nxt, r + 3 - ROWS);
+        }
+        if (r == 0) hf[1][in] = *reinterpret_cast<const bf16x8*>(cur + h_rd + in * 16 * 128 + coff1);
+        if constexpr (SYNC.value) {
+          if (r == SYNC_ROW) hf[0][in] = *reinterpret_cast<const bf16x8*>(nxt + h_rd + in * 16 * 128 + coff0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  // the first STAGES - 1 slices, and of the next one the loads that a slice's tail would have issued
+#pragma unroll
+  for (int st = 0; st < STAGES - 1; ++st)
+    if (st < KT) issue_slice<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, st, smem + st * STAGE_BYTES, wave);
+  if (STAGES - 1 < KT) {
+#pragma unroll
+    for (int l = 0; l < L0; ++l) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, l, STAGES - 1, smem + (STAGES - 1) * STAGE_BYTES, wave);
   }
-  issue_slice<A_LOADS, B_LOADS, NWAVES, BM, BN>(ap, bp, 0, smem, wave);
-  for (int kt = 0; kt < KT - 1; ++kt) {
-    const unsigned char* cur = smem + (kt & 1) * STAGE_BYTES;
-    unsigned char* nxt = smem + ((kt + 1) & 1) * STAGE_BYTES;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of slice kt has landed
-    __syncthreads();                                    // ... and everyone's; slice kt-1 fully consumed
-    k_slice<BM, BN, WGM, WGN, W_FIRST, true>(ap, bp, kt + 1, cur, nxt, a_rd, b_rd, sw, lhi, wave, acc);
+  // slice 0 has landed (everything, where a short K loop issued less than the pipeline holds)
+  if (KT < STAGES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  else if (all_loads) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 2) * LT + L0) : "memory");
+  else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 2) * (LT - 1) + (L0 < LT ? L0 : LT - 1)) : "memory");
+  barrier();
+#pragma unroll
+  for (int in = 0; in < NI; ++in) hf[0][in] = *reinterpret_cast<const bf16x8*>(smem + h_rd + in * 16 * 128 + coff0);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) sf[r] = read_streamed(smem, r);
+
+  constexpr bool_tag<true> YES{};
+  constexpr bool_tag<false> NO_{};
+  int s = 0, stage = 0;   // slice, and the buffer it is in
+  auto next_of = [&](int st) { return st + 1 == STAGES ? 0 : st + 1; };
+  auto prev_of = [&](int st) { return st == 0 ? STAGES - 1 : st - 1; };   // of slice s - 1, and of slice s - 1 + STAGES
+  for (; s + STAGES < KT; ++s) {
+    const int nx = next_of(stage);
+    slice(YES, YES, YES, STAGES - 2, smem + stage * STAGE_BYTES, smem + nx * STAGE_BYTES, smem + prev_of(stage) * STAGE_BYTES,
+          s - 1 + STAGES, s + STAGES);
+    stage = nx;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
+  if (KT >= STAGES) {   // s == KT - STAGES: the loads of the last slice are still to be completed
+    const int nx = next_of(stage);
+    slice(YES, YES, NO_, STAGES - 2, smem + stage * STAGE_BYTES, smem + nx * STAGE_BYTES, smem + prev_of(stage) * STAGE_BYTES, KT - 1, 0);
+    stage = nx;
+    ++s;
+  }
+  if constexpr (STAGES > 2) {
+    for (; s < KT - 1; ++s) {
+      const int nx = next_of(stage);
+      slice(NO_, YES, NO_, KT - 2 - s, smem + stage * STAGE_BYTES, smem + nx * STAGE_BYTES, nullptr, 0, 0);
+      stage = nx;
+    }
+  }
   before_last();
-  k_slice<BM, BN, WGM, WGN, W_FIRST, false>(ap, bp, 0, smem + ((KT - 1) & 1) * STAGE_BYTES, nullptr, a_rd, b_rd, sw, lhi,
-                                            wave, acc);
+  slice(NO_, NO_, NO_, 0, smem + stage * STAGE_BYTES, nullptr, nullptr, 0, 0);
 }
 
-template <int V>
-struct int_tag { static constexpr int value = V; };
 
 // A 64-row tile for the rows behind the last full tile row exists when every wave can own whole
 // 32-column blocks of it (and the epilogue has no pairing of column blocks).
 template <int BN, int WGM, int WGN, int EPI>
 constexpr bool light_tail() {
   constexpr int WN = BN / (WGM * WGN);                           // columns per wave of the 64-row tile
-  constexpr int UNIT = use_mfma16<WGM * WGN>() ? 16 : 32;          // (a 16x16x32 wave may own half a 32-column block)
-  return EPI != EPI_SWIGLU_BF16 && WN % UNIT == 0 && WN >= UNIT && (EPI != EPI_QKV || WN % 32 == 0);
+  return EPI != EPI_SWIGLU_BF16 && WN % 16 == 0 && WN >= 16 && (EPI != EPI_QKV || WN % 32 == 0);   // (a wave may own half a 32-column block)
 }
 
 // One output tile: K loop and epilogue.
 // LDS_ALLOC: bytes of LDS the launch has (that of its largest tile shape).
-template <int BM, int BN, int WGM, int WGN, int EPI, int LDS_ALLOC = tile_lds_bytes<BM, BN, WGM * WGN, EPI>(), int STAGES_ARG = 0>
+template <int BM, int BN, int WGM, int WGN, int EPI, int STAGES, int LDS_ALLOC>
 __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem, const int m0, const int n0) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = (WN + 31) / 32;
   constexpr int STAGE_BYTES = (BM + BN) * 128;
   constexpr int NWAVES = WGM * WGN;
-  constexpr bool MFMA16 = use_mfma16<NWAVES, BM, BN>();
   static_assert((EPI != EPI_SWIGLU_BF16 && EPI != EPI_QKV) || WN % 32 == 0, "these epilogues work on whole 32-column blocks");
   static_assert(EPI != EPI_SWIGLU_BF16 || (TN % 2 == 0), "gate/up pairs need an even number of column tiles");
-  static_assert(EPI != EPI_QKV || (TM % 2 == 0), "v tiles leave through LDS two row blocks at a time");
   // the epilogue chunks live in the idle stage buffer; where that is too small for them (a 64-row tail tile of a
   // narrow launch) they go behind everything else this tile uses, inside what the launch's main tile shape allocated
-  constexpr bool CHUNKS_BEHIND = NWAVES * CHUNK_BYTES > STAGE_BYTES;
+  // (of four stages two neighbouring ones are idle whichever holds the last slice)
+  constexpr bool CHUNKS_IN_TWO = STAGES == 4 && NWAVES * CHUNK_BYTES > STAGE_BYTES && NWAVES * CHUNK_BYTES <= 2 * STAGE_BYTES;
+  constexpr bool CHUNKS_BEHIND = NWAVES * CHUNK_BYTES > STAGE_BYTES && !CHUNKS_IN_TWO;
   constexpr int XTRA = extra_lds_bytes<BM, BN, NWAVES, EPI>();
-  constexpr int STAGES = STAGES_ARG ? STAGES_ARG : stages<BM, BN, NWAVES, EPI>();
-  // (QKV: behind the K loop the rotary table and the chunks above it take the space of the first two stage buffers)
+  // (QKV: behind the K loop the rotary table and the chunks above it take the space of the stage buffers)
   static_assert(!CHUNKS_BEHIND || (STAGES * STAGE_BYTES + XTRA + NWAVES * CHUNK_BYTES <= LDS_ALLOC && EPI != EPI_QKV),
                 "no room for the epilogue chunks");
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int M = g.M, N = g.N;
   // The extra LDS behind the stage buffers.  Consumer of a folded normalisation: BM row scales, BM row shifts
@@ -573,10 +535,11 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
     __syncthreads();
   };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN][4];
   // this wave's epilogue chunk, in the stage buffer the last K slice did not use
   unsigned char* chunk = CHUNKS_BEHIND ? smem + STAGES * STAGE_BYTES + XTRA + wave * CHUNK_BYTES
-                                       : smem + ((g.K >> 6) % STAGES) * STAGE_BYTES + wave * CHUNK_BYTES;
+                         : CHUNKS_IN_TWO ? smem + (((g.K >> 6) - 1) % STAGES < 2 ? 2 * STAGE_BYTES : 0) + wave * CHUNK_BYTES
+                                         : smem + ((g.K >> 6) % STAGES) * STAGE_BYTES + wave * CHUNK_BYTES;
 
   if constexpr (EPI == EPI_QKV) {
     if (n0 >= 2 * g.hidden) {
@@ -584,42 +547,43 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
       // group holds one v dimension n (the block "row" here) and four consecutive tokens; written as
       // rows of the transposed v buffer, 64 tokens of one dimension per chunk row.  With the roles of
       // the operands swapped the two halves of a 16x16x32 group index swap too (vsub).
+      constexpr int VB = TM % 2 == 0 ? 2 : 1;   // row blocks of 32 tokens that leave together
       float bv[TN][4];
       main_loop<BM, BN, WGM, WGN, false, STAGES>(g, smem, m0, n0, acc, [&] {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const int n = n0 + wn * WN + j * 32 + blk_row<MFMA16>(q, lane);
+            const int n = n0 + wn * WN + j * 32 + blk_row(q, lane);
             bv[j][q] = (g.bias && n < N) ? g.bias[n] : 0.f;
           }
         gather_scale();
       });
       publish_scale();
       const bool wide = (g.ld_vt & 7) == 0;
-      const bool wt_v = lines_exclusive(g.vt, g.ld_vt * 2);   // a workgroup writes 512-byte runs of a v^T row
+      const bool wt_v = lines_exclusive(g.vt, g.ld_vt * 2);   // a workgroup writes runs of 128 bytes or more of a v^T row
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
 #pragma unroll
-        for (int i = 0; i < TM; i += 2) {
-          f32x4 v[2][4];
+        for (int i = 0; i < TM; i += VB) {
+          f32x4 v[VB][4];
 #pragma unroll
-          for (int ii = 0; ii < 2; ++ii)
+          for (int ii = 0; ii < VB; ++ii)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const int vsub = MFMA16 ? (((q & 1) << 1) | (q >> 1)) : q;
+              const int vsub = ((q & 1) << 1) | (q >> 1);
               // the group's four values are four consecutive tokens: their row scales
               f32x4 rs = {1.f, 1.f, 1.f, 1.f}, sh = {0.f, 0.f, 0.f, 0.f};
               float cn = 0.f;   // LayerNorm: the shift of this v dimension
-              if (g.ss_in) rs = *reinterpret_cast<const f32x4*>(extra_lds + wm * WM + (i + ii) * 32 + blk_col<MFMA16>(q, lane));
+              if (g.ss_in) rs = *reinterpret_cast<const f32x4*>(extra_lds + wm * WM + (i + ii) * 32 + blk_col(q, lane));
               if (layer_norm) {
-                sh = *reinterpret_cast<const f32x4*>(extra_lds + BM + wm * WM + (i + ii) * 32 + blk_col<MFMA16>(q, lane));
-                cn = extra_lds[2 * BM + wn * WN + j * 32 + blk_row<MFMA16>(q, lane)];
+                sh = *reinterpret_cast<const f32x4*>(extra_lds + BM + wm * WM + (i + ii) * 32 + blk_col(q, lane));
+                cn = extra_lds[2 * BM + wn * WN + j * 32 + blk_row(q, lane)];
               }
 #pragma unroll
-              for (int e = 0; e < 4; ++e) v[ii][q][e] = acc[i + ii][j][4 * vsub + e] * rs[e] - sh[e] * cn + bv[j][q];
+              for (int e = 0; e < 4; ++e) v[ii][q][e] = acc[i + ii][j][vsub][e] * rs[e] - sh[e] * cn + bv[j][q];
             }
-          store_block<2, bf16_t, false, MFMA16>(chunk, v, g.vt, g.ld_vt, nullptr, n0 + wn * WN + j * 32 - 2 * g.hidden,
+          store_block<VB, bf16_t, false>(chunk, v, g.vt, g.ld_vt, nullptr, n0 + wn * WN + j * 32 - 2 * g.hidden,
                                         N - 2 * g.hidden, m0 + wm * WM + i * 32, M, wide, wt_v);
         }
       }
@@ -628,21 +592,17 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   }
 
   // Residual add: the old values are needed in the epilogue, where a load's latency would be
-  // paid once per chunk (the stores in between keep the compiler from hoisting the loads).  With
-  // four waves per workgroup (one per SIMD, or small tiles) the registers for the whole wave tile
-  // are free, so every lane fetches the 16-byte pieces it will update before the last K slice.
-  // With eight waves there is room for one row block before the last K slice; the second row block is
+  // paid once per chunk (the stores in between keep the compiler from hoisting the loads), so every lane fetches
+  // the 16-byte pieces it will update ahead of their use.
+  // There is room for one row block before the last K slice; the second row block is
   // requested right behind the K loop, into the registers the operands leave, and from then on the pieces of
   // row block i + 2 are requested as soon as those of row block i are stored (into the same registers), so two
   // row blocks of x are in flight all through the epilogue (the narrow tiles: out projection 559 -> 575, down
   // projection 838 -> 870 TFLOP/s on 8192 tokens; the 256 x 256 tile, whose four row blocks per wave leave no
   // registers for it, stays with one: with two it spills more and gains nothing).
   constexpr bool RESADD = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SCALED_F32 || EPI == EPI_RESADD_SUMS_F32;
-  constexpr bool TWO_PER_SIMD = NWAVES > 4 || (BM == 128 && BN == 160);   // 256 registers per wave, not 512
-  constexpr bool HOLD = RESADD && !TWO_PER_SIMD;
-  constexpr bool HOLD_ROW = RESADD && TWO_PER_SIMD;
-  constexpr bool HOLD_TWO = HOLD_ROW && TM > 1 && BN < 256;
-  [[maybe_unused]] f32x4 held[HOLD ? TM : HOLD_TWO ? 2 : 1][(HOLD || HOLD_ROW) ? TN : 1][4];
+  constexpr bool HOLD_TWO = RESADD && TM > 1 && BN < 256;
+  [[maybe_unused]] f32x4 held[HOLD_TWO ? 2 : 1][RESADD ? TN : 1][4];
   [[maybe_unused]] auto fetch_old = [&](int i, int j, f32x4 (&dst)[4]) {
     const int r = lane >> 3, c = (lane & 7) * 4;
     int n = n0 + wn * WN + j * 32 + c;
@@ -661,8 +621,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   };
   // The bias of the lane's columns is fetched there too (a load inside the epilogue waits out its
   // latency once per chunk).
-  // (with the 16x16x32 shape groups q and q + 2 hold the same columns: two distinct column groups per block)
-  constexpr int CQ = MFMA16 ? 2 : 4;
+  // (groups q and q + 2 hold the same columns: two distinct column groups per block)
+  constexpr int CQ = 2;
   f32x4 bias_r[TN][CQ];
   [[maybe_unused]] f32x4 scale_r[EPI == EPI_RESADD_SCALED_F32 ? TN : 1][CQ];
   main_loop<BM, BN, WGM, WGN, true, STAGES>(g, smem, m0, n0, acc, [&] {
@@ -670,7 +630,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int q = 0; q < CQ; ++q) {
-        const int n = n0 + wn * WN + j * 32 + blk_col<MFMA16>(q, lane);
+        const int n = n0 + wn * WN + j * 32 + blk_col(q, lane);
         bias_r[j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (g.bias && n < N) bias_r[j][q] = *reinterpret_cast<const f32x4*>(g.bias + n);
         if constexpr (EPI == EPI_RESADD_SCALED_F32) {
@@ -678,12 +638,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
           if (n < N) scale_r[j][q] = *reinterpret_cast<const f32x4*>(g.col_scale + n);
         }
       }
-    if constexpr (HOLD) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fetch_old(i, j, held[i][j]);
-    } else if constexpr (HOLD_ROW) {
+    if constexpr (RESADD) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) fetch_old(0, j, held[0][j]);
     }
@@ -725,7 +680,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
       const int cpr = half >> 1;                       // 16-byte pieces per token row (two pairs each)
       const int upr = (cpr + 1) | 1;                   // ... per padded LDS row: odd, so rows spread over the banks
       rope_stride = upr * 16;
-      chunk = smem + 2 * STAGE_BYTES - (NWAVES - wave) * CHUNK_BYTES;
+      chunk = smem + STAGES * STAGE_BYTES - (NWAVES - wave) * CHUNK_BYTES;
+      static_assert((BM * 21 + 64) * 16 + NWAVES * CHUNK_BYTES <= STAGES * STAGE_BYTES, "rotary table and chunks");
       __syncthreads();                                 // every wave is done reading the last K slice
       // LDS-direct loads, all in flight at once: piece u of the padded table comes from row u / upr
       // (the padding pieces repeat the row's last one; the tail of the last instruction runs up to
@@ -760,7 +716,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int q = 0; q < CQ; ++q) {
-        const int n = nw + j * 32 + blk_col<MFMA16>(q, lane);
+        const int n = nw + j * 32 + blk_col(q, lane);
         rope_off[j][q] = ((((n < g.hidden ? n : n - g.hidden)) % g.head_dim) >> 1) * 8;
       }
   }
@@ -774,13 +730,13 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
     if constexpr (CONSUMES_NORM) {
       if (g.ss_in) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) rsq[q] = extra_lds[mrow - m0 + blk_row<MFMA16>(q, lane)];
+        for (int q = 0; q < 4; ++q) rsq[q] = extra_lds[mrow - m0 + blk_row(q, lane)];
       }
     }
     if constexpr (CONSUMES_LAYERNORM) {
       if (layer_norm) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) msq[q] = extra_lds[BM + mrow - m0 + blk_row<MFMA16>(q, lane)];
+        for (int q = 0; q < 4; ++q) msq[q] = extra_lds[BM + mrow - m0 + blk_row(q, lane)];
       }
     }
     // ... producer side: sums of squares of the updated rows, gathered by the residual store
@@ -798,9 +754,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
             const f32x4 bg = bias_r[j][q % CQ], bu = bias_r[j + 1][q % CQ];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              v[b][q][e] = silu_f(acc[i][j][4 * q + e] * rsq[q] + bg[e]) * (acc[i][j + 1][4 * q + e] * rsq[q] + bu[e]);
+              v[b][q][e] = silu_f(acc[i][j][q][e] * rsq[q] + bg[e]) * (acc[i][j + 1][q][e] * rsq[q] + bu[e]);
           }
-        store_block<NB, bf16_t, false, MFMA16>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M,
+        store_block<NB, bf16_t, false>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M,
                                        (nw >> 1) + p0 * 32, N >> 1, wide, wt);
       };
       constexpr int NP = TN / 2;
@@ -817,10 +773,10 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int j = j0 + b;
-            const int n = nw + j * 32 + blk_col<MFMA16>(q, lane);
+            const int n = nw + j * 32 + blk_col(q, lane);
             f32x4 t;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) t[e] = acc[i][j][4 * q + e];
+            for (int e = 0; e < 4; ++e) t[e] = acc[i][j][q][e];
             if constexpr (CONSUMES_NORM && EPI != EPI_SWIGLU_BF16) t *= rsq[q];
             if constexpr (CONSUMES_LAYERNORM) {
               if (layer_norm) t -= msq[q] * *reinterpret_cast<const f32x4*>(extra_lds + 2 * BM + (n - n0));
@@ -834,7 +790,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
             if constexpr (EPI == EPI_QKV) {
               // q and k columns: rotary on neighbouring columns (2p, 2p+1), both held by this lane
               if (g.rope_cs) {
-                const f32x4 cs = *reinterpret_cast<const f32x4*>(smem + (mrow - m0 + blk_row<MFMA16>(q, lane)) * rope_stride + rope_off[j][q % CQ]);  // cos,sin,cos,sin
+                const f32x4 cs = *reinterpret_cast<const f32x4*>(smem + (mrow - m0 + blk_row(q, lane)) * rope_stride + rope_off[j][q % CQ]);  // cos,sin,cos,sin
                 const float r0 = t[0] * cs[0] - t[1] * cs[1], r1 = t[1] * cs[0] + t[0] * cs[1];
                 const float r2 = t[2] * cs[2] - t[3] * cs[3], r3 = t[3] * cs[2] + t[2] * cs[3];
                 t[0] = r0; t[1] = r1; t[2] = r2; t[3] = r3;
@@ -845,22 +801,22 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
           }
         const int col0 = nw + j0 * 32;
         if constexpr (RESADD) {
-          store_block<NB, float, true, MFMA16, FOLDS_SUMS>(chunk, v, static_cast<float*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, true,
+          store_block<NB, float, true, FOLDS_SUMS>(chunk, v, static_cast<float*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, true,
                                        wt && CS_GEMM_RESADD_WT && !g.plain_stores,
-                                       HOLD ? held[i][j0] : HOLD_TWO ? held[i & 1][j0] : HOLD_ROW ? held[0][j0] : nullptr,
+                                       HOLD_TWO ? held[i & 1][j0] : held[0][j0],
                                        folding ? &fold : nullptr);
           if constexpr (HOLD_TWO) {
             if (i + 2 < TM) fetch_old(i + 2, j0, held[i & 1][j0]);
-          } else if constexpr (HOLD_ROW) {
+          } else {
             if (i + 1 < TM) fetch_old(i + 1, j0, held[0][j0]);
           }
         } else if constexpr (OUT_F32) {
-          store_block<NB, float, false, MFMA16>(chunk, v, static_cast<float*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, true, wt);
+          store_block<NB, float, false>(chunk, v, static_cast<float*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, true, wt);
         } else if constexpr (EPI == EPI_QKV) {
-          store_block<NB, bf16_t, false, MFMA16>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M, col0,
+          store_block<NB, bf16_t, false>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M, col0,
                                          2 * g.hidden, wide, wt);
         } else {
-          store_block<NB, bf16_t, false, MFMA16>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, wide, wt);
+          store_block<NB, bf16_t, false>(chunk, v, static_cast<bf16_t*>(g.out), g.ldo, g.row_map, mrow, M, col0, n_end, wide, wt);
           if constexpr (EPI == EPI_GELU_SPLIT) {
             // second half of the row: what the bf16 rounding of the first half dropped
 #pragma unroll
@@ -870,7 +826,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
                 const bf16x4 h = __builtin_convertvector(v[b][q], bf16x4);
                 v[b][q] -= __builtin_convertvector(h, f32x4);
               }
-            store_block<NB, bf16_t, false, MFMA16>(chunk, v, static_cast<bf16_t*>(g.out) + N, g.ldo, g.row_map, mrow, M, col0, n_end,
+            store_block<NB, bf16_t, false>(chunk, v, static_cast<bf16_t*>(g.out) + N, g.ldo, g.row_map, mrow, M, col0, n_end,
                                            wide && (N & 7) == 0, wt && (N & 63) == 0);
           }
         }
@@ -961,22 +917,25 @@ __device__ __forceinline__ void tile_origin(int id, int tiles_m, int tiles_n, in
 }
 
 // LDS of a launch: that of its main tile, or what the deeper pipeline of its 64-row tail tiles needs.
-template <int BM, int BN, int NWAVES, int EPI, int TAIL>
+template <int BM, int BN, int NWAVES, int EPI, int TAIL, int STAGES>
 constexpr int launch_lds_bytes() {
-  const int main_tile = tile_lds_bytes<BM, BN, NWAVES, EPI>();
+  const int main_tile = tile_lds_bytes<BM, BN, NWAVES, EPI, STAGES>();
   if (TAIL != 1 /* TAIL_LIGHT */) return main_tile;
   const int light = light_lds_need<BN, NWAVES, EPI>(light_stages<BN, NWAVES, EPI>());
   return light > main_tile ? light : main_tile;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL>
+template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES>
 __global__ __launch_bounds__(64 * WGM * WGN)
 // (the four-wave 128 x 160 tile must leave room for a second workgroup on the CU: 256 registers, not 512)
-__attribute__((amdgpu_waves_per_eu(BM == 128 && BN == 160 ? 2 : 1))) void gemm_kernel(GemmArgs g) {
+__attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
-  if (gridDim.y > 1) {   // split K (plain fp32 partial sums only): this workgroup's part of A, W and of the output
-    g.A += (int64_t)blockIdx.y * g.K;
-    g.W += (int64_t)blockIdx.y * g.K;
+  constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL, STAGES>();
+  if (gridDim.y > 1) {   // split K (plain fp32 partial sums only): this workgroup's K slices of A and W, its partial sums
+    const int kt = g.K >> 6, first = (int)blockIdx.y * kt / (int)gridDim.y, last = ((int)blockIdx.y + 1) * kt / (int)gridDim.y;
+    g.A += (int64_t)first * 64;
+    g.W += (int64_t)first * 64;
+    g.K = (last - first) * 64;
     g.out = static_cast<float*>(g.out) + (int64_t)blockIdx.y * g.split_stride;
   }
   const int M = g.M, N = g.N;
@@ -1002,7 +961,7 @@ __attribute__((amdgpu_waves_per_eu(BM == 128 && BN == 160 ? 2 : 1))) void gemm_k
       tile_origin<BM, BN>(n_main + (t >> 1), tiles_m, tiles_n, m0, n0);
       m0 += (t & 1) * (BM / 2);
       if (m0 >= M) return;   // the lower half of a tile of a ragged last tile row may be empty
-      tile_body<BM / 2, BN, WGM, WGN, EPI, tile_lds_bytes<BM, BN, WGM * WGN, EPI>()>(g, smem, m0, n0);
+      tile_body<BM / 2, BN, WGM, WGN, EPI, 2, LDS>(g, smem, m0, n0);
       return;
     }
     nb = n_main;
@@ -1012,7 +971,7 @@ __attribute__((amdgpu_waves_per_eu(BM == 128 && BN == 160 ? 2 : 1))) void gemm_k
     if ((int)blockIdx.x >= n_main) {
       const int t = blockIdx.x - n_main;
       const int tail_m = (M - full_m * BM + 63) / 64;
-      tile_body<64, BN, 1, WGM * WGN, EPI, launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL>(), light_stages<BN, WGM * WGN, EPI>()>(
+      tile_body<64, BN, 1, WGM * WGN, EPI, light_stages<BN, WGM * WGN, EPI>(), LDS>(
           g, smem, full_m * BM + (t % tail_m) * 64, (t / tail_m) * BN);
       return;
     }
@@ -1030,7 +989,7 @@ __attribute__((amdgpu_waves_per_eu(BM == 128 && BN == 160 ? 2 : 1))) void gemm_k
   }
   int m0, n0;
   tile_origin<BM, BN>(bid, tiles_m, tiles_n, m0, n0);
-  tile_body<BM, BN, WGM, WGN, EPI>(g, smem, m0, n0);
+  tile_body<BM, BN, WGM, WGN, EPI, STAGES, LDS>(g, smem, m0, n0);
 }
 
 // Measurement switch: CS_GEMM_NO_TAIL_SPLIT=1 in the environment keeps whole tiles in the last round, so
@@ -1043,15 +1002,14 @@ static bool tail_split_off() {
   return off;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL>
+template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES>
 static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   constexpr int NT = 64 * WGM * WGN;
-  constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL>();
+  constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL, STAGES>();
   static_assert(LDS <= 160 * 1024, "LDS of a CU");
-  auto kern = gemm_kernel<BM, BN, WGM, WGN, EPI, TAIL>;
+  auto kern = gemm_kernel<BM, BN, WGM, WGN, EPI, TAIL, STAGES>;
   if (g.describe) {
-    snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d>%s", BM, BN, WGM, WGN, EPI, TAIL,
-             use_mfma16<WGM * WGN, BM, BN>() ? " 16x16x32" : " 32x32x16");
+    snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32", BM, BN, WGM, WGN, EPI, TAIL);
     return CS_OK;
   }
   // one attribute call per instantiation (two threads that both see `false` repeat a harmless call)
@@ -1081,42 +1039,19 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   return CS_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI>
+template <int BM, int BN, int WGM, int WGN, int EPI, int STAGES = default_stages<BM, BN, WGM * WGN>()>
 static cs_status launch_cfg(const GemmArgs& g, hipStream_t stream) {
   // the light-tail variant where the last, partly empty tile row is at least 1/64 of the tile rows
-  if constexpr (light_tail<BN, WGM, WGN, EPI>()) {
-    if (g.M % BM != 0 && (g.M + BM - 1) / BM <= 64) return launch_one<BM, BN, WGM, WGN, EPI, TAIL_LIGHT>(g, stream);
+  if constexpr (BM > 64 && light_tail<BN, WGM, WGN, EPI>()) {
+    if (g.M % BM != 0 && (g.M + BM - 1) / BM <= 64) return launch_one<BM, BN, WGM, WGN, EPI, TAIL_LIGHT, STAGES>(g, stream);
   }
   // half tiles for a last round that is at most half full (the big tile only: that is where a round is long)
   if constexpr (BM == 256 && BN == 256) {
     const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN), tail = tiles % CHIP_CUS;
     if (g.splits <= 1 && tiles > CHIP_CUS && tail > 0 && tail <= CHIP_CUS / 2 && !tail_split_off())
-      return launch_one<BM, BN, WGM, WGN, EPI, TAIL_SPLIT>(g, stream);
+      return launch_one<BM, BN, WGM, WGN, EPI, TAIL_SPLIT, STAGES>(g, stream);
   }
-  return launch_one<BM, BN, WGM, WGN, EPI, TAIL_NONE>(g, stream);
-}
-
-// Measurement switch: CS_GEMM_NARROW8 in the environment (read once) says when the 256 x 160 tile runs with
-// eight waves of 64 x 80 instead of four of 64 x 160 (and the 256 x 128 tile with eight of 64 x 64 instead of four
-// of 64 x 128): 0 never, 1 for long K loops, 2 (default) always.  Measured on the 8-image step: 11.92 / 11.88 /
-// 11.84 ms for 0 / 1 / 2.
-static int narrow8_mode() {
-  static const int mode = [] {
-    const char* v = getenv("CS_GEMM_NARROW8");
-    return v && *v >= '0' && *v <= '2' ? *v - '0' : 2;
-  }();
-  return mode;
-}
-
-// CS_GEMM_RESADD_PAIR in the environment (read once): 1 runs the residual GEMMs with N = 1280 on 128 x 160 tiles
-// of four waves, two workgroups per CU (independent of each other: one's barriers and epilogue run under the
-// other's MFMAs), instead of one eight-wave 256 x 160 tile per CU; 0 does not.
-static int resadd_pair_mode() {
-  static const int mode = [] {
-    const char* v = getenv("CS_GEMM_RESADD_PAIR");
-    return v && *v >= '0' && *v <= '1' ? *v - '0' : 0;
-  }();
-  return mode;
+  return launch_one<BM, BN, WGM, WGN, EPI, TAIL_NONE, STAGES>(g, stream);
 }
 
 // The fewest 256 x 256 tiles beyond one round of the chip for which a launch takes that tile: 257.  With the half
@@ -1149,9 +1084,46 @@ static bool narrow_resadd() {
   return on;
 }
 
+// Launches that fit one round of the chip: one workgroup per CU, several K slices in flight, and as many CUs at work as
+// the shape allows.  Such a launch waits for its operands: measured with weights that come from HBM, a slice takes the
+// times below whatever the number of workgroups (a lone CU draws 45 - 60 B/ns), so the smallest tile that still makes
+// at most one round is the fastest (256 x 3840 x 1280: 64 x 64 9.4 us, 64 x 128 12.8, 128 x 128 16.9, and 20.4 with two
+// slices in flight; 1024 x 3840 x 1280: 128 x 128 16.0, two per CU 20.2; 512 x 6912 x 1280: 17.2 against 23.0 for one
+// and a half rounds of 64 x 128).
+struct SmallTile {
+  int bm, bn;
+};
+static constexpr SmallTile SMALL_TILES[] = {{64, 64}, {64, 128}, {128, 128}, {128, 256}};
+enum { TILE_64 = 0, TILE_64x128, TILE_128, TILE_128x256, N_SMALL_TILES };
+
+// the first of those tiles from `first` on that makes at most one round of the chip, N_SMALL_TILES if none does
+static int small_tile(int64_t M, int64_t N, int64_t parts, int first) {
+  int t = first;
+  while (t < N_SMALL_TILES &&
+         ((M + SMALL_TILES[t].bm - 1) / SMALL_TILES[t].bm) * ((N + SMALL_TILES[t].bn - 1) / SMALL_TILES[t].bn) * parts > CHIP_CUS) ++t;
+  return t;
+}
+
 template <int EPI>
 static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   // Tile choice by the number of workgroups it yields for the 256 CUs.
+  constexpr bool RESADD = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SUMS_F32 || EPI == EPI_RESADD_SCALED_F32;
+  // At most one round of small tiles.  (A residual GEMM stays on tiles of which a row has at most eight, so that the
+  // next normalisation folds: N = 1280 on its 128 x 160 tiles below.)
+  if (!(RESADD && g.N % 160 == 0)) {
+    const int t = small_tile(g.M, g.N, g.splits > 1 ? g.splits : 1,
+                             EPI == EPI_SWIGLU_BF16 || (RESADD && g.N > 8 * 64) ? TILE_64x128 : TILE_64);
+    constexpr int SW = EPI == EPI_SWIGLU_BF16 ? 2 : 4;   // (gate | up pairs need 64 columns per wave)
+    if constexpr (EPI != EPI_SWIGLU_BF16) {
+      if (t == TILE_64) return launch_one<64, 64, 2, 2, EPI, TAIL_NONE, 4>(g, stream);
+    }
+    if (t == TILE_64x128) return launch_one<64, 128, 2, SW, EPI, TAIL_NONE, 4>(g, stream);
+    if (t == TILE_128) return launch_one<128, 128, 4, 2, EPI, TAIL_NONE, 4>(g, stream);
+    if constexpr (EPI != EPI_SWIGLU_BF16 && !RESADD) {
+      if (t == TILE_128x256 && (EPI != EPI_QKV || (2 * g.hidden) % 256 == 0))
+        return launch_one<128, 256, 2, 4, EPI, TAIL_NONE, 3>(g, stream);
+    }
+  }
   const int64_t tm = (g.M + 255) / 256;
   const int64_t big = tm * ((g.N + 255) / 256);
   const bool big_ok = EPI != EPI_QKV || (2 * g.hidden) % 256 == 0;
@@ -1172,31 +1144,18 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
     if (big >= (RES ? 384 : big_tile_min()) && big_ok && !narrow_first) return launch_cfg<256, 256, 2, 4, EPI>(g, stream);
   }
   if constexpr (EPI != EPI_QKV && EPI != EPI_SWIGLU_BF16) {
-    // narrow outputs (N = hidden = 1280): 256 x 160 tiles, four waves of 64 x 160, give M/256 * 8
-    // workgroups, one round of the chip at M = 8192
+    // narrow outputs (N = hidden = 1280): 256 x 160 tiles, eight waves of 64 x 80 (a wave's third 32-column block
+    // half used), give M/256 * 8 workgroups, one round of the chip at M = 8192
     if constexpr (EIGHT_WAVES_OK) {
       if (g.N % 160 == 0 && tm * (g.N / 160) >= 192) {
-#if CS_GEMM_MFMA16
-        if constexpr (EPI == EPI_RESADD_F32) {
-          if (resadd_pair_mode() == 1 && !g.s1_out) return launch_cfg<128, 160, 2, 2, EPI>(g, stream);
-        }
-        // eight waves of 64 x 80 (16x16x32 MFMAs, the wave's third 32-column block half used) where the K
-        // loop is long: their main loop is 8 % faster, but with two waves per SIMD the residual epilogue can
-        // prefetch only one row block of x at a time, which costs more than that at K = 1280 (measured:
-        // K = 3456 74 -> 71 us, K = 1280 36.4 -> 37.5 us)
-        if (narrow8_mode() == 2 || (narrow8_mode() == 1 && g.K >= 2560)) return launch_cfg<256, 160, 4, 2, EPI>(g, stream);
-#endif
-        return launch_cfg<256, 160, 4, 1, EPI>(g, stream);
+        return launch_cfg<256, 160, 4, 2, EPI>(g, stream);
       }
     }
     // the same for N = 1024: 256 x 128 tiles (eight waves of 64 x 64 leave room for the scaled residual epilogue too)
     // (not for N = 1280, which it would cut into ten column tiles, too many for the next normalisation to fold:
     // 5120 tokens, 9.73 -> 9.35 ms per step on the 128 x 160 tiles below)
     if (g.N % 128 == 0 && g.N % 160 != 0 && tm * (g.N / 128) >= 192) {
-#if CS_GEMM_MFMA16
-      if (narrow8_mode() == 2 || (narrow8_mode() == 1 && g.K >= 2560)) return launch_cfg<256, 128, 4, 2, EPI>(g, stream);
-#endif
-      return launch_cfg<256, 128, 4, 1, EPI>(g, stream);
+      return launch_cfg<256, 128, 4, 2, EPI>(g, stream);
     }
   }
   if constexpr (EIGHT_WAVES_OK) {
@@ -1204,7 +1163,6 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
     // 128 x 128 tiles; at 120 workgroups it loses)
     if (big >= 160 && big <= 256 && big_ok) return launch_cfg<256, 256, 2, 4, EPI>(g, stream);
   }
-#if CS_GEMM_MFMA16
   // a residual GEMM with N = 1280 too small for the tiles above: 128 x 160 tiles rather than 128 x 128, which makes
   // eight column tiles instead of ten, so the next normalisation still folds into it (vision tower, 4096 tokens:
   // 8.32 -> 7.77 ms per step; audio tower, 3000 tokens: 8.08 -> 7.94 ms).  Up to one tile per CU they run with eight waves of 32 x 80, so that every SIMD has two waves to
@@ -1218,7 +1176,6 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
       return launch_cfg<128, 160, 2, 2, EPI>(g, stream);
     }
   }
-#endif
   return launch_cfg<128, 128, 2, 2, EPI>(g, stream);
 }
 
@@ -1240,17 +1197,20 @@ int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, bool scaled, bool 
 cs_status launch_gemm(int epilogue, const GemmArgs& g_in, hipStream_t stream) {
   GemmArgs g = g_in;
   if (g.M <= 0 || g.N <= 0) return CS_OK;
-  if (g.ldw == 0) g.ldw = (int64_t)g.K * (g.splits > 1 ? g.splits : 1);
+  if (g.ldw == 0) g.ldw = g.K;
   if (g.ldw < g.K || (g.ldw & 7)) return fail(CS_ERR_INVALID_ARG, "gemm: ldw must be at least K and a multiple of 8");
-  if (g.splits > 1 && (epilogue != EPI_F32 || g.bias || g.row_map || g.splits > 16 ||
+  if (g.splits > 1 && (epilogue != EPI_F32 || g.bias || g.row_map || g.splits > 16 || g.splits > g.K >> 6 ||
                        g.split_stride < (int64_t)g.M * g.ldo || (g.split_stride & 3)))
-    return fail(CS_ERR_UNSUPPORTED, "gemm: split K writes plain fp32 partial sums (no bias, no row map), at most 16 parts");
+    return fail(CS_ERR_UNSUPPORTED, "gemm: split K writes plain fp32 partial sums (no bias, no row map), at most 16 parts of whole K slices");
   if (g.K <= 0 || (g.K & 63)) return fail(CS_ERR_UNSUPPORTED, "gemm: K must be a positive multiple of 64");
   // lda < K is allowed: rows may overlap (a k=3 convolution reads three consecutive frames per row)
   if ((g.lda & 7) || (reinterpret_cast<uintptr_t>(g.A) & 15) || (reinterpret_cast<uintptr_t>(g.W) & 15))
     return fail(CS_ERR_INVALID_ARG, "gemm: A and W rows must be 16-byte aligned");
   if ((g.N & 3) || (g.ldo & 3) || (reinterpret_cast<uintptr_t>(g.out) & 15) || (reinterpret_cast<uintptr_t>(g.bias) & 15))
     return fail(CS_ERR_UNSUPPORTED, "gemm: N and the output row stride must be multiples of 4, out and bias 16-byte aligned");
+  // a lane addresses its rows of a tile by a 32-bit byte offset from the tile's first row
+  if (!gemm_rows_addressable(g.M, g.lda) || !gemm_rows_addressable(g.N, g.ldw))
+    return fail(CS_ERR_UNSUPPORTED, "gemm: the rows of a tile of A or W span 4 GiB or more");
   switch (epilogue) {
     case EPI_BF16: return launch_epi<EPI_BF16>(g, stream);
     case EPI_F32: return launch_epi<EPI_F32>(g, stream);
