@@ -22,63 +22,83 @@ __device__ __forceinline__ float wave_sum(float v) {
 constexpr int NORM_MAX_V4 = 8;  // a wave keeps a row of up to 64*4*8 = 2048 floats in registers
 
 // One wave per row.  MODE 0: RMSNorm.  MODE 1: LayerNorm.  POOL rows of x are averaged first.
-template <int MODE>
-__global__ __launch_bounds__(256) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,
-                                                   const float* __restrict__ bias, float eps,
-                                                   bf16_t* __restrict__ y, int64_t rows, int dim, int pool, int split_group,
-                                                   bool wt, PendingSum add) {
+// A row is a dozen kilobytes and the work on it a few hundred instructions, so a launch over few rows (a small batch,
+// whose pending split-K sums join here) lasts as long as its loads' latency: PARTS, the number of pending sums, is a
+// template argument, and all the loads of the row and of the sums are issued before the first is used.
+// NV: float4 pieces of a row per lane, the smallest instantiation that covers dim.
+template <int MODE, int PARTS, int NV>
+__global__ __launch_bounds__(64) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,
+                                                  const float* __restrict__ bias, float eps,
+                                                  bf16_t* __restrict__ y, int64_t rows, int dim, int pool, int split_group,
+                                                  bool wt, PendingSum add) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  float4 v[NORM_MAX_V4];
+  const int64_t row = blockIdx.x;
+  float4 v[NV];
   const int nv = dim >> 2;
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (PARTS == 0) {
 #pragma unroll
-  for (int i = 0; i < NORM_MAX_V4; ++i) {
-    const int c = lane + 64 * i;
-    v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c < nv) {
-      for (int p = 0; p < pool; ++p) {
-        const float4 t = reinterpret_cast<const float4*>(x + (row * pool + p) * dim)[c];
-        v[i].x += t.x; v[i].y += t.y; v[i].z += t.z; v[i].w += t.w;
+    for (int i = 0; i < NV; ++i) v[i] = zero;
+    for (int p = 0; p < pool; ++p) {
+      float4 t[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = lane + 64 * i;
+        t[i] = zero;
+        if (c < nv) t[i] = reinterpret_cast<const float4*>(x + (row * pool + p) * dim)[c];
       }
-      if (pool > 1) {
-        const float ip = 1.0f / pool;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        v[i].x += t[i].x; v[i].y += t[i].y; v[i].z += t[i].z; v[i].w += t[i].w;
+      }
+    }
+    if (pool > 1) {
+      const float ip = 1.0f / pool;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
         v[i].x *= ip; v[i].y *= ip; v[i].z *= ip; v[i].w *= ip;
       }
-      if (add.parts) {   // pending split-K sums join the residual stream here (pool == 1)
-        // all parts are requested before the first is used (a loop over a run-time count waits for every
-        // load in turn); summed in part order as before
-        float4 part[PENDING_MAX_PARTS];
+    }
+  } else {   // pending split-K sums join the residual stream here (pool == 1), in part order
+    float4 part[PARTS][NV], pb[NV], ps[NV];
 #pragma unroll
-        for (int s = 0; s < PENDING_MAX_PARTS; ++s)
-          if (s < add.n_parts) part[s] = reinterpret_cast<const float4*>(add.parts + s * add.stride + row * dim)[c];
-        float4 a = part[0];
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane + 64 * i;
+      const bool in = c < nv;
 #pragma unroll
-        for (int s = 1; s < PENDING_MAX_PARTS; ++s)
-          if (s < add.n_parts) { a.x += part[s].x; a.y += part[s].y; a.z += part[s].z; a.w += part[s].w; }
-        if (add.bias) {
-          const float4 t = reinterpret_cast<const float4*>(add.bias)[c];
-          a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
-        }
-        if (add.scale) {
-          const float4 t = reinterpret_cast<const float4*>(add.scale)[c];
-          a.x *= t.x; a.y *= t.y; a.z *= t.z; a.w *= t.w;
-        }
-        v[i].x += a.x; v[i].y += a.y; v[i].z += a.z; v[i].w += a.w;
-        reinterpret_cast<float4*>(x + row * dim)[c] = v[i];
+      for (int s = 0; s < PARTS; ++s) part[s][i] = in ? reinterpret_cast<const float4*>(add.parts + s * add.stride + row * dim)[c] : zero;
+      v[i] = in ? reinterpret_cast<const float4*>(x + row * dim)[c] : zero;
+      pb[i] = in && add.bias ? reinterpret_cast<const float4*>(add.bias)[c] : zero;
+      ps[i] = in && add.scale ? reinterpret_cast<const float4*>(add.scale)[c] : make_float4(1.f, 1.f, 1.f, 1.f);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      float4 a = part[0][i];
+#pragma unroll
+      for (int s = 1; s < PARTS; ++s) {
+        a.x += part[s][i].x; a.y += part[s][i].y; a.z += part[s][i].z; a.w += part[s][i].w;
       }
+      if (add.bias) {
+        a.x += pb[i].x; a.y += pb[i].y; a.z += pb[i].z; a.w += pb[i].w;
+      }
+      if (add.scale) {
+        a.x *= ps[i].x; a.y *= ps[i].y; a.z *= ps[i].z; a.w *= ps[i].w;
+      }
+      v[i].x += a.x; v[i].y += a.y; v[i].z += a.z; v[i].w += a.w;
+      const int c = lane + 64 * i;
+      if (c < nv) reinterpret_cast<float4*>(x + row * dim)[c] = v[i];
     }
   }
   float mean = 0.f;
   if (MODE == 1) {
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < NORM_MAX_V4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
     mean = wave_sum(s) / dim;
   }
   float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < NORM_MAX_V4; ++i) {
+  for (int i = 0; i < NV; ++i) {
     if (lane + 64 * i < nv) {
       const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
       ss += (a * a + b * b) + (c * c + d * d);
@@ -86,7 +106,7 @@ __global__ __launch_bounds__(256) void norm_kernel(float* __restrict__ x, const 
   }
   const float rstd = rsqrtf(wave_sum(ss) / dim + eps);
 #pragma unroll
-  for (int i = 0; i < NORM_MAX_V4; ++i) {
+  for (int i = 0; i < NV; ++i) {
     const int c = lane + 64 * i;
     if (c < nv) {
       const float4 g = reinterpret_cast<const float4*>(gain)[c];
@@ -117,7 +137,32 @@ static cs_status norm_check(int64_t rows, int dim, const PendingSum& add = Pendi
     return fail(CS_ERR_UNSUPPORTED, "norm: dim must be a multiple of 4, at most 2048");
   if (add.parts && (add.n_parts < 1 || add.n_parts > PENDING_MAX_PARTS || (add.stride & 3)))
     return fail(CS_ERR_UNSUPPORTED, "norm: pending sums come in 1 to 4 parts, their stride a multiple of 4");
-  if (rows > (int64_t)4 * 0x7fffffff) return fail(CS_ERR_UNSUPPORTED, "norm: too many rows");
+  if (rows > 0x7fffffff) return fail(CS_ERR_UNSUPPORTED, "norm: too many rows");
+  return CS_OK;
+}
+
+// (a wave is a workgroup of its own: 256 rows make 256 workgroups, one per CU)
+template <int MODE, int PARTS>
+static void norm_launch_nv(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+                           int split_group, const PendingSum& add, hipStream_t s) {
+  const bool wt = lines_exclusive(y, (int64_t)dim * 2);
+  const dim3 grid((unsigned)rows), block(64);
+  if (dim <= 1024) hipLaunchKernelGGL((norm_kernel<MODE, PARTS, 4>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
+  else if (dim <= 1280) hipLaunchKernelGGL((norm_kernel<MODE, PARTS, 5>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
+  else hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NORM_MAX_V4>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
+}
+template <int MODE>
+static cs_status norm_launch(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+                             int split_group, const PendingSum& add, hipStream_t s) {
+  static_assert(PENDING_MAX_PARTS == 4, "one instantiation per number of pending sums");
+  switch (add.parts ? add.n_parts : 0) {
+    case 0: norm_launch_nv<MODE, 0>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+    case 1: norm_launch_nv<MODE, 1>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+    case 2: norm_launch_nv<MODE, 2>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+    case 3: norm_launch_nv<MODE, 3>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+    default: norm_launch_nv<MODE, 4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+  }
+  CS_HIP(hipGetLastError());
   return CS_OK;
 }
 
@@ -125,10 +170,7 @@ cs_status launch_rmsnorm(float* x, const float* gain, float eps, bf16_t* y, int6
                          const PendingSum& add) {
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
-  hipLaunchKernelGGL(norm_kernel<0>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, x, gain, nullptr, eps, y,
-                     rows, dim, 1, 0, lines_exclusive(y, (int64_t)dim * 2), add);
-  CS_HIP(hipGetLastError());
-  return CS_OK;
+  return norm_launch<0>(x, gain, nullptr, eps, y, rows, dim, 1, 0, add, s);
 }
 
 cs_status launch_rmsnorm_split(float* x, const float* gain, float eps, bf16_t* y, int64_t rows, int32_t dim,
@@ -136,20 +178,14 @@ cs_status launch_rmsnorm_split(float* x, const float* gain, float eps, bf16_t* y
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
   if (group < 1 || rows % group) return fail(CS_ERR_INVALID_ARG, "rmsnorm_split: rows must be a multiple of the group");
-  hipLaunchKernelGGL(norm_kernel<0>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, x, gain, nullptr, eps, y,
-                     rows, dim, 1, group, lines_exclusive(y, (int64_t)dim * 2), add);
-  CS_HIP(hipGetLastError());
-  return CS_OK;
+  return norm_launch<0>(x, gain, nullptr, eps, y, rows, dim, 1, group, add, s);
 }
 
 cs_status launch_layernorm(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows,
                            int32_t dim, hipStream_t s, const PendingSum& add) {
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
-  hipLaunchKernelGGL(norm_kernel<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, x, gain, bias, eps, y, rows,
-                     dim, 1, 0, lines_exclusive(y, (int64_t)dim * 2), add);
-  CS_HIP(hipGetLastError());
-  return CS_OK;
+  return norm_launch<1>(x, gain, bias, eps, y, rows, dim, 1, 0, add, s);
 }
 
 cs_status launch_pool_layernorm(const float* x, const float* gain, const float* bias, float eps, bf16_t* y,
@@ -157,10 +193,7 @@ cs_status launch_pool_layernorm(const float* x, const float* gain, const float* 
   if (out_rows <= 0) return CS_OK;
   if (cs_status st = norm_check(out_rows, dim)) return st;
   if (pool < 1) return fail(CS_ERR_INVALID_ARG, "pool_layernorm: pool < 1");
-  hipLaunchKernelGGL(norm_kernel<1>, dim3((unsigned)((out_rows + 3) / 4)), dim3(256), 0, s, const_cast<float*>(x), gain, bias,
-                     eps, y, out_rows, dim, pool, 0, lines_exclusive(y, (int64_t)dim * 2), PendingSum());
-  CS_HIP(hipGetLastError());
-  return CS_OK;
+  return norm_launch<1>(const_cast<float*>(x), gain, bias, eps, y, out_rows, dim, pool, 0, PendingSum(), s);
 }
 
 // ---- gather + cast to bf16 with zero padding; 4 elements per thread
