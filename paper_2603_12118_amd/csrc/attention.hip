@@ -31,10 +31,17 @@ __device__ __forceinline__ uint32_t pack2_a(float a, float b) {
 // (three waves per SIMD, six workgroups per CU, which is also what their LDS tiles allow).
 // SINGLE: every work item has at most 64 keys (windows of up to 64 tokens): one tile, nothing to
 // prefetch, so the staging registers are dead before the accumulators come alive.
-template <int DH, int NW, int QT, bool SINGLE>
+// KG > 1: the key tiles of an item are dealt to KG groups of NW / KG waves, each with tiles of its own in LDS; the
+// groups' running maxima, sums and outputs are merged at the end.  For launches whose items do not fill the chip, where
+// the time is the number of tiles one workgroup walks (1.4 us each, mostly waiting): 1025 keys, 16 heads 43 us in two
+// launches -> 18.6 us; 1500 keys, 20 heads 34.2 -> 26.2 us.  (Four groups of 64 queries draw twice the bytes: 20.5 and
+// 28.2 us.)  plan.cpp says which batches take it.
+template <int DH, int NW, int QT, bool SINGLE, int KG = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(SINGLE ? 3 : (NW == 8 ? 4 : 2), SINGLE ? 3 : (NW == 8 ? 4 : 2))))
 void attn_kernel(AttnArgs a) {
-  constexpr int NT = 64 * NW;
+  constexpr int NWG = NW / KG;           // waves of a key group
+  constexpr int NT = 64 * NWG;
+  static_assert((NT & (NT - 1)) == 0, "threads of a key group");
   constexpr int KS = DH / 16;            // k-steps of the score product
   constexpr int DT = (DH + 31) / 32;     // 32-row tiles of O^T
   constexpr int KSTR = DH * 2 + 16;      // LDS row stride of the K tile, bytes
@@ -43,12 +50,18 @@ void attn_kernel(AttnArgs a) {
   // Head dimension 80, eight waves: the query fragments wait in LDS (each lane's own 16-byte pieces, read
   // back in lane order: no conflicts) instead of 20 registers, which brings the kernel under 128 registers
   // and a second workgroup onto the CU.
-  constexpr bool Q_IN_LDS = DH > 64 && NW == 8;
-  __shared__ __align__(16) unsigned char k_lds[64 * KSTR];
-  __shared__ __align__(16) unsigned char v_lds[DT * 32 * VSTR];
+  // (Key groups: the groups have the same queries and write the same bytes.)
+  constexpr bool Q_IN_LDS = (DH > 64 && NW == 8) || KG > 1;
+  static_assert(KG == 1 || (!SINGLE && QT == 1 && DH % 32 == 0), "key groups: one 32-query block per wave");
+  constexpr int K_BYTES = 64 * KSTR, V_BYTES = DT * 32 * VSTR;
+  __shared__ __align__(16) unsigned char k_lds_all[KG == 1 ? K_BYTES : KG * (K_BYTES + V_BYTES)];
+  __shared__ __align__(16) unsigned char v_lds_all[KG == 1 ? V_BYTES : 16];
   __shared__ __align__(16) unsigned char q_lds[Q_IN_LDS ? QT * KS * NT * 16 : 16];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
+  const int tid = threadIdx.x & (NT - 1), lane = tid & 63, wave = tid >> 6;   // inside the key group
+  unsigned char* const k_lds = k_lds_all + group * (K_BYTES + V_BYTES);
+  unsigned char* const v_lds = KG == 1 ? v_lds_all : k_lds + K_BYTES;
   const int l31 = lane & 31, lhi = lane >> 5;
   // Workgroup -> (work item, head).  Consecutive workgroups run on different XCDs (id % 8), each with its own L2.
   int head, item;
@@ -121,6 +134,25 @@ void attn_kernel(AttnArgs a) {
   u32x4 kreg[K_PT];
   u32x2 vreg[V_PT];
   auto load_tile = [&](int kv) {
+    if constexpr (KG > 1) {
+      // the same by 32-bit offsets from the item's first key (launch_attention bounds the keys of such an item): a
+      // group's waves hold four times the staging registers, and 64-bit addresses of their own do not fit beside them
+      const unsigned char* kb = reinterpret_cast<const unsigned char*>(kbase + (int64_t)w.kv0 * ldq);
+      const unsigned char* vb = reinterpret_cast<const unsigned char*>(vbase + w.kv0);
+#pragma unroll
+      for (int u = 0; u < K_PT; ++u) {
+        const int c = tid + u * NT;
+        int row = kv - w.kv0 + c / KCH;
+        row = row < last_tok - w.kv0 ? row : last_tok - w.kv0;
+        kreg[u] = *reinterpret_cast<const u32x4*>(kb + ((uint32_t)row * (uint32_t)(ldq * 2) + (c % KCH) * 16));
+      }
+      int tok = kv - w.kv0 + (tid & 15) * 4;
+      tok = tok < vt_last - w.kv0 ? tok : vt_last - w.kv0;
+      const uint32_t v0 = (uint32_t)(tid >> 4) * (uint32_t)(a.ld_vt * 2) + tok * 2;
+#pragma unroll
+      for (int u = 0; u < V_PT; ++u) vreg[u] = *reinterpret_cast<const u32x2*>(vb + (v0 + (uint32_t)u * (uint32_t)(NT / 16 * 2 * a.ld_vt)));
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < K_PT; ++u) {
       int c = tid + u * NT;
@@ -155,19 +187,26 @@ void attn_kernel(AttnArgs a) {
 
   // a wave whose queries lie beyond the item (the last query block of a sequence) only helps to stage the tiles
   const bool live = qw < w.q1;
-  load_tile(w.kv0);
-  for (int kv = w.kv0; kv < (SINGLE ? w.kv0 + 1 : w.kv1); kv += 64) {
+  const int kv_first = w.kv0 + 64 * group;   // this group's first tile
+  load_tile(kv_first);
+  for (int kv = kv_first; kv - 64 * group < (SINGLE ? w.kv0 + 1 : w.kv1); kv += 64 * KG) {
     if (!SINGLE) __syncthreads();  // previous tile fully consumed
     store_tile();
     __syncthreads();
-    if (!SINGLE && kv + 64 < w.kv1) load_tile(kv + 64);
+    // (a key group's waves stage four times as much each: their next tile is requested behind the softmax, when the
+    // scores' registers are free)
+    const bool more = !SINGLE && kv + 64 * KG < w.kv1;
+    if (KG == 1 && more) load_tile(kv + 64 * KG);
     __builtin_amdgcn_sched_barrier(0);
-    if (!SINGLE && !live) continue;
+    if (!SINGLE && (!live || (KG > 1 && kv >= w.kv1))) {   // (or no tile is left for this group)
+      if (KG > 1 && more) load_tile(kv + 64 * KG);
+      continue;
+    }
 
     // ---- S^T tiles: s[it][jt] covers keys kv + jt*32 .. +31 (rows) x queries it*32 .. +31 (lanes)
     // The accumulators start at minus the query's running maximum (a lane's scores all belong to one
     // query), so the products come out as score - maximum and the common case below needs no subtraction.
-    const bool first = kv == w.kv0;
+    const bool first = kv == kv_first;
     f32x16 s[QT][2];
 #pragma unroll
     for (int it = 0; it < QT; ++it) {
@@ -255,6 +294,10 @@ void attn_kernel(AttnArgs a) {
         }
       lrun[it] += sum;
     }
+    if constexpr (KG > 1) {
+      if (more) load_tile(kv + 64 * KG);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // ---- O^T += V^T P^T.  k-slot e of lane-half lhi in step (jt,u) is key jt*32 + 16u + 8*(e/4) + 4*lhi + e%4
 #pragma unroll
     for (int ku = 0; ku < 4; ++ku) {
@@ -270,6 +313,45 @@ void attn_kernel(AttnArgs a) {
         for (int it = 0; it < QT; ++it)
           o[it][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[it][ku], o[it][dt], 0, 0, 0);
       }
+    }
+  }
+
+  if constexpr (KG > 1) {
+    // ---- merge: every group but the first leaves its state in LDS (lane order, 4-byte words: no conflicts), the first
+    // adds the groups in order, each scaled to the common maximum
+    constexpr int STATE = 16 * DT + 2;     // words per lane
+    static_assert((KG - 1) * NWG * STATE * 256 <= KG * (K_BYTES + V_BYTES), "the states fit where the tiles were");
+    __syncthreads();
+    float* st = reinterpret_cast<float*>(k_lds_all) + wave * STATE * 64 + lane;
+    if (group > 0) {
+      float* mine = st + (group - 1) * NWG * STATE * 64;
+      mine[0] = mrun[0];
+      mine[64] = lrun[0];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[(2 + 16 * dt + r) * 64] = o[0][dt][r];
+    }
+    __syncthreads();
+    if (group > 0) return;
+    float m = mrun[0];
+#pragma unroll
+    for (int k = 1; k < KG; ++k) m = fmaxf(m, st[(k - 1) * NWG * STATE * 64]);
+    const float a0 = __builtin_amdgcn_exp2f(mrun[0] - m);   // (the first group always has a tile: m is finite)
+    lrun[0] *= a0;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[0][dt][r] *= a0;
+#pragma unroll
+    for (int k = 1; k < KG; ++k) {
+      const float* other = st + (k - 1) * NWG * STATE * 64;
+      const float ak = __builtin_amdgcn_exp2f(other[0] - m);   // 0 for a group without a tile (its maximum is -inf)
+      lrun[0] += ak * other[64];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[0][dt][r] += ak * other[(2 + 16 * dt + r) * 64];
     }
   }
 
@@ -307,13 +389,19 @@ cs_status launch_attention(const AttnArgs& a, hipStream_t stream) {
   // every wave owns 32 queries: two waves per 64-query work item (window layers), eight per 256-query item,
   // two waves per SIMD so that one wave's softmax arithmetic runs under the other's MFMAs
   if (a.single_tile && a.q_per_block != 64) return fail(CS_ERR_INVALID_ARG, "attention: single-tile items are 64-query items");
+  if (a.q_per_block == 128 ? a.key_groups != 2 : a.key_groups > 1 && (a.key_groups != 4 || a.q_per_block != 64))
+    return fail(CS_ERR_INVALID_ARG, "attention: key groups are two of 128-query items or four of 64-query items");
+  if (a.key_groups > 1 && (a.head_dim != 64 || a.single_tile || a.n_tok > 1 << 24))
+    return fail(CS_ERR_UNSUPPORTED, "attention: key groups need head_dim 64, several key tiles and at most 2^24 tokens");
   if (a.head_dim == 80 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<80, 2, 1, true>), grid, dim3(128), 0, stream, a);
   else if (a.head_dim == 80 && a.q_per_block == 64) hipLaunchKernelGGL((attn_kernel<80, 2, 1, false>), grid, dim3(128), 0, stream, a);
   else if (a.head_dim == 80 && a.q_per_block == 256) hipLaunchKernelGGL((attn_kernel<80, 8, 1, false>), grid, dim3(512), 0, stream, a);
   else if (a.head_dim == 64 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<64, 2, 1, true>), grid, dim3(128), 0, stream, a);
+  else if (a.head_dim == 64 && a.q_per_block == 64 && a.key_groups > 1) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 4>), grid, dim3(512), 0, stream, a);
+  else if (a.head_dim == 64 && a.q_per_block == 128) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 2>), grid, dim3(512), 0, stream, a);
   else if (a.head_dim == 64 && a.q_per_block == 64) hipLaunchKernelGGL((attn_kernel<64, 2, 1, false>), grid, dim3(128), 0, stream, a);
   else if (a.head_dim == 64 && a.q_per_block == 256) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false>), grid, dim3(512), 0, stream, a);
-  else return fail(CS_ERR_UNSUPPORTED, "attention: head_dim must be 64 or 80 and q_per_block 64 or 256");
+  else return fail(CS_ERR_UNSUPPORTED, "attention: head_dim must be 64 or 80 and q_per_block 64, 128 or 256");
   CS_HIP(hipGetLastError());
   return CS_OK;
 }

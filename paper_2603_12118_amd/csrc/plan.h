@@ -25,8 +25,9 @@ struct BatchPlan {
                             // queries would still walk every key tile and cost the launch a round of the chip)
   int32_t n_win_work = 0, n_full_work = 0, n_tail_work = 0;
   bool win_single_tile = false;  // no window has more than 64 tokens
-  int32_t full_q_per_block = 256;   // queries per item of full_work: 256, or 64 when the segments are short chunks
+  int32_t full_q_per_block = 256;   // queries per item of full_work: 256, 128 with key groups, or 64 when the segments are short chunks
   bool full_single_tile = false;    // no full_work item has more than 64 keys
+  int32_t full_key_groups = 1, tail_key_groups = 1;   // > 1: the items share out their key tiles inside the workgroup
   std::vector<int32_t> win_cu;  // host only: window boundaries in internal token order
   // audio
   int64_t n_pad_rows = 0;   // sum(frames_i + 2): rows of the zero-padded frame buffers
