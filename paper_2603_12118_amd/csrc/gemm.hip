@@ -250,7 +250,8 @@ __device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS>& op
 // registers = rows m).
 // On return the stage buffer that does not hold the last slice is idle: every wave passed the last barrier after
 // reading it and nothing was loaded into it since.
-// before_last() runs ahead of the last slice's MFMAs: global loads it issues are in flight while those execute.
+// before_last() runs ahead of the last slice's MFMAs and in_last() in the middle of them, where the fragments of the
+// first k-step have left their registers: global loads they issue are in flight while those execute.
 //
 // Fragment i of A (16 rows) pairs with fragment j of W into quarter 2 (i % 2) + j % 2 of block (i / 2, j / 2).  The
 // operand with fewer fragments per wave is held for a k-step of 32 (double-buffered over the two k-steps of a slice);
@@ -258,9 +259,9 @@ __device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS>& op
 // The loads of slice s + STAGES go out one at a time between MFMAs, from the barrier of slice s (which frees that
 // slice's buffer) to the middle of the first k-step of slice s + 1: in one burst they queue in the texture-address
 // unit (16 clocks each, all waves at once) and every wave sits in the issue stall.
-template <int BM, int BN, int WGM, int WGN, bool W_FIRST, int STAGES, typename F>
+template <int BM, int BN, int WGM, int WGN, bool W_FIRST, int STAGES, typename F, typename G>
 __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem, int m0, int n0,
-                                          f32x4 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32][4], F&& before_last) {
+                                          f32x4 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32][4], F&& before_last, G&& in_last) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = (WN + 31) / 32;
   constexpr int STAGE_BYTES = (BM + BN) * 128;
@@ -347,6 +348,9 @@ __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
       const int ks = r / NO, o = r % NO;
+      if constexpr (!SYNC.value) {
+        if (r == NO) in_last();
+      }
       if constexpr (SYNC.value) {
         if (r == SYNC_ROW) {
           wait_newer(newer);   // this wave's part of the next slice has landed
@@ -560,7 +564,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
             bv[j][q] = (g.bias && n < N) ? g.bias[n] : 0.f;
           }
         gather_scale();
-      });
+      }, [] {});
       publish_scale();
       const bool wide = (g.ld_vt & 7) == 0;
       const bool wt_v = lines_exclusive(g.vt, g.ld_vt * 2);   // a workgroup writes runs of 128 bytes or more of a v^T row
@@ -604,6 +608,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   // registers for it, stays with one: with two it spills more and gains nothing).
   constexpr bool RESADD = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SCALED_F32 || EPI == EPI_RESADD_SUMS_F32;
   constexpr bool HOLD_TWO = RESADD && TM > 1 && BN < 256;
+  // (the 256 x 256 tile has registers for that one only in the second half of the last slice: requested ahead of it,
+  // 28 registers of accumulators were spilled around the slice; 32 mixed images 161.8 -> 157.4 ms)
+  constexpr bool HELD_LATE = RESADD && BN == 256;
   [[maybe_unused]] f32x4 held[HOLD_TWO ? 2 : 1][RESADD ? TN : 1][4];
   [[maybe_unused]] auto fetch_old = [&](int i, int j, f32x4 (&dst)[4]) {
     const int r = lane >> 3, c = (lane & 7) * 4;
@@ -640,11 +647,16 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
           if (n < N) scale_r[j][q] = *reinterpret_cast<const f32x4*>(g.col_scale + n);
         }
       }
-    if constexpr (RESADD) {
+    if constexpr (RESADD && !HELD_LATE) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) fetch_old(0, j, held[0][j]);
     }
     if constexpr (CONSUMES_NORM) gather_scale();
+  }, [&] {
+    if constexpr (HELD_LATE) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fetch_old(0, j, held[0][j]);
+    }
   });
   if constexpr (CONSUMES_NORM) publish_scale();
   if constexpr (HOLD_TWO) {
