@@ -80,6 +80,7 @@ struct cs_encoder {
   int device = 0;
   // derived sizes
   int P_pad = 0, I_pad = 0, MH_pad = 0, half = 0;
+  int I_ld = 0;                              // row pitch of the MLP activations and of the weights that read them (activation_pitch)
   bool rope = false;
   // weights
   unsigned char* dev = nullptr;
@@ -260,6 +261,11 @@ static size_t pack_vector(Arena& A, const SrcTensor& t, int64_t n_pad, RowOf idx
   return off;
 }
 
+// Rows whose pitch is a multiple of 1 KB start on few of the memory channels, and the rows of a tile are read in step:
+// a line of 128 bytes more per row spreads them (pitch 10240 B, 24 000 x 1280 x 5120: 255 -> 245 us; 8192 B,
+// 8224 x 1024 x 4096: 84.1 -> 78.4 us; pitches of 2048 and 2560 B at K = 1024 and 1280: no change).
+static int activation_pitch(int cols) { return cols >= 2048 && cols % 512 == 0 ? cols + 64 : cols; }
+
 static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
   const cs_encoder_config& c = e->cfg;
   const int64_t D = c.hidden, I = c.mlp_dim, dh = c.head_dim;
@@ -323,7 +329,7 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
       }
       if (cs_status st = wb.get(p + "mlp.down.weight", D * I, t)) return st;
       if (cs_status st = wb.get(p + "mlp.down.bias", D, b, true)) return st;
-      L.w2 = pack_matrix(A, t, D, I, Ip, ident);
+      L.w2 = pack_matrix(A, t, D, I, e->I_ld, ident);
       L.b2 = pack_vector(A, b, D, ident);
     } else {
       const int64_t Ip = e->I_pad;
@@ -333,7 +339,7 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
       L.b1 = pack_vector(A, b, Ip, [&](int64_t r) { return r < I ? r : -1; });
       if (cs_status st = wb.get(p + "mlp.fc2.weight", D * I, t)) return st;
       if (cs_status st = wb.get(p + "mlp.fc2.bias", D, b, true)) return st;
-      L.w2 = pack_matrix(A, t, D, I, Ip, ident);
+      L.w2 = pack_matrix(A, t, D, I, e->I_ld, ident);
       L.b2 = pack_vector(A, b, D, ident);
       fold_vectors(A, L.wqkv, L.bqkv, L.g1, L.be1, 3 * D, D, &L.cqkv, &L.dqkv);
       fold_vectors(A, L.w1, L.b1, L.g2, L.be2, Ip, D, &L.c1, &L.d1);
@@ -483,14 +489,14 @@ static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
     return o;
   };
   w.plan = take(p.blob.size() * 4);
-  w.rope = take((size_t)N * std::max(e->half, 1) * 8);
+  w.rope = take(e->rope ? (size_t)N * std::max(e->half, 1) * 8 : 0);
   w.x = take((size_t)N * D * 4);
-  w.xn = take((size_t)N * D * 4);            // bf16 tokens; twice that for the merger's hi|lo input
+  w.xn = take((size_t)N * D * (c.arch == CS_ARCH_AUDIO ? 2 : 4));   // bf16 tokens; twice that for the merger's hi|lo input
   w.attn = take((size_t)N * D * 2);
   w.qk = take((size_t)N * 2 * D * 2);
   w.ld_vt = round_up(N, 64);   // rows of v^T start on 128-byte lines (write-through stores need that)
   w.vt = take((size_t)D * w.ld_vt * 2);
-  size_t big = (size_t)N * e->I_pad * 2;                                   // MLP activation
+  size_t big = (size_t)N * e->I_ld * 2;                                   // MLP activation
   if (c.arch != CS_ARCH_AUDIO) {
     big = std::max(big, (size_t)N * e->P_pad * 2);                          // gathered patches
     big = std::max(big, (size_t)p.n_groups * e->MH_pad * 4);                // merger hidden, hi|lo
@@ -661,6 +667,7 @@ static cs_status encoder_create(const cs_encoder_config* config, const cs_tensor
   const cs_encoder_config& c = e->cfg;
   e->P_pad = (int)round_up(c.patch_dim, 64);
   e->I_pad = (int)round_up(c.mlp_dim, 64);
+  e->I_ld = activation_pitch(e->I_pad);
   e->MH_pad = c.arch != CS_ARCH_AUDIO ? (int)round_up(c.merger_hidden, 64) : 0;
   e->half = c.head_dim / 2;
   e->rope = c.arch == CS_ARCH_VIT && (c.rope_sections[0] + c.rope_sections[1] + c.rope_sections[2]) > 0;
@@ -925,9 +932,9 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
   auto gemm_residual = [&](const bf16_t* A, int64_t lda, size_t W, size_t bias, size_t scale, int64_t K, size_t next_gain,
                            int fold_parts, int S) -> cs_status {
     GemmArgs g = {};
-    g.A = A; g.lda = lda; g.W = e->ptr<bf16_t>(W); g.ldo = D; g.M = (int32_t)N; g.N = (int32_t)D;
+    g.A = A; g.lda = lda; g.W = e->ptr<bf16_t>(W); g.ldw = lda; g.ldo = D; g.M = (int32_t)N; g.N = (int32_t)D;   // (A and W have one pitch)
     if (S > 1) {
-      g.ldw = K; g.K = (int32_t)K; g.splits = S; g.split_stride = N * D; g.out = parts;
+      g.K = (int32_t)K; g.splits = S; g.split_stride = N * D; g.out = parts;
       if (cs_status st = launch_gemm(EPI_F32, g, stream)) return st;
       // the sums stay pending: the normalisation that reads x next adds them on its way through
       pending.parts = parts; pending.n_parts = S; pending.stride = N * D;
@@ -1016,14 +1023,14 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       StepTimer tm(e, CS_STEP_MLP_UP, stream);
       if (vit) {
         GemmArgs g = {};
-        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_pad;
+        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
         g.M = (int32_t)N; g.N = 2 * e->I_pad; g.K = (int32_t)D;
         consume_norm(g);
         if (cs_status st = launch_gemm(EPI_SWIGLU_BF16, g, stream)) return st;
       }
       else {
         GemmArgs g = {};
-        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_pad;
+        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
         g.M = (int32_t)N; g.N = e->I_pad; g.K = (int32_t)D;
         consume_norm(g, L.c1, L.d1);
         if (cs_status st = launch_gemm(EPI_GELU_BF16, g, stream)) return st;
@@ -1033,7 +1040,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       StepTimer tm(e, CS_STEP_MLP_DOWN, stream);
       // (the norm behind the last block is the merger's, which splits its output: a kernel of its own)
       const size_t next_g1 = l + 1 < c.n_layers ? e->layers[l + 1].g1 : 0;
-      if (cs_status st = gemm_residual(big, e->I_pad, L.w2, L.b2, cls ? L.ls2 : 0, e->I_pad, next_g1, w.fold_down, w.s_down)) return st;
+      if (cs_status st = gemm_residual(big, e->I_ld, L.w2, L.b2, cls ? L.ls2 : 0, e->I_pad, next_g1, w.fold_down, w.s_down)) return st;
     }
   }
 
