@@ -62,7 +62,7 @@ __device__ __forceinline__ float silu_f(float z) {
 // through a private 32-row LDS chunk and writes them out as whole 64- or 128-byte row segments,
 // 16 bytes per lane.  LDS serves one wave's instructions in order, so no wait is needed between a
 // chunk's writes and reads beyond keeping the compiler from reordering them.
-// What a tile may use behind its two stage buffers: 1 KB of per-column values, then the waves' per-row partial
+// What a tile may use behind its stage buffers: 1 KB of per-column values, then the waves' per-row partial
 // sums of a folded normalisation, [2][WGN][BM] floats (sums of squares, plain sums).  (The 128 x 160 tiles, of
 // which the four-wave one must fit a CU twice, have 128 rows and two waves along N: 2 KB of sums.)
 constexpr int EXTRA_LDS_BYTES = 1024 + 2 * 4 * 256 * 4;
@@ -71,7 +71,8 @@ template <int BM, int BN, int NWAVES = 0, int EPI = -1>
 constexpr int extra_lds_bytes() {
   return BM == 128 && BN == 160 ? EXTRA_LDS_BYTES_PAIR : EXTRA_LDS_BYTES;
 }
-// Stage buffers of the K loop.  Two everywhere (a slice's MFMAs cover the next slice's loads where the tile is
+// Stage buffers of the K loop, where the launcher does not say otherwise (its one-round tiles have three or four).  Two
+// (a slice's MFMAs cover the next slice's loads where the tile is
 // large, and more would not fit) except on the eight-wave 128 x 160 tile, which runs one workgroup per CU in
 // launches that do not fill the chip: its slice of MFMAs is much shorter than the loads' latency, so it keeps
 // CS_GEMM_SMALL_STAGES - 1 slices in flight, four stages being what 160 KB of LDS hold (build-time switch for
@@ -1103,7 +1104,8 @@ static bool narrow_resadd() {
 // times below whatever the number of workgroups (a lone CU draws 45 - 60 B/ns), so the smallest tile that still makes
 // at most one round is the fastest (256 x 3840 x 1280: 64 x 64 9.4 us, 64 x 128 12.8, 128 x 128 16.9, and 20.4 with two
 // slices in flight; 1024 x 3840 x 1280: 128 x 128 16.0, two per CU 20.2; 512 x 6912 x 1280: 17.2 against 23.0 for one
-// and a half rounds of 64 x 128).
+// and a half rounds of 64 x 128).  More slices in flight change nothing (eight for 64 x 64: 10.0 against 9.5 us), nor do
+// weights that are already in the memory-side cache (7.8 us).
 struct SmallTile {
   int bm, bn;
 };
@@ -1144,11 +1146,6 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   // (the scaled residual epilogue spills registers with eight waves and with 160-wide wave tiles: it
   // takes the 256 x 128 or 128 x 128 tiles)
   constexpr bool EIGHT_WAVES_OK = EPI != EPI_RESADD_SCALED_F32;
-#ifdef CS_GEMM_FORCE_256      // measurement build: the 256 x 256 tile whatever the number of workgroups
-  if constexpr (EIGHT_WAVES_OK) {
-    if (big_ok) return launch_cfg<256, 256, 2, 4, EPI>(g, stream);
-  }
-#endif
   if constexpr (EIGHT_WAVES_OK) {
     // 256 x 256 for more than a round of the chip (CS_GEMM_NARROW_RESADD=1 in the environment makes the
     // residual add take the narrow tile below at any size, for measurement: the 32-image batch 166.5 -> 177.4 ms)
