@@ -69,6 +69,7 @@ def lib() -> C.CDLL:
         L.cs_forward_embeddings.argtypes = [vp, vp, vp, i64, i64, C.c_int32, C.c_int32, vp, vp]
         L.cs_plan_tokens.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p, i32p, i32p, C.c_int32, i32p]
         L.cs_linear_bf16.argtypes = [vp, i64, vp, vp, vp, C.c_int32, i64, C.c_int32, C.c_int32, vp]
+        L.cs_linear_kernel.argtypes = [i64, C.c_int32, i64, C.c_int32, C.c_int32, C.c_char_p, C.c_size_t]
         L.cs_attention_varlen.argtypes = [vp, vp, i64, vp, i32p, C.c_int32, C.c_int32, C.c_int32, vp]
         L.cs_pack_batch.argtypes = [i32p, C.c_int32, i64, C.c_int32, i32p, i32p, i32p, i32p]
         L.cs_patchify.argtypes = [vp, C.c_int32, i32p, C.c_int32, C.c_int32, C.c_int32, vp, C.c_int32, i32p, i32p, vp]
@@ -102,7 +103,7 @@ def lib() -> C.CDLL:
         for f in ("cs_encoder_create", "cs_encoder_query", "cs_encode", "cs_encode_static", "cs_encoder_plan_cache_stats", "cs_encode_graph_create",
                   "cs_encode_graph_launch",
                   "cs_forward_embeddings", "cs_plan_tokens",
-                  "cs_linear_bf16", "cs_attention_varlen", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
+                  "cs_linear_bf16", "cs_linear_kernel", "cs_attention_varlen", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
                   "cs_encoder_read_timing", "cs_patchify", "cs_mfma_ceiling", "cs_pack_batch", "cs_channel_create",
                   "cs_channel_acquire", "cs_channel_publish", "cs_channel_forward", "cs_channel_release",
                   "cs_channel_describe", "cs_xchannel_create", "cs_xchannel_open", "cs_xchannel_acquire",
@@ -444,6 +445,13 @@ def cs_linear_bf16(A, W, bias, out, stream=None) -> None:
     _check(lib().cs_linear_bf16(A.data_ptr(), A.stride(0), W.data_ptr(), bias.data_ptr() if bias is not None else None,
                                 out.data_ptr(), CS_BF16 if out.dtype == torch.bfloat16 else CS_F32, M, N, K,
                                 _stream(stream)))
+
+
+def cs_linear_kernel(M: int, N: int, K: int, lda: int = 0, out_dtype: str = "f32") -> str:
+    """Name of the kernel instantiation cs_linear_bf16 runs for these sizes (lda 0: K)."""
+    buf = C.create_string_buffer(128)
+    _check(lib().cs_linear_kernel(lda or K, CS_BF16 if out_dtype == "bf16" else CS_F32, M, N, K, buf, 128))
+    return buf.value.decode()
 
 
 def cs_attention_varlen(qk, vt, out, seg_cu: Sequence[int], n_heads: int, head_dim: int, stream=None) -> None:

@@ -521,10 +521,10 @@ static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   // folds the next RMSNorm into its epilogue, which saves more than the split gains (2048 tokens: 5.33 -> 5.19 ms
   // per step; 1024 tokens: 3.95 -> 4.00 ms, so those stay split).
   if (w.s_proj > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
-      gemm_norm_fold_parts(N, D, D, scaled, ln) > 0)
+      gemm_norm_fold_parts(N, D, D, D, scaled, ln) > 0)
     w.s_proj = 1;
-  w.fold_proj = w.s_proj == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, D, scaled, ln) : 0;
-  w.fold_down = w.s_down == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, e->I_pad, scaled, ln) : 0;
+  w.fold_proj = w.s_proj == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, D, D, scaled, ln) : 0;
+  w.fold_down = w.s_down == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, e->I_pad, e->I_ld, scaled, ln) : 0;
   w.ss = take((w.fold_proj || w.fold_down) ? (size_t)8 * w.ss_stride * 4 : 0);
   w.s1 = take(ln && (w.fold_proj || w.fold_down) ? (size_t)8 * w.ss_stride * 4 : 0);
   w.total = off;
@@ -777,7 +777,7 @@ cs_status cs_encoder_step_kernel(const cs_encoder* enc, int32_t step, int64_t n_
   if (epi == EPI_RESADD_F32 && c.arch == CS_ARCH_AUDIO && !fold_off() &&
       (n_tokens > SPLIT_K_MAX_TOKENS || k_parts(n_tokens, D, g.K) == 1))
     g.s1_out = reinterpret_cast<float*>(uintptr_t(16));   // describe mode: only looked at, never written
-  g.lda = g.K;
+  g.lda = g.ldw = step == CS_STEP_MLP_DOWN ? enc->I_ld : g.K;
   if (epi == EPI_RESADD_SCALED_F32) g.col_scale = enc->ptr<float>(enc->layers[0].ls1);
   // (batches small enough for split K run other launches; this names the kernel of the unsplit path)
   return launch_gemm(epi, g, nullptr);
@@ -1181,20 +1181,18 @@ cs_status cs_linear_bf16(const void* A, int64_t lda, const void* W, const float*
                          int64_t M, int32_t N, int32_t K, void* stream) {
   if (!A || !W || !C) return fail(CS_ERR_INVALID_ARG, "cs_linear_bf16: NULL argument");
   if (M < 0 || M > 0x7fffffff || N < 0) return fail(CS_ERR_INVALID_ARG, "cs_linear_bf16: sizes");
-  // rows too far apart for a tile's 32-bit offsets go in several launches
-  int64_t rows = std::max<int64_t>(M, 1), cols = std::max<int64_t>(N, 1);
-  while (rows > 1 && !gemm_rows_addressable(rows, lda)) rows = std::min<int64_t>(rows, 256) / 2;
-  while (cols > 8 && !gemm_rows_addressable(cols, K)) cols = (std::min<int64_t>(cols, 256) / 2 + 7) & ~int64_t(7);
-  for (int64_t m = 0; m < M; m += rows)
-    for (int64_t n = 0; n < N; n += cols) {
-      GemmArgs g = {};
-      g.A = static_cast<const bf16_t*>(A) + m * lda; g.lda = lda; g.W = static_cast<const bf16_t*>(W) + n * K;
-      g.bias = bias ? bias + n : nullptr;
-      g.out = static_cast<unsigned char*>(C) + (m * N + n) * (c_dtype == CS_BF16 ? 2 : 4);
-      g.ldo = N; g.M = (int32_t)std::min(rows, M - m); g.N = (int32_t)std::min<int64_t>(cols, N - n); g.K = K;
-      if (cs_status st = launch_gemm(c_dtype == CS_BF16 ? EPI_BF16 : EPI_F32, g, static_cast<hipStream_t>(stream))) return st;
-    }
-  return CS_OK;
+  GemmArgs g = {};
+  g.A = static_cast<const bf16_t*>(A); g.lda = lda; g.W = static_cast<const bf16_t*>(W); g.bias = bias;
+  g.out = C; g.ldo = N; g.M = (int32_t)M; g.N = N; g.K = K;
+  return launch_gemm(c_dtype == CS_BF16 ? EPI_BF16 : EPI_F32, g, static_cast<hipStream_t>(stream));
+}
+
+cs_status cs_linear_kernel(int64_t lda, int32_t c_dtype, int64_t M, int32_t N, int32_t K, char* out, size_t capacity) {
+  if (!out || capacity < 96) return fail(CS_ERR_INVALID_ARG, "cs_linear_kernel: NULL argument or capacity below 96");
+  if (M <= 0 || M > 0x7fffffff || N <= 0) return fail(CS_ERR_INVALID_ARG, "cs_linear_kernel: sizes");
+  GemmArgs g = {};
+  g.lda = lda; g.ldo = N; g.M = (int32_t)M; g.N = N; g.K = K; g.describe = out;
+  return launch_gemm(c_dtype == CS_BF16 ? EPI_BF16 : EPI_F32, g, nullptr);
 }
 
 static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,

@@ -111,15 +111,17 @@ struct GemmArgs {
   int32_t plain_stores;
 };
 
-// The kernels address the rows of a tile (at most 256) by 32-bit byte offsets from its first row.
+// Whether the rows of a tile (at most 256) can be addressed by 32-bit byte offsets from its first row, as all GEMM
+// kernels but one do; launch_gemm takes the one with 64-bit row pointers otherwise.
 inline bool gemm_rows_addressable(int64_t rows, int64_t pitch) {
   const int64_t n = (rows < 256 ? rows : 256) - 1;
   return n <= 0 || (pitch >= 0 && pitch <= (0xFFFFFF00ll / 2 - 64) / n);
 }
 cs_status launch_gemm(int epilogue, const GemmArgs& g, hipStream_t stream);
 // Column tiles (= partial sums of squares per row) of a residual GEMM that can fold the next RMSNorm into its
-// epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.
-int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, bool scaled = false, bool sums = false);
+// epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.  pitch: elements
+// between the rows of its operands.
+int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, int64_t pitch, bool scaled = false, bool sums = false);
 
 // ---- write-through global stores -----------------------------------------------------------
 // Every XCD has its own L2, and the end of a kernel writes back whatever is dirty in it before the

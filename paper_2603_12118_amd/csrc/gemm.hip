@@ -209,11 +209,18 @@ struct bool_tag { static constexpr bool value = V; };
 // from it (row and swizzled chunk).  LDS-direct loads go through buffer instructions, not global_load_lds: the
 // compiler counts the latter in both wait counters without a known order, so that every wait for an LDS read in the
 // loop became "all of them" (lgkmcnt(0)); buffer loads count in vmcnt alone and the LDS waits are exact.
-template <int A_LOADS, int B_LOADS>
+// FAR: rows that lie too far apart for 32-bit offsets from the tile's first one (gemm_rows_addressable) are addressed by
+// a 64-bit pointer per load and lane, and fetched with global_load_lds: slower, for pitches that nothing ordinary has.
+template <int A_LOADS, int B_LOADS, bool FAR>
 struct Operands {
   const bf16_t* a;            // uniform
   const bf16_t* w;
   uint32_t a_off[A_LOADS], b_off[B_LOADS];
+};
+template <int A_LOADS, int B_LOADS>
+struct Operands<A_LOADS, B_LOADS, true> {
+  const bf16_t* a[A_LOADS];
+  const bf16_t* w[B_LOADS];
 };
 template <int AUX>
 __device__ __forceinline__ void load_lds16(const bf16_t* base, uint32_t byte_off, unsigned char* lds) {
@@ -222,21 +229,30 @@ __device__ __forceinline__ void load_lds16(const bf16_t* base, uint32_t byte_off
                                            (lds_void*)(uintptr_t)lds, 16, byte_off, 0, 0, AUX);
 #endif
 }
+template <int AUX>
+__device__ __forceinline__ void load_lds16_far(const bf16_t* src, unsigned char* lds) {
+  __builtin_amdgcn_global_load_lds(src, (lds_void*)(uintptr_t)lds, 16, 0, AUX);
+}
 
 // Issues the LDS-direct loads of one 64-wide K slice: every wave instruction moves 64 x 16 bytes
 // from the lanes' global addresses to 1 KB of LDS starting at a wave-uniform address, in lane order.
 // (A wave whose share of the W rows lies beyond the tile, where BN is not a multiple of 8 rows per wave,
 // skips that load: wave-uniform.)
 // One of the A_LOADS + B_LOADS loads of a slice, by index.
-template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN>
-__device__ __forceinline__ void issue_one(const Operands<A_LOADS, B_LOADS>& op, int l, int kt, unsigned char* stage, int wave) {
-  if (l < A_LOADS)
-    load_lds16<CS_GEMM_A_AUX>(op.a + (int64_t)kt * 64, op.a_off[l], stage + (l * NWAVES + wave) * 1024);
-  else if (BN % (8 * NWAVES) == 0 || ((l - A_LOADS) * NWAVES + wave) * 8 < BN)
-    load_lds16<CS_GEMM_W_AUX>(op.w + (int64_t)kt * 64, op.b_off[l - A_LOADS], stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024);
+template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN, bool FAR>
+__device__ __forceinline__ void issue_one(const Operands<A_LOADS, B_LOADS, FAR>& op, int l, int kt, unsigned char* stage, int wave) {
+  if (l < A_LOADS) {
+    unsigned char* lds = stage + (l * NWAVES + wave) * 1024;
+    if constexpr (FAR) load_lds16_far<CS_GEMM_A_AUX>(op.a[l] + (int64_t)kt * 64, lds);
+    else load_lds16<CS_GEMM_A_AUX>(op.a + (int64_t)kt * 64, op.a_off[l], lds);
+  } else if (BN % (8 * NWAVES) == 0 || ((l - A_LOADS) * NWAVES + wave) * 8 < BN) {
+    unsigned char* lds = stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024;
+    if constexpr (FAR) load_lds16_far<CS_GEMM_W_AUX>(op.w[l - A_LOADS] + (int64_t)kt * 64, lds);
+    else load_lds16<CS_GEMM_W_AUX>(op.w + (int64_t)kt * 64, op.b_off[l - A_LOADS], lds);
+  }
 }
-template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN>
-__device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS>& op, int kt, unsigned char* stage, int wave) {
+template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN, bool FAR>
+__device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS, FAR>& op, int kt, unsigned char* stage, int wave) {
 #pragma unroll
   for (int l = 0; l < A_LOADS + B_LOADS; ++l) issue_one<A_LOADS, B_LOADS, NWAVES, BM, BN>(op, l, kt, stage, wave);
 }
@@ -260,7 +276,7 @@ __device__ __forceinline__ void issue_slice(const Operands<A_LOADS, B_LOADS>& op
 // The loads of slice s + STAGES go out one at a time between MFMAs, from the barrier of slice s (which frees that
 // slice's buffer) to the middle of the first k-step of slice s + 1: in one burst they queue in the texture-address
 // unit (16 clocks each, all waves at once) and every wave sits in the issue stall.
-template <int BM, int BN, int WGM, int WGN, bool W_FIRST, int STAGES, typename F, typename G>
+template <int BM, int BN, int WGM, int WGN, bool W_FIRST, int STAGES, bool FAR, typename F, typename G>
 __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem, int m0, int n0,
                                           f32x4 (&acc)[BM / WGM / 32][(BN / WGN + 31) / 32][4], F&& before_last, G&& in_last) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -300,20 +316,26 @@ __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem
       for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int lr = lane >> 3;  // row inside an 8-row group
-  Operands<A_LOADS, B_LOADS> op;
-  op.a = g.A + (int64_t)m0 * g.lda;
-  op.w = g.W + (int64_t)n0 * g.ldw;
+  Operands<A_LOADS, B_LOADS, FAR> op;
+  if constexpr (!FAR) {
+    op.a = g.A + (int64_t)m0 * g.lda;
+    op.w = g.W + (int64_t)n0 * g.ldw;
+  }
 #pragma unroll
   for (int i = 0; i < A_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;  // row inside the tile
     const int r = m0 + rt < M ? rt : M - 1 - m0;
-    op.a_off[i] = (uint32_t)r * (uint32_t)(g.lda * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
+    const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
+    if constexpr (FAR) op.a[i] = g.A + (int64_t)(m0 + r) * g.lda + chunk * 8;
+    else op.a_off[i] = (uint32_t)r * (uint32_t)(g.lda * 2) + (chunk << 4);
   }
 #pragma unroll
   for (int i = 0; i < B_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;
     const int r = n0 + rt < N ? rt : N - 1 - n0;
-    op.b_off[i] = (uint32_t)r * (uint32_t)(g.ldw * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
+    const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
+    if constexpr (FAR) op.w[i] = g.W + (int64_t)(n0 + r) * g.ldw + chunk * 8;
+    else op.b_off[i] = (uint32_t)r * (uint32_t)(g.ldw * 2) + (chunk << 4);
   }
   const int KT = K >> 6;
 
@@ -446,7 +468,7 @@ constexpr bool light_tail() {
 
 // One output tile: K loop and epilogue.
 // LDS_ALLOC: bytes of LDS the launch has (that of its largest tile shape).
-template <int BM, int BN, int WGM, int WGN, int EPI, int STAGES, int LDS_ALLOC>
+template <int BM, int BN, int WGM, int WGN, int EPI, int STAGES, int LDS_ALLOC, bool FAR = false>
 __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem, const int m0, const int n0) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = (WN + 31) / 32;
@@ -556,7 +578,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
       // the operands swapped the two halves of a 16x16x32 group index swap too (vsub).
       constexpr int VB = TM % 2 == 0 ? 2 : 1;   // row blocks of 32 tokens that leave together
       float bv[TN][4];
-      main_loop<BM, BN, WGM, WGN, false, STAGES>(g, smem, m0, n0, acc, [&] {
+      main_loop<BM, BN, WGM, WGN, false, STAGES, FAR>(g, smem, m0, n0, acc, [&] {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -635,7 +657,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   constexpr int CQ = 2;
   f32x4 bias_r[TN][CQ];
   [[maybe_unused]] f32x4 scale_r[EPI == EPI_RESADD_SCALED_F32 ? TN : 1][CQ];
-  main_loop<BM, BN, WGM, WGN, true, STAGES>(g, smem, m0, n0, acc, [&] {
+  main_loop<BM, BN, WGM, WGN, true, STAGES, FAR>(g, smem, m0, n0, acc, [&] {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -940,7 +962,7 @@ constexpr int launch_lds_bytes() {
   return light > main_tile ? light : main_tile;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES>
+template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES, bool FAR>
 __global__ __launch_bounds__(64 * WGM * WGN)
 // (the four-wave 128 x 160 tile must leave room for a second workgroup on the CU: 256 registers, not 512)
 __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
@@ -959,6 +981,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
   int nb = gridDim.x;
   constexpr bool LIGHT = TAIL == TAIL_LIGHT;
   static_assert(!LIGHT || light_tail<BN, WGM, WGN, EPI>(), "no 64-row tile for this shape");
+  static_assert(!FAR || TAIL == TAIL_NONE, "far rows: whole tiles only");
   static_assert(TAIL != TAIL_SPLIT || (BM / 2 / WGM) % 32 == 0, "half tiles need whole 32-row blocks per wave");
   if constexpr (TAIL == TAIL_SPLIT) {
     // workgroups [0, n_main) run the full rounds; the rest each take half of a tile of the last round
@@ -1004,7 +1027,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
   }
   int m0, n0;
   tile_origin<BM, BN>(bid, tiles_m, tiles_n, m0, n0);
-  tile_body<BM, BN, WGM, WGN, EPI, STAGES, LDS>(g, smem, m0, n0);
+  tile_body<BM, BN, WGM, WGN, EPI, STAGES, LDS, FAR>(g, smem, m0, n0);
 }
 
 // Measurement switch: CS_GEMM_NO_TAIL_SPLIT=1 in the environment keeps whole tiles in the last round, so
@@ -1017,14 +1040,14 @@ static bool tail_split_off() {
   return off;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES>
+template <int BM, int BN, int WGM, int WGN, int EPI, int TAIL, int STAGES, bool FAR = false>
 static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   constexpr int NT = 64 * WGM * WGN;
   constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL, STAGES>();
   static_assert(LDS <= 160 * 1024, "LDS of a CU");
-  auto kern = gemm_kernel<BM, BN, WGM, WGN, EPI, TAIL, STAGES>;
+  auto kern = gemm_kernel<BM, BN, WGM, WGN, EPI, TAIL, STAGES, FAR>;
   if (g.describe) {
-    snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32", BM, BN, WGM, WGN, EPI, TAIL);
+    snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32%s", BM, BN, WGM, WGN, EPI, TAIL, FAR ? ", far rows" : "");
     return CS_OK;
   }
   // one attribute call per instantiation (two threads that both see `false` repeat a harmless call)
@@ -1122,6 +1145,9 @@ static int small_tile(int64_t M, int64_t N, int64_t parts, int first) {
 
 template <int EPI>
 static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
+  // rows whose offsets inside a tile do not fit 32 bits
+  if (!gemm_rows_addressable(g.M, g.lda) || !gemm_rows_addressable(g.N, g.ldw))
+    return launch_one<128, 128, 2, 2, EPI, TAIL_NONE, 2, true>(g, stream);
   // Tile choice by the number of workgroups it yields for the 256 CUs.
   constexpr bool RESADD = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SUMS_F32 || EPI == EPI_RESADD_SCALED_F32;
   // At most one round of small tiles.  (A residual GEMM stays on tiles of which a row has at most eight, so that the
@@ -1190,12 +1216,12 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   return launch_cfg<128, 128, 2, 2, EPI>(g, stream);
 }
 
-int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, bool scaled, bool sums) {
+int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, int64_t pitch, bool scaled, bool sums) {
   // ask the launcher itself which tile such a residual GEMM runs on: one partial sum per column tile
   if (M <= 0 || M > 0x7fffffff || N <= 0 || K <= 0 || (N & 3) || (K & 63)) return 0;
   char name[96] = {0};
   GemmArgs g = {};
-  g.M = (int32_t)M; g.N = (int32_t)N; g.K = (int32_t)K; g.lda = K; g.ldo = N; g.describe = name;
+  g.M = (int32_t)M; g.N = (int32_t)N; g.K = (int32_t)K; g.lda = g.ldw = pitch; g.ldo = N; g.describe = name;
   g.col_scale = scaled ? reinterpret_cast<const float*>(uintptr_t(16)) : nullptr;   // only its alignment is looked at
   g.s1_out = sums ? reinterpret_cast<float*>(uintptr_t(16)) : nullptr;              // a LayerNorm tower: sums as well
   int bm = 0, bn = 0;
@@ -1219,9 +1245,6 @@ cs_status launch_gemm(int epilogue, const GemmArgs& g_in, hipStream_t stream) {
     return fail(CS_ERR_INVALID_ARG, "gemm: A and W rows must be 16-byte aligned");
   if ((g.N & 3) || (g.ldo & 3) || (reinterpret_cast<uintptr_t>(g.out) & 15) || (reinterpret_cast<uintptr_t>(g.bias) & 15))
     return fail(CS_ERR_UNSUPPORTED, "gemm: N and the output row stride must be multiples of 4, out and bias 16-byte aligned");
-  // a lane addresses its rows of a tile by a 32-bit byte offset from the tile's first row
-  if (!gemm_rows_addressable(g.M, g.lda) || !gemm_rows_addressable(g.N, g.ldw))
-    return fail(CS_ERR_UNSUPPORTED, "gemm: the rows of a tile of A or W span 4 GiB or more");
   switch (epilogue) {
     case EPI_BF16: return launch_epi<EPI_BF16>(g, stream);
     case EPI_F32: return launch_epi<EPI_F32>(g, stream);
