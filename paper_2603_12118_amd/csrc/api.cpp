@@ -264,7 +264,9 @@ static size_t pack_vector(Arena& A, const SrcTensor& t, int64_t n_pad, RowOf idx
 // Rows whose pitch is a multiple of 1 KB start on few of the memory channels, and the rows of a tile are read in step:
 // a line of 128 bytes more per row spreads them (pitch 10240 B, 24 000 x 1280 x 5120: 255 -> 245 us; 8192 B,
 // 8224 x 1024 x 4096: 84.1 -> 78.4 us; pitches of 2048 and 2560 B at K = 1024 and 1280: no change).
-static int activation_pitch(int cols) { return cols >= 2048 && cols % 512 == 0 ? cols + 64 : cols; }
+// Not with a rotary table, whose place in the workspace pays for the 128 bytes per token elsewhere: a batch that fits a
+// workspace of a given size, the static scratch for one, must go on fitting it.
+static int activation_pitch(int cols, bool rope) { return !rope && cols >= 2048 && cols % 512 == 0 ? cols + 64 : cols; }
 
 static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
   const cs_encoder_config& c = e->cfg;
@@ -667,10 +669,10 @@ static cs_status encoder_create(const cs_encoder_config* config, const cs_tensor
   const cs_encoder_config& c = e->cfg;
   e->P_pad = (int)round_up(c.patch_dim, 64);
   e->I_pad = (int)round_up(c.mlp_dim, 64);
-  e->I_ld = activation_pitch(e->I_pad);
   e->MH_pad = c.arch != CS_ARCH_AUDIO ? (int)round_up(c.merger_hidden, 64) : 0;
   e->half = c.head_dim / 2;
   e->rope = c.arch == CS_ARCH_VIT && (c.rope_sections[0] + c.rope_sections[1] + c.rope_sections[2]) > 0;
+  e->I_ld = activation_pitch(e->I_pad, e->rope);
   Arena A;
   A.alloc(256);  // offset 0 stays unused so that 0 can mean "absent"
   cs_status st = build_weights(e, wb, A);

@@ -60,3 +60,18 @@ def test_static_scratch_refuses_what_does_not_fit():
     assert ei.value.status == B.CS_ERR_WORKSPACE and "static scratch" in str(ei.value)
     torch.cuda.synchronize()
     assert not out.any()          # refused before anything was enqueued
+
+
+def test_static_scratch_holds_a_wide_mlp():
+    # a rotary tower whose MLP rows are a multiple of 1 KB: 1352 tokens take 67 054 080 bytes or a little less, of
+    # 67 108 864; a pitch of 128 bytes more per token would not fit
+    cfg = replace(wl.vit_7b_config(1), dtype="bf16", full_attn_layers=(), mlp_dim=4096)
+    w = wl.images_workload("one_image", cfg, [(364, 728)], seq_len=1024)
+    enc = B.Encoder(cfg, w.weights)
+    _, ws_bytes = enc.cs_encoder_query(w.cu_seqlens, w.grid_thw)
+    assert (64 << 20) - 128 * 1352 < ws_bytes <= 64 << 20
+    x = dev_bf16(w.patches)
+    ref, _ = enc.cs_encode(x, w.cu_seqlens, w.grid_thw)
+    out = enc.cs_encode_static(x, w.cu_seqlens, w.grid_thw)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
