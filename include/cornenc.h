@@ -350,6 +350,17 @@ cs_status cs_xchannel_describe(cs_xchannel* ch, int32_t slot, int32_t* state, co
 cs_status cs_plan_tokens(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
                          int32_t n_items, int32_t* src_row, int32_t* out_row, int32_t* win_cu,
                          int32_t win_cu_capacity, int32_t* n_windows);
+/* The same for the work lists of the full-attention layers (audio: of every layer): `work` [n_full + n_tail, 4]
+ * (or NULL) receives query range and key range (q0, q1, kv0, kv1) of each item, internal token order, the items of
+ * the main launch first, then those of the launch for short last blocks (items of at most 64 queries). */
+typedef struct {
+  int32_t n_full, n_tail;
+  int32_t q_per_block;     /* queries an item of the main list has at most: 64, 128 or 256 */
+  int32_t key_groups;      /* groups of a workgroup's waves that share out the key tiles of an item, */
+  int32_t tail_key_groups; /* ... of the main list and of the short items (1: no groups) */
+} cs_attention_plan;
+cs_status cs_plan_attention(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
+                            int32_t n_items, int32_t* work, int32_t work_capacity, cs_attention_plan* out);
 
 /* Component calls: the two contraction kernels on their own, for parity tests and
  * micro-benchmarks.  All pointers dev.

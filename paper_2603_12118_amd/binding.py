@@ -40,6 +40,10 @@ class cs_encoder_config(C.Structure):
                 ("conv_kernel", C.c_int32), ("input_order", C.c_int32), ("attn_chunk", C.c_int32)]
 
 
+class cs_attention_plan(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("n_full", "n_tail", "q_per_block", "key_groups", "tail_key_groups")]
+
+
 class cs_tensor(C.Structure):
     _fields_ = [("name", C.c_char_p), ("data", C.c_void_p), ("numel", C.c_int64)]
 
@@ -68,6 +72,7 @@ def lib() -> C.CDLL:
         L.cs_encoder_plan_cache_stats.argtypes = [vp, C.POINTER(i64), C.POINTER(i64)]
         L.cs_forward_embeddings.argtypes = [vp, vp, vp, i64, i64, C.c_int32, C.c_int32, vp, vp]
         L.cs_plan_tokens.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p, i32p, i32p, C.c_int32, i32p]
+        L.cs_plan_attention.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p, C.c_int32, C.POINTER(cs_attention_plan)]
         L.cs_linear_bf16.argtypes = [vp, i64, vp, vp, vp, C.c_int32, i64, C.c_int32, C.c_int32, vp]
         L.cs_linear_kernel.argtypes = [i64, C.c_int32, i64, C.c_int32, C.c_int32, C.c_char_p, C.c_size_t]
         L.cs_attention_varlen.argtypes = [vp, vp, i64, vp, i32p, C.c_int32, C.c_int32, C.c_int32, vp]
@@ -102,7 +107,7 @@ def lib() -> C.CDLL:
         L.cs_last_error.restype = C.c_char_p
         for f in ("cs_encoder_create", "cs_encoder_query", "cs_encode", "cs_encode_static", "cs_encoder_plan_cache_stats", "cs_encode_graph_create",
                   "cs_encode_graph_launch",
-                  "cs_forward_embeddings", "cs_plan_tokens",
+                  "cs_forward_embeddings", "cs_plan_tokens", "cs_plan_attention",
                   "cs_linear_bf16", "cs_linear_kernel", "cs_attention_varlen", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
                   "cs_encoder_read_timing", "cs_patchify", "cs_mfma_ceiling", "cs_pack_batch", "cs_channel_create",
                   "cs_channel_acquire", "cs_channel_publish", "cs_channel_forward", "cs_channel_release",
@@ -287,6 +292,16 @@ def cs_plan_tokens(cfg, cu_seqlens, grid_thw):
     _check(lib().cs_plan_tokens(C.byref(cc), _i32p(cu), _i32p(g), n_items, _i32p(src_row),
                                 _i32p(out_row), _i32p(win_cu), n + 2, C.byref(nw)))
     return src_row[:n_tok], out_row[:n_tok // 4], win_cu[:nw.value + 1].copy()
+
+
+def cs_plan_attention(cfg, cu_seqlens, grid_thw):
+    """Host-only: (plan, full items, tail items) of the full-attention layers; items are rows (q0, q1, kv0, kv1)."""
+    cu, g = _i32(cu_seqlens), _i32(grid_thw)
+    cc, p = make_config(cfg), cs_attention_plan()
+    _check(lib().cs_plan_attention(C.byref(cc), _i32p(cu), _i32p(g), g.shape[0], None, 0, C.byref(p)))
+    work = np.empty((p.n_full + p.n_tail, 4), np.int32)
+    _check(lib().cs_plan_attention(C.byref(cc), _i32p(cu), _i32p(g), g.shape[0], _i32p(work), len(work), C.byref(p)))
+    return p, work[:p.n_full], work[p.n_full:]
 
 
 def cs_forward_embeddings(src, placeholder_index, dst_seq, err_flag=None, stream=None) -> None:

@@ -53,15 +53,22 @@ static void push_full(std::vector<int32_t>& full, std::vector<int32_t>& tail, in
   }
 }
 
-// Where a full-attention list of `blocks` 256-query items would leave a quarter of the CUs without one, and a workgroup
-// walks more than eight key tiles, the items are cut to 128 queries and share out their tiles between two key groups
-// of the workgroup (attention.hip).  Head dimension 64.  Measured, whole encoder: one 1500-token clip (120 items)
-// 5.08 -> 4.81 ms, one class-token tile (64) 2.89 -> 2.46, three (192) 4.40 -> 4.15, four (256) the same, four
-// 600-token clips (240) 6.87 -> 6.92.
-constexpr int64_t SHARE_KEYS_MAX_ITEMS = 192;
+// Key groups (attention.hip): where a full-attention launch leaves CUs idle and a workgroup walks more than eight key
+// tiles, its items are cut to 128 queries and their tiles shared out between two groups of the workgroup's waves.
+// Head dimension 64.  The limit is how many workgroups a CU gets: an item of 128 queries with groups takes 0.8 of the
+// time of one of 256 without, two of them on a CU more than one of those.  Attention per layer, without -> with groups:
+//   one each:        120 -> 240 workgroups (1500 tokens x 20 heads) 36.1 -> 29.0 us, 120 -> 200 (2 x 600 x 20) 18.9 -> 16.0
+//   one against two: 180 -> 300 (3 x 600 x 20) 19.9 -> 21.4, 160 -> 320 (2000 x 20) 44.5 -> 46.6, 192 -> 384 (4 x 680 x 16) 22.0 -> 24.6
+//   two each:        300 -> 500 (5 x 600 x 20) 30.9 -> 23.6, 288 -> 480 (6 x 580 x 16) 30.1 -> 23.3
+// Where the last query blocks would go to a launch of their own (push_full), that launch is saved too and groups pay up
+// to 192 256-query items: 144 (3 x 788 x 16) 35.0 -> 26.5, 192 (3 x 1028 x 16) 41.9 -> 32.2, 256 (4 x 1028 x 16) the same.
+// (512 keys is where this was first looked at; 256 keys 12.1 -> 11.2, 512 keys 16.1 -> 13.7, 128 keys 8.6 -> 9.2.)
 constexpr int SHARE_KEYS_MIN = 512, SHARE_KEYS_MAX = 1 << 16;   // (the kernel's 32-bit offsets hold for far more)
-static bool share_keys(const cs_encoder_config& cfg, int64_t blocks, int max_keys) {
-  return cfg.head_dim == 64 && blocks * cfg.n_heads <= SHARE_KEYS_MAX_ITEMS && max_keys > SHARE_KEYS_MIN && max_keys <= SHARE_KEYS_MAX;
+static bool share_keys(const cs_encoder_config& cfg, int64_t items_256, int64_t items_128, bool tail_launch, int max_keys) {
+  if (cfg.head_dim != 64 || max_keys <= SHARE_KEYS_MIN || max_keys > SHARE_KEYS_MAX) return false;
+  const int64_t without = items_256 * cfg.n_heads, with = items_128 * cfg.n_heads;
+  if (tail_launch && without <= 192) return true;
+  return with <= 256 || (without > 256 && with <= 512);
 }
 
 cs_status build_vit_plan(const cs_encoder_config& cfg, const int32_t* cu, const int32_t* grid, int32_t n_items,
@@ -167,7 +174,9 @@ cs_status build_cls_plan(const cs_encoder_config& cfg, int32_t n_positions, cons
   out_row.reserve(p.n_groups);
   int64_t out_base = 0;
   // (every tile of a batch has n_positions keys)
-  const bool share = share_keys(cfg, (int64_t)n_items * ((n_positions + 3) / 256), n_positions);
+  const int tokens = n_positions + 3;
+  const bool tail = tokens % 256 > 0 && tokens % 256 <= 64;   // as push_full cuts
+  const bool share = share_keys(cfg, (int64_t)n_items * ((tokens + 255) / 256 - tail), (int64_t)n_items * ((tokens + 127) / 128), tail, n_positions);
   if (share) p.full_q_per_block = 128;
   p.full_key_groups = share ? 2 : 1;
   // (the tail items, four queries each, in four groups: 19.8 -> 13.9 us per layer of eight tiles)
@@ -232,13 +241,17 @@ cs_status build_audio_plan(const cs_encoder_config& cfg, const int32_t* cu, cons
   int off = 0, tok = 0;
   // short chunks: two-wave workgroups of 64 queries instead of eight waves of which most would idle
   int max_seg = 0;
-  int64_t blocks = 0;
+  int64_t items_256 = 0, items_128 = 0;
   for (int i = 0; i < n_items; ++i) {
     const int n = grid[3 * i + 2] / 2, seg = cfg.attn_chunk > 0 ? std::min(cfg.attn_chunk, n) : n;
     max_seg = std::max(max_seg, seg);
-    blocks += (int64_t)((n + seg - 1) / seg) * ((seg + 255) / 256);
+    for (int s0 = 0; s0 < n; s0 += seg) {
+      const int len = std::min(seg, n - s0);
+      items_256 += (len + 255) / 256;
+      items_128 += (len + 127) / 128;
+    }
   }
-  const bool share = share_keys(cfg, blocks, max_seg);
+  const bool share = share_keys(cfg, items_256, items_128, false, max_seg);
   p.full_key_groups = share ? 2 : 1;
   const int qpb = share ? 128 : cfg.attn_chunk > 0 && cfg.attn_chunk <= 128 ? 64 : 256;
   p.full_q_per_block = qpb;

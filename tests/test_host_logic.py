@@ -244,3 +244,75 @@ def test_flop_model_matches_hand_count():
     att = 28 * 4 * (8 * 16 * 64 ** 2) * d + 4 * 4 * (8 * 1024 ** 2) * d
     assert f["total"] == lin + att
     assert abs(f["total"] / 1e12 - 10.78) < 0.01
+
+
+# ---- work lists of the full-attention layers
+def attention_lists(cfg, grid):
+    g = np.asarray(grid, np.int32)
+    cu = np.concatenate([[0], np.cumsum(g.astype(np.int64).prod(1))]).astype(np.int32)
+    p, full, tail = B.cs_plan_attention(cfg, cu, g)
+    # every query of every segment once, with the keys of its segment and no item longer than its workgroup takes
+    segs, base = [], 0
+    for t, h, w in grid:
+        if cfg.arch == "audio":
+            n = w // 2
+            chunk = cfg.attn_chunk or n
+            segs += [(base + c, base + min(c + chunk, n)) * 2 for c in range(0, n, chunk)]
+        else:
+            n = t * h * w + (4 if cfg.arch == "vit_cls" else 0)
+            segs.append((base, base + n, base, base + n - (3 if cfg.arch == "vit_cls" else 0)))
+        base += n
+    got = sorted(map(tuple, np.concatenate([full, tail]).tolist()))
+    merged = []
+    for q0, q1, k0, k1 in got:
+        if merged and merged[-1][1] == q0 and merged[-1][2:] == [k0, k1]:
+            merged[-1][1] = q1
+        else:
+            merged.append([q0, q1, k0, k1])
+    assert [tuple(m) for m in merged] == segs
+    assert (full[:, 1] - full[:, 0]).max() <= p.q_per_block and (full[:, 1] > full[:, 0]).all()
+    assert all(0 < q1 - q0 <= 64 for q0, q1, _, _ in tail)
+    return p, full, tail
+
+
+def takes_key_groups(lens, heads, tail_launch=False):
+    """More than 512 keys, and a CU gets no more workgroups of 128 queries with groups than of 256 without, up to two;
+    or the groups save the launch for short last blocks and there are at most 192 of the latter."""
+    without = heads * sum((n // 256 + (n % 256 > 64)) if tail_launch else -(-n // 256) for n in lens)
+    with_ = heads * sum(-(-n // 128) for n in lens)
+    return max(lens) > 512 and (with_ <= 256 or (without > 256 and with_ <= 512) or (tail_launch and without <= 192))
+
+
+@pytest.mark.parametrize("h,w", [(32, 32), (24, 24), (26, 26), (28, 28), (22, 24), (46, 46), (60, 64)])
+def test_class_token_tiles_take_key_groups_by_their_number_of_items(h, w):
+    n_tok = h * w + 4
+    for n in range(1, 9):
+        p, full, tail = attention_lists(wl.vit_cls_config(), [(1, h, w)] * n)
+        grouped = h * w + 1 > 512 and takes_key_groups([n_tok] * n, 16, 0 < n_tok % 256 <= 64)
+        assert (p.key_groups, p.q_per_block) == ((2, 128) if grouped else (1, 256)), n
+        if not grouped:
+            assert p.n_full == n * (n_tok // 256 + (n_tok % 256 > 64)) and p.n_tail == n * (0 < n_tok % 256 <= 64)
+
+
+def test_key_groups_where_both_sides_were_measured():
+    for side, n, groups in [(24, 3, 2), (24, 4, 1), (24, 5, 1), (24, 6, 2), (24, 8, 1), (26, 4, 1), (28, 4, 2), (32, 1, 2),
+                            (32, 3, 2), (32, 6, 1), (40, 1, 2), (40, 2, 1)]:
+        assert attention_lists(wl.vit_cls_config(), [(1, side, side)] * n)[0].key_groups == groups, (side, n)
+    for frames, n, groups in [(3000, 1, 2), (1200, 2, 2), (1200, 3, 1), (1200, 4, 1), (1200, 5, 2), (2000, 2, 1), (4000, 1, 1),
+                              (3000, 2, 1), (3000, 16, 1), (1024, 1, 1)]:
+        assert attention_lists(wl.audio_config(), [(1, 1, frames)] * n)[0].key_groups == groups, (frames, n)
+
+
+@pytest.mark.parametrize("frames,chunk", [([3000], 0), ([3000, 64], 0), ([64, 8, 1208], 0), ([1208] * 4, 0), ([2048], 0),
+                                          ([1024], 0), ([1032], 0), ([1960, 1208], 100), ([1960, 1208], 52),
+                                          ([3000], 700), ([3000] * 8, 0), ([1200] + [8] * 500, 0)])
+def test_audio_attention_items(frames, chunk):
+    p, full, _ = attention_lists(replace(wl.audio_config(), attn_chunk=chunk), [(1, 1, f) for f in frames])
+    lens = [min(chunk or f // 2, f // 2 - s) for f in frames for s in range(0, f // 2, chunk or f // 2)]
+    assert p.key_groups == (2 if takes_key_groups(lens, 20) else 1)
+
+
+def test_vision_tower_attention_items():
+    for grid in ([(1, 32, 32)], [(1, 4, 4), (1, 2, 130)], [(8, 32, 32)] * 2, [(1, 18, 34)]):
+        p, full, tail = attention_lists(wl.vit_7b_config(), grid)
+        assert (p.key_groups, p.tail_key_groups, p.q_per_block) == (1, 1, 256)
