@@ -179,8 +179,11 @@ cs_status build_cls_plan(const cs_encoder_config& cfg, int32_t n_positions, cons
   const bool share = share_keys(cfg, (int64_t)n_items * ((tokens + 255) / 256 - tail), (int64_t)n_items * ((tokens + 127) / 128), tail, n_positions);
   if (share) p.full_q_per_block = 128;
   p.full_key_groups = share ? 2 : 1;
-  // (the tail items, four queries each, in four groups: 19.8 -> 13.9 us per layer of eight tiles)
-  p.tail_key_groups = cfg.head_dim == 64 && n_positions > SHARE_KEYS_MIN && n_positions <= SHARE_KEYS_MAX && n_tok <= 1 << 24 ? 4 : 1;
+  // The tail items, four queries each, in four groups while that is one workgroup per CU; a CU holds two of those and
+  // six of the two-wave ones.  Attention per layer, one -> four groups: 8 tiles x 16 heads 68.2 -> 64.4 us, 16 113.2 ->
+  // 111.4, 24 156.3 -> 158.8, 48 302 -> 314, 96 the same.
+  p.tail_key_groups = cfg.head_dim == 64 && n_positions > SHARE_KEYS_MIN && n_positions <= SHARE_KEYS_MAX &&
+                              n_tok <= 1 << 24 && (int64_t)n_items * cfg.n_heads <= 256 ? 4 : 1;
   for (int i = 0; i < n_items; ++i) {
     const int h = grid[3 * i + 1], w = grid[3 * i + 2];
     const int start = (int)src_row.size();

@@ -312,6 +312,11 @@ def test_audio_attention_items(frames, chunk):
     assert p.key_groups == (2 if takes_key_groups(lens, 20) else 1)
 
 
+@pytest.mark.parametrize("side,n,groups", [(32, 1, 4), (32, 8, 4), (32, 16, 4), (32, 17, 1), (32, 96, 1), (20, 4, 1)])
+def test_tail_items_take_four_key_groups_up_to_one_workgroup_per_cu(side, n, groups):
+    assert attention_lists(wl.vit_cls_config(), [(1, side, side)] * n)[0].tail_key_groups == groups
+
+
 def test_vision_tower_attention_items():
     for grid in ([(1, 32, 32)], [(1, 4, 4), (1, 2, 130)], [(8, 32, 32)] * 2, [(1, 18, 34)]):
         p, full, tail = attention_lists(wl.vit_7b_config(), grid)
