@@ -384,6 +384,12 @@ cs_status cs_linear_kernel(int64_t lda, int32_t c_dtype, int64_t M, int32_t N, i
  * before it returns (cs_encode keeps its work lists in the plan and does neither). */
 cs_status cs_attention_varlen(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,
                               int32_t n_seg, int32_t n_heads, int32_t head_dim, void* stream);
+/* The same with the kernel named: key_groups 1 as above, 2 (128 queries per workgroup) or 4 (64): the key tiles of a
+ * segment shared out between so many groups of a workgroup's waves (head_dim 64), as cs_encode does where a launch
+ * leaves the GPU partly idle.  CS_ERR_UNSUPPORTED, before anything is allocated, for segments whose K rows, or a V^T
+ * pitch whose 64 rows, span 4 GiB. */
+cs_status cs_attention_varlen_groups(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,
+                                     int32_t n_seg, int32_t n_heads, int32_t head_dim, int32_t key_groups, void* stream);
 
 /* Timing of one step of the encoder task with HIP events on the caller's stream (measurement
  * aid; Sec. 1 mentions tracing only in passing).  After cs_encoder_time_step(enc, step), every

@@ -76,6 +76,7 @@ def lib() -> C.CDLL:
         L.cs_linear_bf16.argtypes = [vp, i64, vp, vp, vp, C.c_int32, i64, C.c_int32, C.c_int32, vp]
         L.cs_linear_kernel.argtypes = [i64, C.c_int32, i64, C.c_int32, C.c_int32, C.c_char_p, C.c_size_t]
         L.cs_attention_varlen.argtypes = [vp, vp, i64, vp, i32p, C.c_int32, C.c_int32, C.c_int32, vp]
+        L.cs_attention_varlen_groups.argtypes = [vp, vp, i64, vp, i32p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, vp]
         L.cs_pack_batch.argtypes = [i32p, C.c_int32, i64, C.c_int32, i32p, i32p, i32p, i32p]
         L.cs_patchify.argtypes = [vp, C.c_int32, i32p, C.c_int32, C.c_int32, C.c_int32, vp, C.c_int32, i32p, i32p, vp]
         L.cs_channel_create.argtypes = [C.c_int32, C.c_size_t, C.POINTER(vp)]
@@ -108,7 +109,7 @@ def lib() -> C.CDLL:
         for f in ("cs_encoder_create", "cs_encoder_query", "cs_encode", "cs_encode_static", "cs_encoder_plan_cache_stats", "cs_encode_graph_create",
                   "cs_encode_graph_launch",
                   "cs_forward_embeddings", "cs_plan_tokens", "cs_plan_attention",
-                  "cs_linear_bf16", "cs_linear_kernel", "cs_attention_varlen", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
+                  "cs_linear_bf16", "cs_linear_kernel", "cs_attention_varlen", "cs_attention_varlen_groups", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
                   "cs_encoder_read_timing", "cs_patchify", "cs_mfma_ceiling", "cs_pack_batch", "cs_channel_create",
                   "cs_channel_acquire", "cs_channel_publish", "cs_channel_forward", "cs_channel_release",
                   "cs_channel_describe", "cs_xchannel_create", "cs_xchannel_open", "cs_xchannel_acquire",
@@ -473,6 +474,12 @@ def cs_attention_varlen(qk, vt, out, seg_cu: Sequence[int], n_heads: int, head_d
     seg = _i32(seg_cu)
     _check(lib().cs_attention_varlen(qk.data_ptr(), vt.data_ptr(), vt.stride(0), out.data_ptr(), _i32p(seg),
                                      len(seg) - 1, n_heads, head_dim, _stream(stream)))
+
+
+def cs_attention_varlen_groups(qk, vt, out, seg_cu: Sequence[int], n_heads: int, head_dim: int, key_groups: int, stream=None) -> None:
+    seg = _i32(seg_cu)
+    _check(lib().cs_attention_varlen_groups(qk.data_ptr(), vt.data_ptr(), vt.stride(0), out.data_ptr(), _i32p(seg),
+                                            len(seg) - 1, n_heads, head_dim, key_groups, _stream(stream)))
 
 
 def cs_pack_batch(grid_thw, row_budget: int, max_items: int = 1 << 30):

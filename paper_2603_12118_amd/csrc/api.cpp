@@ -1014,7 +1014,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
 
   // ---- transformer blocks
   AttnArgs aa = {};
-  aa.qk = qk; aa.vt = vt; aa.ld_vt = w.ld_vt; aa.out = attn; aa.n_tok = (int32_t)N; aa.n_heads = c.n_heads; aa.head_dim = c.head_dim;
+  aa.qk = qk; aa.vt = vt; aa.ld_vt = w.ld_vt; aa.out = attn; aa.n_tok = (int32_t)N; aa.n_heads = c.n_heads; aa.head_dim = c.head_dim; aa.max_keys = p.full_max_keys;
   const float q_scale = (float)(1.4426950408889634 / sqrt((double)c.head_dim));
   auto norm = [&](size_t gain, size_t bias) -> cs_status {
     if (folded) return CS_OK;      // the residual GEMM in front has written xn and the sums of squares
@@ -1231,8 +1231,9 @@ cs_status cs_linear_kernel(int64_t lda, int32_t c_dtype, int64_t M, int32_t N, i
 }
 
 static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,
-                                  int32_t n_seg, int32_t n_heads, int32_t head_dim, void* stream_) {
+                                  int32_t n_seg, int32_t n_heads, int32_t head_dim, int32_t key_groups, void* stream_) {
   if (!qk || !vt || !out || !seg_cu || n_seg <= 0) return fail(CS_ERR_INVALID_ARG, "cs_attention_varlen: NULL argument");
+  if (key_groups != 1 && key_groups != 2 && key_groups != 4) return fail(CS_ERR_INVALID_ARG, "cs_attention_varlen: key_groups");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   std::vector<int32_t> work;
   int max_len = 0;
@@ -1240,7 +1241,14 @@ static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt,
     if (seg_cu[s] % 4 || seg_cu[s + 1] <= seg_cu[s]) return fail(CS_ERR_SHAPE, "cs_attention_varlen: segment boundaries");
     max_len = std::max(max_len, seg_cu[s + 1] - seg_cu[s]);
   }
-  const int qpb = max_len <= 64 ? 64 : 256;
+  const bool single = key_groups == 1 && max_len <= 64;
+  const int qpb = key_groups == 2 ? 128 : key_groups == 4 || single ? 64 : 256;
+  AttnArgs a = {};
+  a.qk = static_cast<const bf16_t*>(qk); a.vt = static_cast<const bf16_t*>(vt); a.ld_vt = ld_vt;
+  a.out = static_cast<bf16_t*>(out); a.n_tok = seg_cu[n_seg]; a.n_heads = n_heads; a.head_dim = head_dim;
+  a.q_per_block = qpb; a.single_tile = single; a.key_groups = key_groups; a.max_keys = max_len;
+  if (key_groups > 1 && (head_dim != 64 || !attention_groups_addressable(a)))   // before the work list is allocated
+    return fail(CS_ERR_UNSUPPORTED, "cs_attention_varlen: key groups need head_dim 64 and segments whose keys 32-bit offsets reach");
   for (int s = 0; s < n_seg; ++s)
     for (int q = seg_cu[s]; q < seg_cu[s + 1]; q += qpb) {
       work.push_back(q); work.push_back(std::min(q + qpb, seg_cu[s + 1])); work.push_back(seg_cu[s]); work.push_back(seg_cu[s + 1]);
@@ -1252,10 +1260,7 @@ static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt,
   cs_status st = CS_OK;
   if (he != hipSuccess) st = fail(CS_ERR_HIP, hipGetErrorString(he));
   if (st == CS_OK) {
-    AttnArgs a = {};
-    a.qk = static_cast<const bf16_t*>(qk); a.vt = static_cast<const bf16_t*>(vt); a.ld_vt = ld_vt;
-    a.out = static_cast<bf16_t*>(out); a.work = dwork; a.n_work = (int32_t)(work.size() / 4);
-    a.n_tok = seg_cu[n_seg]; a.n_heads = n_heads; a.head_dim = head_dim; a.q_per_block = qpb; a.single_tile = max_len <= 64;
+    a.work = dwork; a.n_work = (int32_t)(work.size() / 4);
     st = launch_attention(a, stream);
     (void)hipStreamSynchronize(stream);
   }
@@ -1265,7 +1270,12 @@ static cs_status attention_varlen(const void* qk, const void* vt, int64_t ld_vt,
 
 cs_status cs_attention_varlen(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,
                               int32_t n_seg, int32_t n_heads, int32_t head_dim, void* stream) {
-  return guarded("cs_attention_varlen", [&] { return attention_varlen(qk, vt, ld_vt, out, seg_cu, n_seg, n_heads, head_dim, stream); });
+  return guarded("cs_attention_varlen", [&] { return attention_varlen(qk, vt, ld_vt, out, seg_cu, n_seg, n_heads, head_dim, 1, stream); });
+}
+
+cs_status cs_attention_varlen_groups(const void* qk, const void* vt, int64_t ld_vt, void* out, const int32_t* seg_cu,
+                                     int32_t n_seg, int32_t n_heads, int32_t head_dim, int32_t key_groups, void* stream) {
+  return guarded("cs_attention_varlen_groups", [&] { return attention_varlen(qk, vt, ld_vt, out, seg_cu, n_seg, n_heads, head_dim, key_groups, stream); });
 }
 
 static cs_status pack_batch(const int32_t* grid_thw, int32_t n_pending, int64_t row_budget, int32_t max_items,

@@ -135,7 +135,7 @@ void attn_kernel(AttnArgs a) {
   u32x2 vreg[V_PT];
   auto load_tile = [&](int kv) {
     if constexpr (KG > 1) {
-      // the same by 32-bit offsets from the item's first key (launch_attention bounds the keys of such an item): a
+      // the same by 32-bit offsets from the item's first key (attention_groups_addressable): a
       // group's waves hold four times the staging registers, and 64-bit addresses of their own do not fit beside them
       const unsigned char* kb = reinterpret_cast<const unsigned char*>(kbase + (int64_t)w.kv0 * ldq);
       const unsigned char* vb = reinterpret_cast<const unsigned char*>(vbase + w.kv0);
@@ -391,8 +391,8 @@ cs_status launch_attention(const AttnArgs& a, hipStream_t stream) {
   if (a.single_tile && a.q_per_block != 64) return fail(CS_ERR_INVALID_ARG, "attention: single-tile items are 64-query items");
   if (a.q_per_block == 128 ? a.key_groups != 2 : a.key_groups > 1 && (a.key_groups != 4 || a.q_per_block != 64))
     return fail(CS_ERR_INVALID_ARG, "attention: key groups are two of 128-query items or four of 64-query items");
-  if (a.key_groups > 1 && (a.head_dim != 64 || a.single_tile || a.n_tok > 1 << 24))
-    return fail(CS_ERR_UNSUPPORTED, "attention: key groups need head_dim 64, several key tiles and at most 2^24 tokens");
+  if (a.key_groups > 1 && (a.head_dim != 64 || a.single_tile || a.max_keys <= 0 || !attention_groups_addressable(a)))
+    return fail(CS_ERR_UNSUPPORTED, "attention: key groups need head_dim 64 and items whose keys 32-bit offsets reach");
   if (a.head_dim == 80 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<80, 2, 1, true>), grid, dim3(128), 0, stream, a);
   else if (a.head_dim == 80 && a.q_per_block == 64) hipLaunchKernelGGL((attn_kernel<80, 2, 1, false>), grid, dim3(128), 0, stream, a);
   else if (a.head_dim == 80 && a.q_per_block == 256) hipLaunchKernelGGL((attn_kernel<80, 8, 1, false>), grid, dim3(512), 0, stream, a);

@@ -196,8 +196,15 @@ struct AttnArgs {
   int32_t q_per_block;  // 64, 128 or 256 queries per workgroup (work items are cut accordingly)
   int32_t single_tile;  // nonzero: no work item has more than 64 keys (64-query items only)
   int32_t key_groups;   // 2 (128-query items) or 4 (64-query items): the key tiles of an item are shared out inside the
-                        // workgroup (head dimension 64; at most 65 536 keys per item and 2^24 tokens)
+                        // workgroup (head dimension 64, attention_groups_addressable)
+  int32_t max_keys;     // with key groups: the most keys an item has
 };
+// The kernels with key groups address K from the first key of an item and the 64 rows of V^T of a head by 32-bit byte
+// offsets; a group's tiles reach at most key_groups tiles beyond the item's last key.
+inline bool attention_groups_addressable(const AttnArgs& a) {
+  const int64_t rows = (int64_t)a.max_keys + 64 * (a.key_groups + 1), limit = 0xFFFFFFFFll;
+  return a.ld_vt <= limit / 256 && rows * 4 * a.n_heads * a.head_dim <= limit && 64 * a.ld_vt * 2 + rows * 2 <= limit;
+}
 cs_status launch_attention(const AttnArgs& a, hipStream_t stream);
 
 // ---- row-wise and copy kernels ----------------------------------------------------------

@@ -178,6 +178,7 @@ cs_status build_cls_plan(const cs_encoder_config& cfg, int32_t n_positions, cons
   const bool tail = tokens % 256 > 0 && tokens % 256 <= 64;   // as push_full cuts
   const bool share = share_keys(cfg, (int64_t)n_items * ((tokens + 255) / 256 - tail), (int64_t)n_items * ((tokens + 127) / 128), tail, n_positions);
   if (share) p.full_q_per_block = 128;
+  p.full_max_keys = n_positions;
   p.full_key_groups = share ? 2 : 1;
   // The tail items, four queries each, in four groups while that is one workgroup per CU; a CU holds two of those and
   // six of the two-wave ones.  Attention per layer, one -> four groups: 8 tiles x 16 heads 68.2 -> 64.4 us, 16 113.2 ->
@@ -256,6 +257,7 @@ cs_status build_audio_plan(const cs_encoder_config& cfg, const int32_t* cu, cons
   }
   const bool share = share_keys(cfg, items_256, items_128, false, max_seg);
   p.full_key_groups = share ? 2 : 1;
+  p.full_max_keys = max_seg;
   const int qpb = share ? 128 : cfg.attn_chunk > 0 && cfg.attn_chunk <= 128 ? 64 : 256;
   p.full_q_per_block = qpb;
   p.full_single_tile = cfg.attn_chunk > 0 && cfg.attn_chunk <= 64;

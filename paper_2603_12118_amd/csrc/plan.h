@@ -29,6 +29,7 @@ struct BatchPlan {
   int32_t full_q_per_block = 256;   // queries per item of full_work: 256, 128 with key groups, or 64 when the segments are short chunks
   bool full_single_tile = false;    // no full_work item has more than 64 keys
   int32_t full_key_groups = 1, tail_key_groups = 1;   // > 1: the items share out their key tiles inside the workgroup
+  int32_t full_max_keys = 0;        // the most keys an item of either list has (set where there are key groups)
   std::vector<int32_t> win_cu;  // host only: window boundaries in internal token order
   // audio
   int64_t n_pad_rows = 0;   // sum(frames_i + 2): rows of the zero-padded frame buffers

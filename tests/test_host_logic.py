@@ -321,3 +321,14 @@ def test_vision_tower_attention_items():
     for grid in ([(1, 32, 32)], [(1, 4, 4), (1, 2, 130)], [(8, 32, 32)] * 2, [(1, 18, 34)]):
         p, full, tail = attention_lists(wl.vit_7b_config(), grid)
         assert (p.key_groups, p.tail_key_groups, p.q_per_block) == (1, 1, 256)
+
+
+@pytest.mark.parametrize("seg,heads,ld_vt,groups", [([0, 1 << 20], 20, 1 << 20, 2), ([0, 4, 1 << 20], 20, 1 << 20, 4),
+                                                    ([0, 838_848], 20, 838_848, 2),           # 838 848 + 192 rows of 5120 bytes
+                                                    ([0, 1024], 1, 1 << 25, 2), ([0, 1024], 1, 1 << 40, 4)])
+def test_key_groups_refuse_keys_beyond_32_bit_offsets(seg, heads, ld_vt, groups):
+    """Refused from the description alone: the pointers are never looked at and nothing is allocated."""
+    s = np.asarray(seg, np.int32)
+    args = (16, 16, ld_vt, 16, s.ctypes.data_as(C.POINTER(C.c_int32)), len(seg) - 1, heads, 64, groups, None)
+    assert B.lib().cs_attention_varlen_groups(*args) == 5            # CS_ERR_UNSUPPORTED
+    assert B.lib().cs_attention_varlen_groups(*args[:8], 3, None) == 1
