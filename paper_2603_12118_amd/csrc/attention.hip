@@ -36,8 +36,10 @@ __device__ __forceinline__ uint32_t pack2_a(float a, float b) {
 // the time is the number of tiles one workgroup walks (1.4 us each, mostly waiting): 1025 keys, 16 heads 43 us in two
 // launches -> 18.6 us; 1500 keys, 20 heads 34.2 -> 26.2 us.  (Four groups of 64 queries draw twice the bytes: 20.5 and
 // 28.2 us.)  plan.cpp says which batches take it.
+// (Waves per SIMD: four groups are taken for at most one workgroup per CU (plan.cpp), so they have the registers of two.)
+constexpr int attn_waves(int nw, bool single, int kg) { return single ? 3 : nw == 8 && kg < 4 ? 4 : 2; }
 template <int DH, int NW, int QT, bool SINGLE, int KG = 1>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(SINGLE ? 3 : (NW == 8 ? 4 : 2), SINGLE ? 3 : (NW == 8 ? 4 : 2))))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(attn_waves(NW, SINGLE, KG), attn_waves(NW, SINGLE, KG))))
 void attn_kernel(AttnArgs a) {
   constexpr int NWG = NW / KG;           // waves of a key group
   constexpr int NT = 64 * NWG;
@@ -206,11 +208,14 @@ void attn_kernel(AttnArgs a) {
     // ---- S^T tiles: s[it][jt] covers keys kv + jt*32 .. +31 (rows) x queries it*32 .. +31 (lanes)
     // The accumulators start at minus the query's running maximum (a lane's scores all belong to one
     // query), so the products come out as score - maximum and the common case below needs no subtraction.
-    const bool first = kv == kv_first;
+    // `first`: there is no maximum yet.  (With key groups per query: the first tiles of a group may hold nothing but
+    // scores of -inf, which another group's keys outweigh.)
+    bool first[QT];
     f32x16 s[QT][2];
 #pragma unroll
     for (int it = 0; it < QT; ++it) {
-      const float init = first ? 0.f : -mrun[it];
+      first[it] = KG > 1 ? mrun[it] == -INFINITY : kv == kv_first;
+      const float init = first[it] ? 0.f : -mrun[it];
 #pragma unroll
       for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
@@ -259,12 +264,13 @@ void attn_kernel(AttnArgs a) {
       mx = fmaxf(mx, __shfl_xor(mx, 32));          // the tile's largest score minus the running maximum
       // v_exp_f32 directly: arguments are bounded above and results that would be denormal may flush to 0,
       // so the library exp2f's range scaling (four more instructions per score) buys nothing here
-      const bool jump = first || mx > MAX_SLACK;   // every tile holds at least one valid key: mx is finite
+      const bool jump = first[it] || mx > MAX_SLACK;   // (every tile holds at least one valid key)
       if (__any(jump)) {                           // some query of this wave takes a new maximum
-        const float base = first ? 0.f : mrun[it];
+        const float base = first[it] ? 0.f : mrun[it];
         const float mnew = jump ? mx + base : mrun[it];
-        const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(mrun[it] - mnew);
-        const float shift = mnew - base;           // 0 in the lanes whose query keeps its maximum
+        const float alpha = first[it] ? 0.f : __builtin_amdgcn_exp2f(mrun[it] - mnew);
+        float shift = mnew - base;                 // 0 in the lanes whose query keeps its maximum
+        if (KG > 1 && mnew == -INFINITY) shift = 0.f;   // no key with weight yet: the probabilities are exp2(-inf)
         mrun[it] = mnew;
         lrun[it] *= alpha;
 #pragma unroll
@@ -337,7 +343,7 @@ void attn_kernel(AttnArgs a) {
     float m = mrun[0];
 #pragma unroll
     for (int k = 1; k < KG; ++k) m = fmaxf(m, st[(k - 1) * NWG * STATE * 64]);
-    const float a0 = __builtin_amdgcn_exp2f(mrun[0] - m);   // (the first group always has a tile: m is finite)
+    const float a0 = __builtin_amdgcn_exp2f(mrun[0] - m);
     lrun[0] *= a0;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -346,7 +352,7 @@ void attn_kernel(AttnArgs a) {
 #pragma unroll
     for (int k = 1; k < KG; ++k) {
       const float* other = st + (k - 1) * NWG * STATE * 64;
-      const float ak = __builtin_amdgcn_exp2f(other[0] - m);   // 0 for a group without a tile (its maximum is -inf)
+      const float ak = __builtin_amdgcn_exp2f(other[0] - m);   // 0 for a group without a tile, or without a key of weight (its maximum is -inf)
       lrun[0] += ak * other[64];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)

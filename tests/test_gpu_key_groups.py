@@ -69,3 +69,19 @@ def test_audio_clips_of_unequal_length(frames):
         cos = (g * ref).sum(1) / (np.linalg.norm(g, axis=1) * np.linalg.norm(ref, axis=1))
         assert np.abs(g - ref).max() <= MAX_ABS and cos.min() >= MIN_COS, (c.name, np.abs(g - ref).max(), cos.min())
     assert row == len(got)
+
+
+# the keys from 64 on to 127 (the first tile of the second group), or all from 64 on to the last 64, score -inf for every
+# query: they weigh nothing, in whichever group they fall
+@pytest.mark.parametrize("groups", [1, 2, 4])
+@pytest.mark.parametrize("n,lo,hi", [(128, 64, 128), (300, 64, 128), (1028, 64, 128), (1028, 64, 964), (640, 64, 640)])
+def test_tiles_of_keys_without_weight(groups, n, lo, hi):
+    rng = np.random.default_rng(n + lo)
+    q = wl.round_to_bf16(rng.standard_normal((n, 64), dtype=np.float32) * np.float32(1.4426950408889634 / 8))
+    k = wl.round_to_bf16(rng.standard_normal((n, 64), dtype=np.float32))
+    v = wl.round_to_bf16(rng.standard_normal((n, 64), dtype=np.float32))
+    q[:, 0], k[:, 0] = 2.0 ** 70, 0.0
+    k[lo:hi, 0] = -(2.0 ** 70)                 # products of -2^140: beyond fp32
+    got, ref = attend([n], 1, q, k, v, groups)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= 2e-2     # as above
