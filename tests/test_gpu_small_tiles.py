@@ -1,5 +1,7 @@
 """GEMM launches of at most one round of the chip (64 x 64 up to 128 x 256 tiles, three or four K slices in flight):
-edges of every tile, K loops shorter than the pipeline, and the towers' small batches that run on them."""
+edges of every tile, K loops shorter than the pipeline, and the towers' small batches that run on them.  The tiles whose
+waves have unequal shares of the W rows (160 columns) are among them."""
+import os
 from dataclasses import replace
 
 import numpy as np
@@ -14,13 +16,15 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("M,N", [(1, 4), (63, 60), (65, 68), (250, 3836),        # 64 x 64 tiles
-                                 (257, 6900), (520, 3844),                       # 64 x 128
-                                 (1000, 3840), (1028, 1028 * 3),                 # 128 x 128
-                                 (1030, 4100), (1500, 3840),                     # 128 x 256
-                                 (1500, 5120), (3000, 1280)])                    # 256 x 160: a wave without a share of the last W rows
+@pytest.mark.parametrize("M,N,tile", [(1, 4, "64, 64"), (63, 60, "64, 64"), (65, 68, "64, 64"), (250, 3836, "64, 64"),
+                                      (257, 6000, "64, 128"), (450, 3844, "64, 128"),
+                                      (257, 6900, "128, 128"), (520, 3844, "128, 128"), (1000, 3840, "128, 128"),
+                                      (1028, 1028 * 3, "128, 128"), (3000, 1280, "128, 128"),
+                                      (1030, 4100, "128, 256"), (1500, 3840, "128, 256"), (1500, 5120, "128, 256"),
+                                      (8190, 1280, "256, 160")])   # two stages; waves without a share of the last W rows
 @pytest.mark.parametrize("K", [64, 128, 192, 256, 320, 1280])
-def test_linear_one_round_tiles(M, N, K):
+def test_linear_one_round_tiles(M, N, tile, K):
+    assert B.cs_linear_kernel(M, N, K).startswith(f"gemm_kernel<{tile}, ")
     g = torch.Generator(device=DEV)
     g.manual_seed(M * 7 + N * 3 + K)
     A = torch.randn(M, K, generator=g, device=DEV).bfloat16()
@@ -34,6 +38,19 @@ def test_linear_one_round_tiles(M, N, K):
     # the partial sums, which stay below 8 sqrt(K): K steps at most
     assert err <= K * 2.0 ** -24 * 8 * (K ** 0.5 + 1), err
     assert (C[M] == 7.0).all()
+
+
+# a residual GEMM on eight-wave 128 x 160 tiles, four stages, of which half the waves load one piece less per slice: the
+# out projection's K loop of five slices, and a down projection of one to five
+@pytest.mark.parametrize("mlp_dim", [64, 128, 192, 256, 320])
+def test_short_k_on_unequal_waves(mlp_dim):
+    cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,), hidden=320, n_heads=4, mlp_dim=mlp_dim,
+                  merger_hidden=1280, out_hidden=512)
+    w = wl.images_workload(f"narrow_{mlp_dim}", cfg, [(308, 364), (56, 84)], seq_len=2048, data_seed=mlp_dim)
+    enc = B.Encoder(cfg, w.weights)
+    for step in ("proj", "mlp_down") if not any(k.startswith("CS_GEMM_") for k in os.environ) else ():
+        assert enc.cs_encoder_step_kernel(B.STEPS[step], int(w.cu_seqlens[-1])).startswith("gemm_kernel<128, 160, 4, 2, 4, 0>")
+    check_items(f"hidden 320, mlp {mlp_dim}", w, w.weights, [0, 1])
 
 
 @pytest.mark.parametrize("sizes", [[(28, 28)], [(56, 84)], [(224, 224)], [(308, 364)], [(224, 224), (336, 420)], [(448, 448)]])
