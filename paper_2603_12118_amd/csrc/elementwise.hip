@@ -24,7 +24,10 @@ constexpr int NORM_MAX_V4 = 8;  // a wave keeps a row of up to 64*4*8 = 2048 flo
 // One wave per row.  MODE 0: RMSNorm.  MODE 1: LayerNorm.  POOL rows of x are averaged first.
 // A row is a dozen kilobytes and the work on it a few hundred instructions, so a launch over few rows (a small batch,
 // whose pending split-K sums join here) lasts as long as its loads' latency: PARTS, the number of pending sums, is a
-// template argument, and all the loads of the row and of the sums are issued before the first is used.
+// template argument, and the loads of the row, of the sums and of their bias and scale are issued before the first is
+// used (four pending sums: 256 rows of 1280 10.2 -> 7.1 us, 1024 rows 12.0 -> 10.5).  What is left of the chain: gain and
+// bias of the output are loaded piece by piece behind the statistics, and with PARTS > 0 the guarded loads compile to
+// flat ones beside 32 bytes of scratch per lane.
 // NV: float4 pieces of a row per lane, the smallest instantiation that covers dim.
 template <int MODE, int PARTS, int NV>
 __global__ __launch_bounds__(64) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,

@@ -632,7 +632,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   constexpr bool RESADD = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SCALED_F32 || EPI == EPI_RESADD_SUMS_F32;
   constexpr bool HOLD_TWO = RESADD && TM > 1 && BN < 256;
   // (the 256 x 256 tile has registers for that one only in the second half of the last slice: requested ahead of it,
-  // 28 registers of accumulators were spilled around the slice; 32 mixed images 161.8 -> 157.4 ms)
+  // 28 registers of accumulators were spilled around the slice; 110 940 x 1280 x 1280 585 -> 533 us, x 3456 1006 -> 955,
+  // 24 000 x 1280 x 1280 129 -> 119)
   constexpr bool HELD_LATE = RESADD && BN == 256;
   [[maybe_unused]] f32x4 held[HOLD_TWO ? 2 : 1][RESADD ? TN : 1][4];
   [[maybe_unused]] auto fetch_old = [&](int i, int j, f32x4 (&dst)[4]) {
@@ -1134,6 +1135,9 @@ struct SmallTile {
 };
 static constexpr SmallTile SMALL_TILES[] = {{64, 64}, {64, 128}, {128, 128}, {128, 256}};
 enum { TILE_64 = 0, TILE_64x128, TILE_128, TILE_128x256, N_SMALL_TILES };
+// The last stands in where 128 x 128 needs more than a round: 1100 - 2048 rows, N = 3584 - 5120, K = 1280 take 20 - 23 us
+// on it, against 20 - 28 on two-stage 128 x 128 tiles, two per CU, which are ahead by up to 2 us where they number 260 -
+// 420 and behind by up to 5 beyond.
 
 // the first of those tiles from `first` on that makes at most one round of the chip, N_SMALL_TILES if none does
 static int small_tile(int64_t M, int64_t N, int64_t parts, int first) {
@@ -1161,11 +1165,13 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
     }
     if (t == TILE_64x128) return launch_one<64, 128, 2, SW, EPI, TAIL_NONE, 4>(g, stream);
     if (t == TILE_128) return launch_one<128, 128, 4, 2, EPI, TAIL_NONE, 4>(g, stream);
+    // (gate | up pairs and residual sums have no 128 x 256 instantiation; none was tried)
     if constexpr (EPI != EPI_SWIGLU_BF16 && !RESADD) {
       if (t == TILE_128x256 && (EPI != EPI_QKV || (2 * g.hidden) % 256 == 0))
         return launch_one<128, 256, 2, 4, EPI, TAIL_NONE, 3>(g, stream);
     }
   }
+  // (The thresholds from here on, and the figures beside them, were measured on a K loop with a barrier between its slices.)
   const int64_t tm = (g.M + 255) / 256;
   const int64_t big = tm * ((g.N + 255) / 256);
   const bool big_ok = EPI != EPI_QKV || (2 * g.hidden) % 256 == 0;
