@@ -242,13 +242,11 @@ __device__ __forceinline__ void load_lds16_far(const bf16_t* src, unsigned char*
 template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN, bool FAR>
 __device__ __forceinline__ void issue_one(const Operands<A_LOADS, B_LOADS, FAR>& op, int l, int kt, unsigned char* stage, int wave) {
   if (l < A_LOADS) {
-    unsigned char* lds = stage + (l * NWAVES + wave) * 1024;
-    if constexpr (FAR) load_lds16_far<CS_GEMM_A_AUX>(op.a[l] + (int64_t)kt * 64, lds);
-    else load_lds16<CS_GEMM_A_AUX>(op.a + (int64_t)kt * 64, op.a_off[l], lds);
+    if constexpr (FAR) load_lds16_far<CS_GEMM_A_AUX>(op.a[l] + (int64_t)kt * 64, stage + (l * NWAVES + wave) * 1024);
+    else load_lds16<CS_GEMM_A_AUX>(op.a + (int64_t)kt * 64, op.a_off[l], stage + (l * NWAVES + wave) * 1024);
   } else if (BN % (8 * NWAVES) == 0 || ((l - A_LOADS) * NWAVES + wave) * 8 < BN) {
-    unsigned char* lds = stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024;
-    if constexpr (FAR) load_lds16_far<CS_GEMM_W_AUX>(op.w[l - A_LOADS] + (int64_t)kt * 64, lds);
-    else load_lds16<CS_GEMM_W_AUX>(op.w + (int64_t)kt * 64, op.b_off[l - A_LOADS], lds);
+    if constexpr (FAR) load_lds16_far<CS_GEMM_W_AUX>(op.w[l - A_LOADS] + (int64_t)kt * 64, stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024);
+    else load_lds16<CS_GEMM_W_AUX>(op.w + (int64_t)kt * 64, op.b_off[l - A_LOADS], stage + BM * 128 + ((l - A_LOADS) * NWAVES + wave) * 1024);
   }
 }
 template <int A_LOADS, int B_LOADS, int NWAVES, int BM, int BN, bool FAR>
@@ -325,17 +323,15 @@ __device__ __forceinline__ void main_loop(const GemmArgs& g, unsigned char* smem
   for (int i = 0; i < A_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;  // row inside the tile
     const int r = m0 + rt < M ? rt : M - 1 - m0;
-    const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
-    if constexpr (FAR) op.a[i] = g.A + (int64_t)(m0 + r) * g.lda + chunk * 8;
-    else op.a_off[i] = (uint32_t)r * (uint32_t)(g.lda * 2) + (chunk << 4);
+    if constexpr (FAR) op.a[i] = g.A + (int64_t)(m0 + r) * g.lda + (((lane & 7) ^ ((rt >> 1) & 7)) << 3);
+    else op.a_off[i] = (uint32_t)r * (uint32_t)(g.lda * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
   }
 #pragma unroll
   for (int i = 0; i < B_LOADS; ++i) {
     const int rt = (i * NWAVES + wave) * 8 + lr;
     const int r = n0 + rt < N ? rt : N - 1 - n0;
-    const int chunk = (lane & 7) ^ ((rt >> 1) & 7);
-    if constexpr (FAR) op.w[i] = g.W + (int64_t)(n0 + r) * g.ldw + chunk * 8;
-    else op.b_off[i] = (uint32_t)r * (uint32_t)(g.ldw * 2) + (chunk << 4);
+    if constexpr (FAR) op.w[i] = g.W + (int64_t)(n0 + r) * g.ldw + (((lane & 7) ^ ((rt >> 1) & 7)) << 3);
+    else op.b_off[i] = (uint32_t)r * (uint32_t)(g.ldw * 2) + (((lane & 7) ^ ((rt >> 1) & 7)) << 4);
   }
   const int KT = K >> 6;
 
