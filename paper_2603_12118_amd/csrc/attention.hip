@@ -47,7 +47,7 @@ void attn_kernel(AttnArgs a) {
   constexpr int KS = DH / 16;            // k-steps of the score product
   constexpr int DT = (DH + 31) / 32;     // 32-row tiles of O^T
   constexpr int KSTR = DH * 2 + 16;      // LDS row stride of the K tile, bytes
-  constexpr int VSTR = 64 * 2 + 8;       // LDS row stride of the V^T tile, bytes
+  constexpr int VSTR = 64 * 2 + 16;      // LDS row stride of the V^T tile, bytes
   constexpr int KCH = DH / 8;            // 16-byte chunks per K row
   // Head dimension 80, eight waves: the query fragments wait in LDS (each lane's own 16-byte pieces, read
   // back in lane order: no conflicts) instead of 20 registers, which brings the kernel under 128 registers
@@ -56,14 +56,13 @@ void attn_kernel(AttnArgs a) {
   constexpr bool Q_IN_LDS = (DH > 64 && NW == 8) || KG > 1;
   static_assert(KG == 1 || (!SINGLE && QT == 1 && DH % 32 == 0), "key groups: one 32-query block per wave");
   constexpr int K_BYTES = 64 * KSTR, V_BYTES = DT * 32 * VSTR;
-  __shared__ __align__(16) unsigned char k_lds_all[KG == 1 ? K_BYTES : KG * (K_BYTES + V_BYTES)];
-  __shared__ __align__(16) unsigned char v_lds_all[KG == 1 ? V_BYTES : 16];
+  __shared__ __align__(16) unsigned char tiles[KG * (K_BYTES + V_BYTES)];
   __shared__ __align__(16) unsigned char q_lds[Q_IN_LDS ? QT * KS * NT * 16 : 16];
 
   const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;
   const int tid = threadIdx.x & (NT - 1), lane = tid & 63, wave = tid >> 6;   // inside the key group
-  unsigned char* const k_lds = k_lds_all + group * (K_BYTES + V_BYTES);
-  unsigned char* const v_lds = KG == 1 ? v_lds_all : k_lds + K_BYTES;
+  unsigned char* const k_lds = tiles + group * (K_BYTES + V_BYTES);
+  unsigned char* const v_lds = k_lds + K_BYTES;
   const int l31 = lane & 31, lhi = lane >> 5;
   // Workgroup -> (work item, head).  Consecutive workgroups run on different XCDs (id % 8), each with its own L2.
   int head, item;
@@ -135,10 +134,25 @@ void attn_kernel(AttnArgs a) {
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
   u32x4 kreg[K_PT];
   u32x2 vreg[V_PT];
+  // The vector unit and the chain of one tile bound these kernels (full layers: ~100 vector instructions and 32
+  // exponentials per wave beside 512 clocks of MFMA), so a tile's addresses cost no vector instructions: a tile that ends
+  // inside the batch has a scalar base and 32-bit offsets which a thread keeps.  With 64-bit products per thread and tile,
+  // the row maximum exchanged between the halves in every tile and V^T read in 8-byte pieces: 16 x 1500 tokens, 20 heads
+  // of 64 222 -> 216 us, 2 x 8192, 16 of 80 761 -> 718, 4 x 3467 320 -> 299, 2000 windows of 64 tokens 379 -> 336.
+  // The batch's last, partly filled tile, whose rows and pieces beyond the end must not be read, and pitches that the
+  // offsets do not reach go the long way.
+  uint32_t koff[K_PT];
+#pragma unroll
+  for (int u = 0; u < K_PT; ++u) {
+    int c = tid + u * NT;
+    c = c < 64 * KCH ? c : 64 * KCH - 1;
+    koff[u] = (uint32_t)(c / KCH) * (uint32_t)(ldq * 2) + (c % KCH) * 16;
+  }
+  const uint32_t voff = (uint32_t)(tid >> 4) * (uint32_t)(a.ld_vt * 2) + (tid & 15) * 8;
+  const bool near = 64 * ldq * 2 <= 0x7fffffff && (int64_t)(DH + NT / 16) * a.ld_vt * 2 <= 0x7fffffff;
   auto load_tile = [&](int kv) {
     if constexpr (KG > 1) {
-      // the same by 32-bit offsets from the item's first key (attention_groups_addressable): a
-      // group's waves hold four times the staging registers, and 64-bit addresses of their own do not fit beside them
+      // by 32-bit offsets from the item's first key throughout (attention_groups_addressable)
       const unsigned char* kb = reinterpret_cast<const unsigned char*>(kbase + (int64_t)w.kv0 * ldq);
       const unsigned char* vb = reinterpret_cast<const unsigned char*>(vbase + w.kv0);
 #pragma unroll
@@ -153,6 +167,18 @@ void attn_kernel(AttnArgs a) {
       const uint32_t v0 = (uint32_t)(tid >> 4) * (uint32_t)(a.ld_vt * 2) + tok * 2;
 #pragma unroll
       for (int u = 0; u < V_PT; ++u) vreg[u] = *reinterpret_cast<const u32x2*>(vb + (v0 + (uint32_t)u * (uint32_t)(NT / 16 * 2 * a.ld_vt)));
+      return;
+    }
+    if (near && kv + 64 <= a.n_tok) {
+      const unsigned char* kb = reinterpret_cast<const unsigned char*>(kbase + (int64_t)kv * ldq);
+      const unsigned char* vb = reinterpret_cast<const unsigned char*>(vbase + kv);
+#pragma unroll
+      for (int u = 0; u < K_PT; ++u) kreg[u] = *reinterpret_cast<const u32x4*>(kb + koff[u]);
+#pragma unroll
+      for (int u = 0; u < V_PT; ++u) {
+        if ((u + 1) * (NT / 16) <= DH || (tid >> 4) + u * (NT / 16) < DH)   // (rows of V^T beyond the head's)
+          vreg[u] = *reinterpret_cast<const u32x2*>(vb + (int64_t)u * (NT / 16) * a.ld_vt * 2 + voff);
+      }
       return;
     }
 #pragma unroll
@@ -183,7 +209,9 @@ void attn_kernel(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < V_PT; ++u) {
       const int c = tid + u * NT;
-      if (c < DH * 16) *reinterpret_cast<u32x2*>(v_lds + (c >> 4) * VSTR + (c & 15) * 8) = vreg[u];
+      // (pieces 1 and 2 of every four change places: the eight keys of a lane's fragment are then 16 bytes side by side)
+      const int ch = c & 15, at = (ch & 12) | ((ch & 1) << 1) | ((ch >> 1) & 1);
+      if (c < DH * 16) *reinterpret_cast<u32x2*>(v_lds + (c >> 4) * VSTR + at * 8) = vreg[u];
     }
   };
 
@@ -221,6 +249,9 @@ void attn_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[it][jt][r] = init;
     }
+    // (these products first: a wave in its exponentials then does not hold up one that is about to have work for them;
+    // 4 x 3467 tokens x 16 heads of 80 304 -> 297 us, 2 x 8192 721 -> 713, three tiles in key groups 28.7 -> 27.1)
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -234,6 +265,7 @@ void attn_kernel(AttnArgs a) {
         }
       }
     }
+    __builtin_amdgcn_s_setprio(0);
     // register r of a tile holds key row 8*(r/4) + 4*lhi + r%4
     if (kv + 64 > w.kv1) {
 #pragma unroll
@@ -261,11 +293,12 @@ void attn_kernel(AttnArgs a) {
       for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[it][jt][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));          // the tile's largest score minus the running maximum
       // v_exp_f32 directly: arguments are bounded above and results that would be denormal may flush to 0,
       // so the library exp2f's range scaling (four more instructions per score) buys nothing here
-      const bool jump = first[it] || mx > MAX_SLACK;   // (every tile holds at least one valid key)
-      if (__any(jump)) {                           // some query of this wave takes a new maximum
+      if (__any(first[it] || mx > MAX_SLACK)) {    // some query of this wave takes a new maximum
+        // (the halves of a wave hold the same queries: only where a maximum moves is the other half's needed)
+        mx = fmaxf(mx, __shfl_xor(mx, 32));        // the tile's largest score minus the running maximum
+        const bool jump = first[it] || mx > MAX_SLACK;   // (every tile holds at least one valid key)
         const float base = first[it] ? 0.f : mrun[it];
         const float mnew = jump ? mx + base : mrun[it];
         const float alpha = first[it] ? 0.f : __builtin_amdgcn_exp2f(mrun[it] - mnew);
@@ -309,12 +342,7 @@ void attn_kernel(AttnArgs a) {
     for (int ku = 0; ku < 4; ++ku) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const unsigned char* vp = v_lds + (dt * 32 + l31) * VSTR + (ku * 16 + 4 * lhi) * 2;
-        uint4 t;
-        const uint2 lo = *reinterpret_cast<const uint2*>(vp);
-        const uint2 hi = *reinterpret_cast<const uint2*>(vp + 16);
-        t.x = lo.x; t.y = lo.y; t.z = hi.x; t.w = hi.y;
-        const bf16x8 vf = *reinterpret_cast<bf16x8*>(&t);
+        const bf16x8 vf = *reinterpret_cast<const bf16x8*>(v_lds + (dt * 32 + l31) * VSTR + ku * 32 + lhi * 16);
 #pragma unroll
         for (int it = 0; it < QT; ++it)
           o[it][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[it][ku], o[it][dt], 0, 0, 0);
@@ -328,7 +356,7 @@ void attn_kernel(AttnArgs a) {
     constexpr int STATE = 16 * DT + 2;     // words per lane
     static_assert((KG - 1) * NWG * STATE * 256 <= KG * (K_BYTES + V_BYTES), "the states fit where the tiles were");
     __syncthreads();
-    float* st = reinterpret_cast<float*>(k_lds_all) + wave * STATE * 64 + lane;
+    float* st = reinterpret_cast<float*>(tiles) + wave * STATE * 64 + lane;
     if (group > 0) {
       float* mine = st + (group - 1) * NWG * STATE * 64;
       mine[0] = mrun[0];
