@@ -19,118 +19,134 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-constexpr int NORM_MAX_V4 = 8;  // a wave keeps a row of up to 64*4*8 = 2048 floats in registers
+constexpr int NORM_MAX_V4 = 8;  // a row is at most 64*4*8 = 2048 floats
+typedef float f32x4_n __attribute__((ext_vector_type(4)));
 
-// One wave per row.  MODE 0: RMSNorm.  MODE 1: LayerNorm.  POOL rows of x are averaged first.
+// MODE 0: RMSNorm.  MODE 1: LayerNorm.  `pool` rows of x are averaged first (PARTS == 0).
+// PARTS: the number of pending split-K sums, which join the residual stream here (pool == 1), in part order.
+// NV: 16-byte pieces of a row per lane of a wave, the smallest instantiation that covers dim.
 // A row is a dozen kilobytes and the work on it a few hundred instructions, so a launch over few rows (a small batch,
-// whose pending split-K sums join here) lasts as long as its loads' latency: PARTS, the number of pending sums, is a
-// template argument, and the loads of the row, of the sums and of their bias and scale are issued before the first is
-// used (four pending sums: 256 rows of 1280 10.2 -> 7.1 us, 1024 rows 12.0 -> 10.5).  What is left of the chain: gain and
-// bias of the output are loaded piece by piece behind the statistics, and with PARTS > 0 the guarded loads compile to
-// flat ones beside 32 bytes of scratch per lane.
-// NV: float4 pieces of a row per lane, the smallest instantiation that covers dim.
-template <int MODE, int PARTS, int NV>
-__global__ __launch_bounds__(64) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,
-                                                  const float* __restrict__ bias, float eps,
-                                                  bf16_t* __restrict__ y, int64_t rows, int dim, int pool, int split_group,
-                                                  bool wt, PendingSum add) {
-  const int lane = threadIdx.x & 63;
+// whose pending sums join here) lasts as long as its loads' latency: every load of a row, of its pending sums and of
+// gain and bias is issued before the first is used, and WIDE gives each piece a wave of its own (a workgroup of NV waves
+// per row; the waves exchange their lanes' sums through LDS and add them piece by piece, in the order in which one wave
+// adds its own, so both forms give the same bits).  Rows of 1280 with four pending sums, before (a wave per row, guarded
+// loads that compiled to single words through the flat path, gain behind the statistics) -> now: 256 rows 5.4 -> 2.8 us,
+// 1024 9.1 -> 4.1, 1500 (LayerNorm) 12.0 -> 6.9, 2560 16.6 -> 13.1 (5.1 TB/s); x is stored write-through where its rows
+// are whole lines (1500 rows 8.4 -> 6.9: no write-back at the kernel's end).
+template <int MODE, int PARTS, int NV, bool WIDE>
+__global__ __launch_bounds__(WIDE ? 64 * NV : 64) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,
+                                                                   const float* __restrict__ bias, float eps,
+                                                                   bf16_t* __restrict__ y, int dim, int pool, int split_group,
+                                                                   bool wt, bool wt_x, PendingSum add) {
+#pragma clang fp contract(off)   // (which products are fused with which sums is written out: it is the same in every form)
+  constexpr int P = WIDE ? 1 : NV;   // pieces of this lane
+  const int lane = threadIdx.x & 63, wave = WIDE ? threadIdx.x >> 6 : 0;
   const int64_t row = blockIdx.x;
-  float4 v[NV];
   const int nv = dim >> 2;
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  const f32x4_n zero = {0.f, 0.f, 0.f, 0.f};
+  int c[P];      // column piece, clamped to the row; beyond it (`in` false) the loads repeat the last piece
+  bool in[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    c[i] = lane + 64 * (wave + i);
+    in[i] = c[i] < nv;
+    c[i] = in[i] ? c[i] : nv - 1;
+  }
+  f32x4_n v[P], g[P], b[P];
+  auto load_affine = [&] {
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      g[i] = reinterpret_cast<const f32x4_n*>(gain)[c[i]];
+      b[i] = MODE == 1 ? reinterpret_cast<const f32x4_n*>(bias)[c[i]] : zero;
+    }
+  };
   if constexpr (PARTS == 0) {
+    if constexpr (WIDE) load_affine();
 #pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = zero;
+    for (int i = 0; i < P; ++i) v[i] = zero;
     for (int p = 0; p < pool; ++p) {
-      float4 t[NV];
+      f32x4_n t[P];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int c = lane + 64 * i;
-        t[i] = zero;
-        if (c < nv) t[i] = reinterpret_cast<const float4*>(x + (row * pool + p) * dim)[c];
-      }
+      for (int i = 0; i < P; ++i) t[i] = reinterpret_cast<const f32x4_n*>(x + (row * pool + p) * dim)[c[i]];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        v[i].x += t[i].x; v[i].y += t[i].y; v[i].z += t[i].z; v[i].w += t[i].w;
-      }
+      for (int i = 0; i < P; ++i) v[i] += t[i];
     }
     if (pool > 1) {
       const float ip = 1.0f / pool;
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        v[i].x *= ip; v[i].y *= ip; v[i].z *= ip; v[i].w *= ip;
-      }
+      for (int i = 0; i < P; ++i) v[i] *= ip;
     }
-  } else {   // pending split-K sums join the residual stream here (pool == 1), in part order
-    float4 part[PARTS][NV], pb[NV], ps[NV];
+  } else {
+    f32x4_n part[PARTS][P], pb[P], ps[P];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int c = lane + 64 * i;
-      const bool in = c < nv;
+    for (int i = 0; i < P; ++i) {
 #pragma unroll
-      for (int s = 0; s < PARTS; ++s) part[s][i] = in ? reinterpret_cast<const float4*>(add.parts + s * add.stride + row * dim)[c] : zero;
-      v[i] = in ? reinterpret_cast<const float4*>(x + row * dim)[c] : zero;
-      pb[i] = in && add.bias ? reinterpret_cast<const float4*>(add.bias)[c] : zero;
-      ps[i] = in && add.scale ? reinterpret_cast<const float4*>(add.scale)[c] : make_float4(1.f, 1.f, 1.f, 1.f);
+      for (int s = 0; s < PARTS; ++s) part[s][i] = reinterpret_cast<const f32x4_n*>(add.parts + s * add.stride + row * dim)[c[i]];
+      v[i] = reinterpret_cast<const f32x4_n*>(x + row * dim)[c[i]];
+      pb[i] = ps[i] = zero;
+      if (add.bias) pb[i] = reinterpret_cast<const f32x4_n*>(add.bias)[c[i]];
+      if (add.scale) ps[i] = reinterpret_cast<const f32x4_n*>(add.scale)[c[i]];
     }
+    load_affine();
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      float4 a = part[0][i];
+    for (int i = 0; i < P; ++i) {
+      f32x4_n a = part[0][i];
 #pragma unroll
-      for (int s = 1; s < PARTS; ++s) {
-        a.x += part[s][i].x; a.y += part[s][i].y; a.z += part[s][i].z; a.w += part[s][i].w;
-      }
-      if (add.bias) {
-        a.x += pb[i].x; a.y += pb[i].y; a.z += pb[i].z; a.w += pb[i].w;
-      }
-      if (add.scale) {
-        a.x *= ps[i].x; a.y *= ps[i].y; a.z *= ps[i].z; a.w *= ps[i].w;
-      }
-      v[i].x += a.x; v[i].y += a.y; v[i].z += a.z; v[i].w += a.w;
-      const int c = lane + 64 * i;
-      if (c < nv) reinterpret_cast<float4*>(x + row * dim)[c] = v[i];
+      for (int s = 1; s < PARTS; ++s) a += part[s][i];
+      if (add.bias) a += pb[i];
+      if (add.scale) a *= ps[i];
+      v[i] += a;
+      if (in[i]) store16(reinterpret_cast<f32x4_n*>(x + row * dim) + c[i], v[i], wt_x);
     }
   }
-  float mean = 0.f;
-  if (MODE == 1) {
+  // sum over the row of what each piece contributes: a lane's pieces in order, then across the lanes
+  [[maybe_unused]] __shared__ float pieces[2][WIDE ? NV * 64 : 1];
+  auto row_sum = [&](const float (&mine)[P], int which) {
     float s = 0.f;
+    if constexpr (WIDE) {
+      pieces[which][threadIdx.x] = mine[0];
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-    mean = wave_sum(s) / dim;
-  }
-  float ss = 0.f;
+      for (int i = 0; i < NV; ++i) s += pieces[which][i * 64 + lane];
+    } else {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    if (lane + 64 * i < nv) {
-      const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-      ss += (a * a + b * b) + (c * c + d * d);
+      for (int i = 0; i < P; ++i) s += mine[i];
     }
-  }
-  const float rstd = rsqrtf(wave_sum(ss) / dim + eps);
+    return wave_sum(s);
+  };
+  float mean = 0.f, part_sum[P];
+  if (MODE == 1) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int c = lane + 64 * i;
-    if (c < nv) {
-      const float4 g = reinterpret_cast<const float4*>(gain)[c];
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (MODE == 1) b = reinterpret_cast<const float4*>(bias)[c];
-      const float o0 = (v[i].x - mean) * rstd * g.x + b.x, o1 = (v[i].y - mean) * rstd * g.y + b.y;
-      const float o2 = (v[i].z - mean) * rstd * g.z + b.z, o3 = (v[i].w - mean) * rstd * g.w + b.w;
-      uint2 pk;
-      pk.x = pack2_e(o0, o1);
-      pk.y = pack2_e(o2, o3);
-      if (split_group == 0) {
-        store8(reinterpret_cast<uint2*>(y + row * dim) + c, __builtin_bit_cast(wt_f32x2, pk), wt);
-      } else {
-        // hi | lo halves of a row of `split_group` tokens: lo = value - hi, again rounded to bf16
-        bf16_t* dst = y + (row / split_group) * (2 * split_group * dim) + (row % split_group) * dim;
-        store8(reinterpret_cast<uint2*>(dst) + c, __builtin_bit_cast(wt_f32x2, pk), wt);
-        uint2 lo;
-        lo.x = pack2_e(o0 - __uint_as_float(pk.x << 16), o1 - __uint_as_float(pk.x & 0xFFFF0000u));
-        lo.y = pack2_e(o2 - __uint_as_float(pk.y << 16), o3 - __uint_as_float(pk.y & 0xFFFF0000u));
-        store8(reinterpret_cast<uint2*>(dst + split_group * dim) + c, __builtin_bit_cast(wt_f32x2, lo), wt);
-      }
+    for (int i = 0; i < P; ++i) part_sum[i] = in[i] ? (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]) : 0.f;
+    mean = row_sum(part_sum, 0) / dim;
+  }
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const f32x4_n d = v[i] - mean;
+    part_sum[i] = in[i] ? __builtin_fmaf(d[0], d[0], d[1] * d[1]) + __builtin_fmaf(d[2], d[2], d[3] * d[3]) : 0.f;
+  }
+  const float rstd = rsqrtf(row_sum(part_sum, 1) / dim + eps);
+  if constexpr (!WIDE) load_affine();   // (many rows: other waves hide the latency, and the registers are better spent on them)
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    if (!in[i]) continue;
+    f32x4_n o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf((v[i][e] - mean) * rstd, g[i][e], b[i][e]);
+    uint2 pk;
+    pk.x = pack2_e(o[0], o[1]);
+    pk.y = pack2_e(o[2], o[3]);
+    if (split_group == 0) {
+      store8(reinterpret_cast<uint2*>(y + row * dim) + c[i], __builtin_bit_cast(wt_f32x2, pk), wt);
+    } else {
+      // hi | lo halves of a row of `split_group` tokens: lo = value - hi, again rounded to bf16
+      const uint32_t group = (uint32_t)row / (uint32_t)split_group, at = (uint32_t)row % (uint32_t)split_group;
+      bf16_t* dst = y + ((int64_t)group * 2 * split_group + at) * dim;
+      store8(reinterpret_cast<uint2*>(dst) + c[i], __builtin_bit_cast(wt_f32x2, pk), wt);
+      uint2 lo;
+      lo.x = pack2_e(o[0] - __uint_as_float(pk.x << 16), o[1] - __uint_as_float(pk.x & 0xFFFF0000u));
+      lo.y = pack2_e(o[2] - __uint_as_float(pk.y << 16), o[3] - __uint_as_float(pk.y & 0xFFFF0000u));
+      store8(reinterpret_cast<uint2*>(dst + (int64_t)split_group * dim) + c[i], __builtin_bit_cast(wt_f32x2, lo), wt);
     }
   }
 }
@@ -144,15 +160,29 @@ static cs_status norm_check(int64_t rows, int dim, const PendingSum& add = Pendi
   return CS_OK;
 }
 
-// (a wave is a workgroup of its own: 256 rows make 256 workgroups, one per CU)
+// A workgroup per row up to so many rows (pending sums come with no more than the encoder splits for and always take it:
+// 2560 rows, four sums, 13.1 us against 17.0 with a wave per row), a wave per row beyond: 1024 x 1280 2.7 against 3.6 us,
+// 2048 4.7 against 4.9, 3000 6.0 against 5.6, 8192 12.5 against 11.1, 110 940 174 against 146.
+constexpr int64_t NORM_WIDE_MAX_ROWS = 2048;
+template <int MODE, int PARTS, int NV>
+static void norm_launch_one(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+                            int split_group, const PendingSum& add, hipStream_t s) {
+  const bool wt = lines_exclusive(y, (int64_t)dim * 2), wt_x = lines_exclusive(x, (int64_t)dim * 4);
+  if constexpr (PARTS == 0) {
+    if (rows > NORM_WIDE_MAX_ROWS) {
+      hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, false>), dim3((unsigned)rows), dim3(64), 0, s, x, gain, bias, eps, y, dim, pool, split_group, wt, wt_x, add);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, true>), dim3((unsigned)rows), dim3(64 * NV), 0, s, x, gain, bias, eps, y, dim, pool, split_group, wt, wt_x, add);
+}
 template <int MODE, int PARTS>
 static void norm_launch_nv(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
                            int split_group, const PendingSum& add, hipStream_t s) {
-  const bool wt = lines_exclusive(y, (int64_t)dim * 2);
-  const dim3 grid((unsigned)rows), block(64);
-  if (dim <= 1024) hipLaunchKernelGGL((norm_kernel<MODE, PARTS, 4>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
-  else if (dim <= 1280) hipLaunchKernelGGL((norm_kernel<MODE, PARTS, 5>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
-  else hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NORM_MAX_V4>), grid, block, 0, s, x, gain, bias, eps, y, rows, dim, pool, split_group, wt, add);
+  if (dim <= 256) norm_launch_one<MODE, PARTS, 1>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
+  else if (dim <= 1024) norm_launch_one<MODE, PARTS, 4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
+  else if (dim <= 1280) norm_launch_one<MODE, PARTS, 5>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
+  else norm_launch_one<MODE, PARTS, NORM_MAX_V4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
 }
 template <int MODE>
 static cs_status norm_launch(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
