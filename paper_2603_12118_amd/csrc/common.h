@@ -109,6 +109,8 @@ struct GemmArgs {
   char* describe;
   // set by the launcher: the residual epilogue stores plainly (through the L2's write-back) instead of write-through
   int32_t plain_stores;
+  // set by the launcher: workgroups that take half a tile of the last round each (a launch with a light tail as well)
+  int32_t half_tiles;
 };
 
 // Whether the rows of a tile (at most 256) can be addressed by 32-bit byte offsets from its first row, as all GEMM

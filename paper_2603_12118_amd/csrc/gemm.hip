@@ -934,8 +934,13 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
 //    last round are cut in two along M and run as BM/2-row tiles by twice as many workgroups, so the
 //    round takes little more than half as long.  A round costs the same however few of its tiles are
 //    there (measured: 864 tiles of 256 x 256 take as long as 1024), and 8192 x 6912 is 3 3/8 rounds.
+//  A 256 x 256 launch with a light tail splits its last round as well, where its halves and the light tiles make one
+//    round (GemmArgs::half_tiles; the tiles counted are the full ones, the light tiles run behind the halves):
+//    5128 x 3840 x 1280, 300 tiles and 15 light ones, 72 -> 64 us, 9300 rows 105 -> 98, 14 000 rows 140 -> 133.
 enum { TAIL_NONE = 0, TAIL_LIGHT = 1, TAIL_SPLIT = 2 };
 constexpr int CHIP_CUS = 256;
+template <int BM, int BN, int TAIL>
+constexpr bool tail_splits() { return TAIL == TAIL_SPLIT || (TAIL == TAIL_LIGHT && BM == 256 && BN == 256); }
 
 // tile id -> first row / column.  Ids walk the tile grid in bands of GROUP_M tile rows, row index
 // fastest, so the ~32 tiles an XCD runs at a time form a GROUP_M x 8 block that shares GROUP_M slices
@@ -979,21 +984,22 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
   constexpr bool LIGHT = TAIL == TAIL_LIGHT;
   static_assert(!LIGHT || light_tail<BN, WGM, WGN, EPI>(), "no 64-row tile for this shape");
   static_assert(!FAR || TAIL == TAIL_NONE, "far rows: whole tiles only");
-  static_assert(TAIL != TAIL_SPLIT || (BM / 2 / WGM) % 32 == 0, "half tiles need whole 32-row blocks per wave");
-  if constexpr (TAIL == TAIL_SPLIT) {
-    // workgroups [0, n_main) run the full rounds; the rest each take half of a tile of the last round
-    const int n_main = (tiles_m * tiles_n / CHIP_CUS) * CHIP_CUS;
-    if ((int)blockIdx.x >= n_main) {
+  constexpr bool SPLIT = tail_splits<BM, BN, TAIL>();
+  static_assert(!SPLIT || (BM / 2 / WGM) % 32 == 0, "half tiles need whole 32-row blocks per wave");
+  if constexpr (SPLIT) {
+    // workgroups [0, n_main) run the full rounds; the next each take half of a tile of the last round
+    const int full = (LIGHT ? M / BM : tiles_m) * tiles_n, n_half = g.half_tiles, n_main = full - n_half / 2;
+    if ((int)blockIdx.x >= n_main && (int)blockIdx.x < n_main + n_half) {
       // (the half tiles get the same treatment as the tiles: consecutive workgroups run on different XCDs,
       // so every XCD takes a contiguous run of half tiles, both halves of a tile among them)
       int t = blockIdx.x - n_main;
       {
-        const int n_half = gridDim.x - n_main, xcd = t & 7, idx = t >> 3;
+        const int xcd = t & 7, idx = t >> 3;
         const int per = n_half >> 3, rem = n_half & 7;
         t = xcd * per + (xcd < rem ? xcd : rem) + idx;
       }
       int m0, n0;
-      tile_origin<BM, BN>(n_main + (t >> 1), tiles_m, tiles_n, m0, n0);
+      tile_origin<BM, BN>(n_main + (t >> 1), LIGHT ? M / BM : tiles_m, tiles_n, m0, n0);
       m0 += (t & 1) * (BM / 2);
       if (m0 >= M) return;   // the lower half of a tile of a ragged last tile row may be empty
       tile_body<BM / 2, BN, WGM, WGN, EPI, 2, LDS>(g, smem, m0, n0);
@@ -1002,16 +1008,16 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
     nb = n_main;
   }
   if constexpr (LIGHT) {
-    const int full_m = M / BM, n_main = full_m * tiles_n;
-    if ((int)blockIdx.x >= n_main) {
-      const int t = blockIdx.x - n_main;
+    const int full_m = M / BM, n_main = full_m * tiles_n, n_half = SPLIT ? g.half_tiles : 0;
+    if ((int)blockIdx.x >= n_main + n_half / 2) {
+      const int t = blockIdx.x - n_main - n_half / 2;
       const int tail_m = (M - full_m * BM + 63) / 64;
       tile_body<64, BN, 1, WGM * WGN, EPI, light_stages<BN, WGM * WGN, EPI>(), LDS>(
           g, smem, full_m * BM + (t % tail_m) * 64, (t / tail_m) * BN);
       return;
     }
     tiles_m = full_m;
-    nb = n_main;
+    nb = n_main - n_half / 2;
   }
 
   // workgroup -> tile.  Consecutive workgroups land on different XCDs (b % 8), each with its own
@@ -1057,9 +1063,17 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   int tiles = ((g.M + BM - 1) / BM) * tiles_n;
   if (TAIL == TAIL_LIGHT)   // full tile rows, then the remaining rows in 64-row tiles
     tiles = (g.M / BM) * tiles_n + ((g.M % BM + 63) / 64) * tiles_n;
-  if (TAIL == TAIL_SPLIT)   // the tiles of the last round twice, as half tiles
-    tiles += tiles % CHIP_CUS;
   GemmArgs ga = g;
+  ga.half_tiles = 0;
+  if constexpr (tail_splits<BM, BN, TAIL>()) {   // the tiles of a last round that is at most half full twice, as half tiles
+    // (beside a light tail only where halves and light tiles make one round together: a third one costs what the split
+    // saves, 8224 x 3072 x 1024 61 -> 65 us with 256 halves and 12 light tiles)
+    const int full = (TAIL == TAIL_LIGHT ? g.M / BM : (g.M + BM - 1) / BM) * tiles_n, rest = full % CHIP_CUS, light = tiles - full;
+    if (TAIL == TAIL_SPLIT || (full > CHIP_CUS && 2 * rest + light <= CHIP_CUS && g.splits <= 1 && !tail_split_off())) {
+      ga.half_tiles = 2 * rest;
+      tiles += rest;
+    }
+  }
   // The residual epilogue's stores are write-through except in launches of the narrow tiles that run more than
   // one round: there the next round's operand loads queue behind the first round's burst of stores, and stores
   // that stay in the L2's write-back do better (16 384 tokens: out projection 487 -> 521, down projection
