@@ -56,20 +56,25 @@ enum GemmEpilogue {
 };
 
 struct GemmArgs {
+  // (what a workgroup needs before its first load comes first, in one 64-byte line of the kernel's arguments and the next)
   const bf16_t* A;   // [M, lda]
   int64_t lda;
   const bf16_t* W;   // [N, ldw], K % 64 == 0
   int64_t ldw;       // row pitch of W in elements; 0 means K
+  int32_t M, N, K;
+  // split K: workgroups with blockIdx.y = s take an equal share, in whole slices of 64, of the K columns of A and W
+  // and write to out + s * split_stride elements; splits <= 1: one part
+  int32_t splits;
+  // set by the launcher: whole tiles along M and N, the workgroups that run one (grid_tiles), those that take half a tile
+  // of the last round each, and reciprocals for the divisions by 4 tiles_n and by splits
+  int32_t tiles_m, tiles_n, grid_tiles, half_tiles;
+  uint64_t band_recip, split_recip;
+  int64_t split_stride;
   const float* bias; // [N] or nullptr
   const float* col_scale;  // [N], EPI_RESADD_SCALED_F32 only
   void* out;         // [*, ldo]
   int64_t ldo;
   const int32_t* row_map;  // nullptr, or destination row per m (negative: skip)
-  int32_t M, N, K;
-  // split K: workgroups with blockIdx.y = s take an equal share, in whole slices of 64, of the K columns of A and W
-  // and write to out + s * split_stride elements; splits <= 1: one part
-  int32_t splits;
-  int64_t split_stride;
   // EPI_QKV only
   bf16_t* vt;        // [hidden, ld_vt]
   int64_t ld_vt;
@@ -109,8 +114,6 @@ struct GemmArgs {
   char* describe;
   // set by the launcher: the residual epilogue stores plainly (through the L2's write-back) instead of write-through
   int32_t plain_stores;
-  // set by the launcher: workgroups that take half a tile of the last round each (a launch with a light tail as well)
-  int32_t half_tiles;
 };
 
 // Whether the rows of a tile (at most 256) can be addressed by 32-bit byte offsets from its first row, as all GEMM

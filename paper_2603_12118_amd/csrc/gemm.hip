@@ -946,13 +946,31 @@ constexpr bool tail_splits() { return TAIL == TAIL_SPLIT || (TAIL == TAIL_LIGHT 
 // fastest, so the ~32 tiles an XCD runs at a time form a GROUP_M x 8 block that shares GROUP_M slices
 // of A and 8 slices of W per k-step (an L2 miss on every W byte otherwise: measured 427 clocks average
 // L2 read latency and the L1 miss queue full 58 % of the time).
+// A workgroup's way to its first load is a chain of scalar work that nothing hides, a tenth of a small launch, so no
+// division is left in it: x / d = high 64 bits of x * reciprocal(d), exact for all x < 2^32, 2 <= d < 2^32 (the reciprocal
+// exceeds 2^64 / d by at most one, which adds less than x / 2^64 < 1 / d to the quotient).  With the launch's tile counts in
+// the arguments and the arguments in two lines: 256 x 3840 x 1280 10.8 -> 10.4 us, 256 x 1280 x 3456 in three parts 8.4 ->
+// 8.1, a lone 64 x 64 x 64 tile 3.4 -> 3.0.
+constexpr int GROUP_M = 4;   // (2: the same within noise; 8: 1 % slower on the 32-image batch; 16: 4 % slower)
+static uint64_t reciprocal(uint32_t d) { return d >= 2 ? ~0ull / d + 1 : 0; }   // (2^64 / d rounded up)
+__device__ __forceinline__ int divide(int x, uint64_t recip) {
+  const uint64_t lo = (uint64_t)(uint32_t)x * (uint32_t)recip, hi = (uint64_t)(uint32_t)x * (uint32_t)(recip >> 32);
+  return (int)((hi + (lo >> 32)) >> 32);
+}
 template <int BM, int BN>
-__device__ __forceinline__ void tile_origin(int id, int tiles_m, int tiles_n, int& m0, int& n0) {
-  constexpr int GROUP_M = 4;   // (2: the same within noise; 8: 1 % slower on the 32-image batch; 16: 4 % slower)
-  const int band = id / (GROUP_M * tiles_n), in_band = id - band * (GROUP_M * tiles_n);
-  const int band_rows = tiles_m - band * GROUP_M < GROUP_M ? tiles_m - band * GROUP_M : GROUP_M;
-  m0 = (band * GROUP_M + in_band % band_rows) * BM;
-  n0 = (in_band / band_rows) * BN;
+__device__ __forceinline__ void tile_origin(const GemmArgs& g, int id, int& m0, int& n0) {
+  const int band_tiles = GROUP_M * g.tiles_n, band = divide(id, g.band_recip), in_band = id - band * band_tiles;
+  const int rows = g.tiles_m - band * GROUP_M;   // of the band; the last one may have fewer than four
+  // (a third: 2^32 / 3 rounded up times in_band < 2^31 is exact)
+  const int col = rows >= GROUP_M ? in_band >> 2 : rows == 3 ? (int)__umulhi((uint32_t)in_band, 0x55555556u) : rows == 2 ? in_band >> 1 : in_band;
+  m0 = (band * GROUP_M + in_band - col * (rows < GROUP_M ? rows : GROUP_M)) * BM;
+  n0 = col * BN;
+}
+
+// the b-th of n workgroups, b % 8 its XCD -> its place in the order in which every XCD has a contiguous run
+__device__ __forceinline__ int xcd_run(int b, int n) {
+  const int xcd = b & 7, idx = b >> 3, per = n >> 3, rem = n & 7;
+  return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
 
 // LDS of a launch: that of its main tile, or what the deeper pipeline of its 64-row tail tiles needs.
@@ -970,66 +988,48 @@ __global__ __launch_bounds__(64 * WGM * WGN)
 __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(GemmArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL, STAGES>();
-  if (gridDim.y > 1) {   // split K (plain fp32 partial sums only): this workgroup's K slices of A and W, its partial sums
-    const int kt = g.K >> 6, first = (int)blockIdx.y * kt / (int)gridDim.y, last = ((int)blockIdx.y + 1) * kt / (int)gridDim.y;
+  if (g.splits > 1) {   // split K (plain fp32 partial sums only): this workgroup's K slices of A and W, its partial sums
+    const int kt = g.K >> 6, part = (int)blockIdx.y;
+    const int first = divide(part * kt, g.split_recip), last = divide((part + 1) * kt, g.split_recip);
     g.A += (int64_t)first * 64;
     g.W += (int64_t)first * 64;
     g.K = (last - first) * 64;
-    g.out = static_cast<float*>(g.out) + (int64_t)blockIdx.y * g.split_stride;
+    g.out = static_cast<float*>(g.out) + (int64_t)part * g.split_stride;
   }
-  const int M = g.M, N = g.N;
-  const int tiles_n = (N + BN - 1) / BN;
-  int tiles_m = (M + BM - 1) / BM;
-  int nb = gridDim.x;
-  constexpr bool LIGHT = TAIL == TAIL_LIGHT;
+  constexpr bool LIGHT = TAIL == TAIL_LIGHT, SPLIT = tail_splits<BM, BN, TAIL>();
   static_assert(!LIGHT || light_tail<BN, WGM, WGN, EPI>(), "no 64-row tile for this shape");
   static_assert(!FAR || TAIL == TAIL_NONE, "far rows: whole tiles only");
-  constexpr bool SPLIT = tail_splits<BM, BN, TAIL>();
   static_assert(!SPLIT || (BM / 2 / WGM) % 32 == 0, "half tiles need whole 32-row blocks per wave");
-  if constexpr (SPLIT) {
-    // workgroups [0, n_main) run the full rounds; the next each take half of a tile of the last round
-    const int full = (LIGHT ? M / BM : tiles_m) * tiles_n, n_half = g.half_tiles, n_main = full - n_half / 2;
-    if ((int)blockIdx.x >= n_main && (int)blockIdx.x < n_main + n_half) {
-      // (the half tiles get the same treatment as the tiles: consecutive workgroups run on different XCDs,
-      // so every XCD takes a contiguous run of half tiles, both halves of a tile among them)
-      int t = blockIdx.x - n_main;
-      {
-        const int xcd = t & 7, idx = t >> 3;
-        const int per = n_half >> 3, rem = n_half & 7;
-        t = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  // workgroups [0, grid_tiles) run whole tiles
+  if constexpr (TAIL != TAIL_NONE) {
+    int t = (int)blockIdx.x - g.grid_tiles;
+    if (t >= 0) {
+      if constexpr (SPLIT) {   // the next each take half of a tile of the last round
+        if (t < g.half_tiles) {
+          // (the half tiles get the same treatment as the tiles: consecutive workgroups run on different XCDs,
+          // so every XCD takes a contiguous run of half tiles, both halves of a tile among them)
+          t = xcd_run(t, g.half_tiles);
+          int m0, n0;
+          tile_origin<BM, BN>(g, g.grid_tiles + (t >> 1), m0, n0);
+          m0 += (t & 1) * (BM / 2);
+          if (m0 >= g.M) return;   // the lower half of a tile of a ragged last tile row may be empty
+          tile_body<BM / 2, BN, WGM, WGN, EPI, 2, LDS>(g, smem, m0, n0);
+          return;
+        }
+        t -= g.half_tiles;
       }
-      int m0, n0;
-      tile_origin<BM, BN>(n_main + (t >> 1), LIGHT ? M / BM : tiles_m, tiles_n, m0, n0);
-      m0 += (t & 1) * (BM / 2);
-      if (m0 >= M) return;   // the lower half of a tile of a ragged last tile row may be empty
-      tile_body<BM / 2, BN, WGM, WGN, EPI, 2, LDS>(g, smem, m0, n0);
+      if constexpr (LIGHT) {   // the others take the rows behind the full tile rows in 64-row tiles
+        const int full = g.tiles_m * BM, tail_m = (g.M - full + 63) / 64;
+        tile_body<64, BN, 1, WGM * WGN, EPI, light_stages<BN, WGM * WGN, EPI>(), LDS>(
+            g, smem, full + (t % tail_m) * 64, (t / tail_m) * BN);
+      }
       return;
     }
-    nb = n_main;
   }
-  if constexpr (LIGHT) {
-    const int full_m = M / BM, n_main = full_m * tiles_n, n_half = SPLIT ? g.half_tiles : 0;
-    if ((int)blockIdx.x >= n_main + n_half / 2) {
-      const int t = blockIdx.x - n_main - n_half / 2;
-      const int tail_m = (M - full_m * BM + 63) / 64;
-      tile_body<64, BN, 1, WGM * WGN, EPI, light_stages<BN, WGM * WGN, EPI>(), LDS>(
-          g, smem, full_m * BM + (t % tail_m) * 64, (t / tail_m) * BN);
-      return;
-    }
-    tiles_m = full_m;
-    nb = n_main - n_half / 2;
-  }
-
   // workgroup -> tile.  Consecutive workgroups land on different XCDs (b % 8), each with its own
   // L2, so every XCD gets a contiguous range of tile ids.
-  int bid = blockIdx.x;
-  {
-    const int xcd = bid & 7, idx = bid >> 3;
-    const int per = nb >> 3, rem = nb & 7;
-    bid = xcd * per + (xcd < rem ? xcd : rem) + idx;
-  }
   int m0, n0;
-  tile_origin<BM, BN>(bid, tiles_m, tiles_n, m0, n0);
+  tile_origin<BM, BN>(g, xcd_run((int)blockIdx.x, g.grid_tiles), m0, n0);
   tile_body<BM, BN, WGM, WGN, EPI, STAGES, LDS, FAR>(g, smem, m0, n0);
 }
 
@@ -1059,21 +1059,26 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
     CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
     attr_set.store(true, std::memory_order_release);
   }
-  const int tiles_n = (g.N + BN - 1) / BN;
-  int tiles = ((g.M + BM - 1) / BM) * tiles_n;
-  if (TAIL == TAIL_LIGHT)   // full tile rows, then the remaining rows in 64-row tiles
-    tiles = (g.M / BM) * tiles_n + ((g.M % BM + 63) / 64) * tiles_n;
   GemmArgs ga = g;
+  const int tiles_n = (g.N + BN - 1) / BN;
+  // the tiles that are run whole or in halves: with a light tail those of the full tile rows
+  ga.tiles_n = tiles_n;
+  ga.tiles_m = TAIL == TAIL_LIGHT ? g.M / BM : (g.M + BM - 1) / BM;
+  const int whole = ga.tiles_m * tiles_n, light = TAIL == TAIL_LIGHT ? ((g.M % BM + 63) / 64) * tiles_n : 0;
+  int tiles = whole + light;   // workgroups
   ga.half_tiles = 0;
   if constexpr (tail_splits<BM, BN, TAIL>()) {   // the tiles of a last round that is at most half full twice, as half tiles
     // (beside a light tail only where halves and light tiles make one round together: a third one costs what the split
     // saves, 8224 x 3072 x 1024 61 -> 65 us with 256 halves and 12 light tiles)
-    const int full = (TAIL == TAIL_LIGHT ? g.M / BM : (g.M + BM - 1) / BM) * tiles_n, rest = full % CHIP_CUS, light = tiles - full;
-    if (TAIL == TAIL_SPLIT || (full > CHIP_CUS && 2 * rest + light <= CHIP_CUS && g.splits <= 1 && !tail_split_off())) {
+    const int rest = whole % CHIP_CUS;
+    if (TAIL == TAIL_SPLIT || (whole > CHIP_CUS && 2 * rest + light <= CHIP_CUS && g.splits <= 1 && !tail_split_off())) {
       ga.half_tiles = 2 * rest;
       tiles += rest;
     }
   }
+  ga.grid_tiles = whole - ga.half_tiles / 2;
+  ga.band_recip = reciprocal((uint32_t)(GROUP_M * tiles_n));
+  ga.split_recip = reciprocal((uint32_t)(g.splits > 1 ? g.splits : 0));
   // The residual epilogue's stores are write-through except in launches of the narrow tiles that run more than
   // one round: there the next round's operand loads queue behind the first round's burst of stores, and stores
   // that stay in the L2's write-back do better (16 384 tokens: out projection 487 -> 521, down projection
