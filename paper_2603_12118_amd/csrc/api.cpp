@@ -1040,12 +1040,14 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       StepTimer tm(e, full ? CS_STEP_ATTN_FULL : CS_STEP_ATTN_WINDOW, stream);
       if (full) {
         aa.work = reinterpret_cast<const AttnWork*>(plan + p.off_full_work); aa.n_work = p.n_full_work; aa.q_per_block = p.full_q_per_block; aa.single_tile = p.full_single_tile; aa.key_groups = p.full_key_groups;
+        aa.q_split = p.full_q_split ? 4 : 1;
+        if (p.full_q_split) aa.n_work += p.n_tail_work;   // (they follow in the list)
       } else {
-        aa.work = reinterpret_cast<const AttnWork*>(plan + p.off_win_work); aa.n_work = p.n_win_work; aa.q_per_block = 64; aa.single_tile = p.win_single_tile; aa.key_groups = 1;
+        aa.work = reinterpret_cast<const AttnWork*>(plan + p.off_win_work); aa.n_work = p.n_win_work; aa.q_per_block = 64; aa.single_tile = p.win_single_tile; aa.key_groups = 1; aa.q_split = 1;
       }
       if (cs_status st = launch_attention(aa, stream)) return st;
-      if (full && p.n_tail_work > 0) {   // the short last query blocks of the items, as 64-query work items
-        aa.work = reinterpret_cast<const AttnWork*>(plan + p.off_tail_work); aa.n_work = p.n_tail_work; aa.q_per_block = 64; aa.single_tile = 0; aa.key_groups = p.tail_key_groups;
+      if (full && p.n_tail_work > 0 && !p.full_q_split) {   // the short last query blocks of the items, as 64-query work items
+        aa.work = reinterpret_cast<const AttnWork*>(plan + p.off_tail_work); aa.n_work = p.n_tail_work; aa.q_per_block = 64; aa.single_tile = 0; aa.key_groups = p.tail_key_groups; aa.q_split = 1;
         if (cs_status st = launch_attention(aa, stream)) return st;
       }
     }

@@ -44,6 +44,7 @@ void attn_kernel(AttnArgs a) {
   constexpr int NWG = NW / KG;           // waves of a key group
   constexpr int NT = 64 * NWG;
   static_assert((NT & (NT - 1)) == 0, "threads of a key group");
+  constexpr bool Q_SPLIT = NW == 2 && !SINGLE;   // may run a quarter of a 256-query item
   constexpr int KS = DH / 16;            // k-steps of the score product
   constexpr int DT = (DH + 31) / 32;     // 32-row tiles of O^T
   constexpr int KSTR = DH * 2 + 16;      // LDS row stride of the K tile, bytes
@@ -78,14 +79,22 @@ void attn_kernel(AttnArgs a) {
       // full layers: the (head, item) pairs in head-major order, cut into eight equal runs: the query blocks of one
       // (item, head), which all read that head's K and V^T, run on one XCD at about the same time instead of on
       // all eight (the 32-image batch fetched 10.5 GB per full-attention layer for 0.85 GB of operands)
-      const int pairs = a.n_work * a.n_heads, per = pairs >> 3, rem = pairs & 7;
+      const int blocks = a.n_work * (Q_SPLIT ? a.q_split : 1), pairs = blocks * a.n_heads, per = pairs >> 3, rem = pairs & 7;
       if (r >= per + (xcd < rem ? 1 : 0)) return;
       const int p = xcd * per + (xcd < rem ? xcd : rem) + r;
-      head = p / a.n_work;
-      item = p - head * a.n_work;
+      head = p / blocks;
+      item = p - head * blocks;
     }
   }
-  const AttnWork w = a.work[item];
+  AttnWork w;
+  if (Q_SPLIT && a.q_split > 1) {   // this workgroup's 64 queries of the item, if it has so many
+    w = a.work[item >> 2];
+    w.q0 += 64 * (item & 3);
+    w.q1 = w.q1 < w.q0 + 64 ? w.q1 : w.q0 + 64;
+    if (w.q0 >= w.q1) return;       // (whole workgroup, before any barrier)
+  } else {
+    w = a.work[item];
+  }
   const int hidden = a.n_heads * DH;
   const int64_t ldq = 2 * (int64_t)hidden;
   const bf16_t* qbase = a.qk + head * DH;
@@ -416,7 +425,11 @@ cs_status launch_attention(const AttnArgs& a, hipStream_t stream) {
   if (a.n_work <= 0) return CS_OK;
   if (a.n_tok < 4 || a.ld_vt < ((a.n_tok + 3) & ~3)) return fail(CS_ERR_INVALID_ARG, "attention: ld_vt too small");
   if (a.ld_vt & 3) return fail(CS_ERR_INVALID_ARG, "attention: ld_vt must be a multiple of 4");
-  const int64_t pairs = (int64_t)a.n_work * a.n_heads;
+  AttnArgs args = a;
+  args.q_split = a.q_split > 1 ? a.q_split : 1;
+  if (args.q_split > 1 && (args.q_split != 4 || a.q_per_block != 256 || a.key_groups > 1 || a.single_tile))
+    return fail(CS_ERR_INVALID_ARG, "attention: only 256-query items run as four workgroups");
+  const int64_t pairs = (int64_t)a.n_work * args.q_split * a.n_heads;
   if (pairs + 8 * (int64_t)a.n_heads > 0x7fffffff) return fail(CS_ERR_UNSUPPORTED, "attention: too many work items");
   // (see the kernel: window layers give an XCD every eighth window, full layers an eighth of the (head, item) pairs)
   dim3 grid(a.single_tile ? (unsigned)(8 * ((a.n_work + 7) / 8) * a.n_heads) : (unsigned)(8 * ((pairs + 7) / 8)));
@@ -427,14 +440,15 @@ cs_status launch_attention(const AttnArgs& a, hipStream_t stream) {
     return fail(CS_ERR_INVALID_ARG, "attention: key groups are two of 128-query items or four of 64-query items");
   if (a.key_groups > 1 && (a.head_dim != 64 || a.single_tile || a.max_keys <= 0 || !attention_groups_addressable(a)))
     return fail(CS_ERR_UNSUPPORTED, "attention: key groups need head_dim 64 and items whose keys 32-bit offsets reach");
-  if (a.head_dim == 80 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<80, 2, 1, true>), grid, dim3(128), 0, stream, a);
-  else if (a.head_dim == 80 && a.q_per_block == 64) hipLaunchKernelGGL((attn_kernel<80, 2, 1, false>), grid, dim3(128), 0, stream, a);
-  else if (a.head_dim == 80 && a.q_per_block == 256) hipLaunchKernelGGL((attn_kernel<80, 8, 1, false>), grid, dim3(512), 0, stream, a);
-  else if (a.head_dim == 64 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<64, 2, 1, true>), grid, dim3(128), 0, stream, a);
-  else if (a.head_dim == 64 && a.q_per_block == 64 && a.key_groups > 1) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 4>), grid, dim3(512), 0, stream, a);
-  else if (a.head_dim == 64 && a.q_per_block == 128) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 2>), grid, dim3(512), 0, stream, a);
-  else if (a.head_dim == 64 && a.q_per_block == 64) hipLaunchKernelGGL((attn_kernel<64, 2, 1, false>), grid, dim3(128), 0, stream, a);
-  else if (a.head_dim == 64 && a.q_per_block == 256) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false>), grid, dim3(512), 0, stream, a);
+  const int q = args.q_split > 1 ? 64 : a.q_per_block;   // queries per workgroup
+  if (a.head_dim == 80 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<80, 2, 1, true>), grid, dim3(128), 0, stream, args);
+  else if (a.head_dim == 80 && q == 64) hipLaunchKernelGGL((attn_kernel<80, 2, 1, false>), grid, dim3(128), 0, stream, args);
+  else if (a.head_dim == 80 && q == 256) hipLaunchKernelGGL((attn_kernel<80, 8, 1, false>), grid, dim3(512), 0, stream, args);
+  else if (a.head_dim == 64 && a.q_per_block == 64 && a.single_tile) hipLaunchKernelGGL((attn_kernel<64, 2, 1, true>), grid, dim3(128), 0, stream, args);
+  else if (a.head_dim == 64 && a.q_per_block == 64 && a.key_groups > 1) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 4>), grid, dim3(512), 0, stream, args);
+  else if (a.head_dim == 64 && a.q_per_block == 128) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false, 2>), grid, dim3(512), 0, stream, args);
+  else if (a.head_dim == 64 && q == 64) hipLaunchKernelGGL((attn_kernel<64, 2, 1, false>), grid, dim3(128), 0, stream, args);
+  else if (a.head_dim == 64 && q == 256) hipLaunchKernelGGL((attn_kernel<64, 8, 1, false>), grid, dim3(512), 0, stream, args);
   else return fail(CS_ERR_UNSUPPORTED, "attention: head_dim must be 64 or 80 and q_per_block 64, 128 or 256");
   CS_HIP(hipGetLastError());
   return CS_OK;

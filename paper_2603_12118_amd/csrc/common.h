@@ -199,6 +199,7 @@ struct AttnArgs {
   const AttnWork* work;
   int32_t n_work, n_tok, n_heads, head_dim;
   int32_t q_per_block;  // 64, 128 or 256 queries per workgroup (work items are cut accordingly)
+  int32_t q_split;      // 256-query items only: 4 runs each as four workgroups of 64 queries (0 or 1: as one)
   int32_t single_tile;  // nonzero: no work item has more than 64 keys (64-query items only)
   int32_t key_groups;   // 2 (128-query items) or 4 (64-query items): the key tiles of an item are shared out inside the
                         // workgroup (head dimension 64, attention_groups_addressable)

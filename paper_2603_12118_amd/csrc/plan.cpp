@@ -71,6 +71,20 @@ static bool share_keys(const cs_encoder_config& cfg, int64_t items_256, int64_t 
   return with <= 256 || (without > 256 && with <= 512);
 }
 
+// Without groups, items of up to 256 queries run as four workgroups of 64 (two waves each) while that makes at most two
+// per CU.  A workgroup of eight waves walks its key tiles at two waves per SIMD, 1.9 us a tile, one of two waves at 1 us,
+// and the short last blocks join the same launch.  Queries keep their waves of 32, so the results are the same bits, and
+// the lists stay as they are (a batch's workspace must not grow).  us a layer, 256 -> 64 queries a workgroup, heads x
+// tokens: 16 x 256 11.5 -> 7.3 (64 workgroups), 576 31.4 -> 12.9 (144), 1024 30.3 -> 21.5 (256), two items of 1024 32.3 ->
+// 30.5 (512); beyond that 2116 60.7 -> 60.5 (544), three of 1024 34.4 -> 36.5 (768), 20 x 8 x 500 25.0 -> 28.3 (1280).
+static void split_queries(const cs_encoder_config& cfg, BatchPlan& p) {
+  if (p.full_q_per_block != 256 || p.full_key_groups != 1 || (p.n_tail_work > 0 && (p.tail_key_groups != 1 || p.off_tail_work != p.off_full_work + 4 * (size_t)p.n_full_work))) return;
+  int64_t blocks = 0;
+  const int32_t* w = p.blob.data() + p.off_full_work;
+  for (int64_t i = 0; i < (int64_t)p.n_full_work + p.n_tail_work; ++i) blocks += (w[4 * i + 1] - w[4 * i] + 63) / 64;
+  p.full_q_split = blocks * cfg.n_heads <= 512;
+}
+
 cs_status build_vit_plan(const cs_encoder_config& cfg, const int32_t* cu, const int32_t* grid, int32_t n_items,
                          BatchPlan& p) {
   if (cs_status st = check_batch(cu, grid, n_items)) return st;
@@ -138,6 +152,7 @@ cs_status build_vit_plan(const cs_encoder_config& cfg, const int32_t* cu, const 
   p.n_win_work = (int32_t)(win_work.size() / 4);
   p.n_full_work = (int32_t)(full_work.size() / 4);
   p.n_tail_work = (int32_t)(tail_work.size() / 4);
+  split_queries(cfg, p);
   return CS_OK;
 }
 
@@ -220,6 +235,7 @@ cs_status build_cls_plan(const cs_encoder_config& cfg, int32_t n_positions, cons
   p.n_full_work = (int32_t)(full_work.size() / 4);
   p.off_tail_work = put(tail_work);
   p.n_tail_work = (int32_t)(tail_work.size() / 4);
+  split_queries(cfg, p);
   return CS_OK;
 }
 
@@ -295,6 +311,7 @@ cs_status build_audio_plan(const cs_encoder_config& cfg, const int32_t* cu, cons
   p.off_pos = put(pos);
   p.off_full_work = put(full_work);
   p.n_full_work = (int32_t)(full_work.size() / 4);
+  split_queries(cfg, p);
   return CS_OK;
 }
 

@@ -27,6 +27,7 @@ struct BatchPlan {
   int32_t n_win_work = 0, n_full_work = 0, n_tail_work = 0;
   bool win_single_tile = false;  // no window has more than 64 tokens
   int32_t full_q_per_block = 256;   // queries per item of full_work: 256, 128 with key groups, or 64 when the segments are short chunks
+  bool full_q_split = false;        // the 256-query items, and the tail items behind them, run as workgroups of 64 queries
   bool full_single_tile = false;    // no full_work item has more than 64 keys
   int32_t full_key_groups = 1, tail_key_groups = 1;   // > 1: the items share out their key tiles inside the workgroup
   int32_t full_max_keys = 0;        // the most keys an item of either list has (set where there are key groups)
