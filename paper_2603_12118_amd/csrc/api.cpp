@@ -80,6 +80,7 @@ struct cs_encoder {
   int device = 0;
   // derived sizes
   int P_pad = 0, I_pad = 0, MH_pad = 0, half = 0;
+  int D_ldw = 0, xn_ld = 0;                  // row pitches (row_pitch) of the weights that read `hidden` columns, and of xn
   int I_ld = 0;                              // row pitch of the MLP activations and of the weights that read them (activation_pitch)
   bool rope = false;
   // weights
@@ -232,7 +233,7 @@ static size_t pack_matrix(Arena& A, const SrcTensor& t, int64_t rows_pad, int64_
 // LN(x) W^T + b = rs ((x g) W^T - mu c) + d with c[j] = sum_k g[k] W[j][k] and d[j] = b[j] + sum_k beta[k] W[j][k]:
 // what a GEMM needs to take a LayerNorm's place (the product itself runs on bf16(x g); rs and mu come from
 // per-row sums).  W, b as packed (bf16 rows in the GEMM's order, fp32 bias), g and beta fp32 [K].
-static void fold_vectors(Arena& A, size_t w, size_t bias, size_t gain, size_t beta, int64_t rows, int64_t K, size_t* c_off,
+static void fold_vectors(Arena& A, size_t w, int64_t ldw, size_t bias, size_t gain, size_t beta, int64_t rows, int64_t K, size_t* c_off,
                          size_t* d_off) {
   *c_off = A.alloc((size_t)rows * 4);
   *d_off = A.alloc((size_t)rows * 4);
@@ -241,7 +242,7 @@ static void fold_vectors(Arena& A, size_t w, size_t bias, size_t gain, size_t be
   for (int64_t j = 0; j < rows; ++j) {
     double c = 0.0, d = b[j];
     for (int64_t k = 0; k < K; ++k) {
-      const double wv = host_bf2f(W[j * K + k]);
+      const double wv = host_bf2f(W[j * ldw + k]);
       c += wv * g[k];
       if (be) d += wv * be[k];
     }
@@ -267,6 +268,16 @@ static size_t pack_vector(Arena& A, const SrcTensor& t, int64_t n_pad, RowOf idx
 // Not with a rotary table, whose place in the workspace pays for the 128 bytes per token elsewhere: a batch that fits a
 // workspace of a given size, the static scratch for one, must go on fitting it.
 static int activation_pitch(int cols, bool rope) { return !rope && cols >= 2048 && cols % 512 == 0 ? cols + 64 : cols; }
+
+// The same for the weights of the GEMMs that read rows of `hidden`, and for those rows (xn) where they have room: pitches
+// that are a multiple of 512 bytes, but not a power of two.  Launches of one round gain most.  Rows of 2560 B -> 2688 B,
+// weights, then weights and xn: 256 x 6912 x 1280 12.9 -> 12.2 -> 11.8 us, 1024 x 3840 17.6 -> 16.9 -> 16.1, 1024 x 6912
+// 28.3 -> 27.5 -> 26.7, 1500 x 3840 25.7 -> 23.8 -> 22.9, 5128 x 3840 63 -> 61 -> 60, 8192 x 6912 126 -> 123.5 -> 124.4,
+// 110 940 rows the same; pitches of 1536, 3072 and 5120 B gain alike, 2048 B loses (1028 x 4096 x 1024 19.4 -> 19.9).
+static int row_pitch(int cols) {
+  const int bytes = 2 * cols;
+  return bytes % 512 == 0 && (bytes & (bytes - 1)) != 0 ? cols + 64 : cols;
+}
 
 static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
   const cs_encoder_config& c = e->cfg;
@@ -297,11 +308,11 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
     }
     if (cs_status st = wb.get(p + "attn.qkv.weight", 3 * D * D, t)) return st;
     if (cs_status st = wb.get(p + "attn.qkv.bias", 3 * D, b, true)) return st;
-    L.wqkv = pack_matrix(A, t, 3 * D, D, D, qkv_row);
+    L.wqkv = pack_matrix(A, t, 3 * D, D, e->D_ldw, qkv_row);
     L.bqkv = pack_vector(A, b, 3 * D, qkv_row);
     if (cs_status st = wb.get(p + "attn.proj.weight", D * D, t)) return st;
     if (cs_status st = wb.get(p + "attn.proj.bias", D, b, true)) return st;
-    L.wo = pack_matrix(A, t, D, D, D, ident);
+    L.wo = pack_matrix(A, t, D, D, e->D_ldw, ident);
     L.bo = pack_vector(A, b, D, ident);
     if (c.arch == CS_ARCH_VIT_CLS) {
       if (cs_status st = wb.get(p + "ls1", D, t)) return st;
@@ -317,7 +328,7 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
       if (cs_status st = wb.get(p + "mlp.gate.bias", I, bg, true)) return st;
       if (cs_status st = wb.get(p + "mlp.up.bias", I, bu, true)) return st;
       const int64_t Ip = e->I_pad;
-      L.w1 = A.alloc((size_t)2 * Ip * D * 2);
+      L.w1 = A.alloc((size_t)2 * Ip * e->D_ldw * 2);
       L.b1 = A.alloc((size_t)2 * Ip * 4);
       for (int64_t r = 0; r < 2 * Ip; ++r) {
         const int64_t blk = r / 64, in = r % 64;
@@ -325,7 +336,7 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
         if (j >= I) continue;
         const SrcTensor& w = in < 32 ? tg : tu;
         const SrcTensor& bb = in < 32 ? bg : bu;
-        bf16_t* d = A.bf(L.w1) + r * D;
+        bf16_t* d = A.bf(L.w1) + r * e->D_ldw;
         for (int64_t k = 0; k < D; ++k) d[k] = w.bits(j * D + k);
         if (bb.data) A.f32(L.b1)[r] = bb.at(j);
       }
@@ -337,14 +348,14 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
       const int64_t Ip = e->I_pad;
       if (cs_status st = wb.get(p + "mlp.fc1.weight", I * D, t)) return st;
       if (cs_status st = wb.get(p + "mlp.fc1.bias", I, b, true)) return st;
-      L.w1 = pack_matrix(A, t, Ip, D, D, [&](int64_t r) { return r < I ? r : -1; });
+      L.w1 = pack_matrix(A, t, Ip, D, e->D_ldw, [&](int64_t r) { return r < I ? r : -1; });
       L.b1 = pack_vector(A, b, Ip, [&](int64_t r) { return r < I ? r : -1; });
       if (cs_status st = wb.get(p + "mlp.fc2.weight", D * I, t)) return st;
       if (cs_status st = wb.get(p + "mlp.fc2.bias", D, b, true)) return st;
       L.w2 = pack_matrix(A, t, D, I, e->I_ld, ident);
       L.b2 = pack_vector(A, b, D, ident);
-      fold_vectors(A, L.wqkv, L.bqkv, L.g1, L.be1, 3 * D, D, &L.cqkv, &L.dqkv);
-      fold_vectors(A, L.w1, L.b1, L.g2, L.be2, Ip, D, &L.c1, &L.d1);
+      fold_vectors(A, L.wqkv, e->D_ldw, L.bqkv, L.g1, L.be1, 3 * D, D, &L.cqkv, &L.dqkv);
+      fold_vectors(A, L.w1, e->D_ldw, L.b1, L.g2, L.be2, Ip, D, &L.c1, &L.d1);
     }
   }
   if (c.arch == CS_ARCH_VIT || c.arch == CS_ARCH_VIT_CLS) {
@@ -523,9 +534,9 @@ static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   // folds the next RMSNorm into its epilogue, which saves more than the split gains (2048 tokens: 5.33 -> 5.19 ms
   // per step; 1024 tokens: 3.95 -> 4.00 ms, so those stay split).
   if (w.s_proj > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
-      gemm_norm_fold_parts(N, D, D, D, scaled, ln) > 0)
+      gemm_norm_fold_parts(N, D, D, e->D_ldw, scaled, ln) > 0)
     w.s_proj = 1;
-  w.fold_proj = w.s_proj == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, D, D, scaled, ln) : 0;
+  w.fold_proj = w.s_proj == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, D, e->D_ldw, scaled, ln) : 0;
   w.fold_down = w.s_down == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, e->I_pad, e->I_ld, scaled, ln) : 0;
   w.ss = take((w.fold_proj || w.fold_down) ? (size_t)8 * w.ss_stride * 4 : 0);
   w.s1 = take(ln && (w.fold_proj || w.fold_down) ? (size_t)8 * w.ss_stride * 4 : 0);
@@ -673,6 +684,9 @@ static cs_status encoder_create(const cs_encoder_config* config, const cs_tensor
   e->half = c.head_dim / 2;
   e->rope = c.arch == CS_ARCH_VIT && (c.rope_sections[0] + c.rope_sections[1] + c.rope_sections[2]) > 0;
   e->I_ld = activation_pitch(e->I_pad, e->rope);
+  e->D_ldw = row_pitch(c.hidden);
+  // (xn has twice the bytes of its rows where the merger's hi | lo input shares it)
+  e->xn_ld = c.arch == CS_ARCH_AUDIO ? c.hidden : e->D_ldw;
   Arena A;
   A.alloc(256);  // offset 0 stays unused so that 0 can mean "absent"
   cs_status st = build_weights(e, wb, A);
@@ -779,7 +793,7 @@ cs_status cs_encoder_step_kernel(const cs_encoder* enc, int32_t step, int64_t n_
   if (epi == EPI_RESADD_F32 && c.arch == CS_ARCH_AUDIO && !fold_off() &&
       (n_tokens > SPLIT_K_MAX_TOKENS || k_parts(n_tokens, D, g.K) == 1))
     g.s1_out = reinterpret_cast<float*>(uintptr_t(16));   // describe mode: only looked at, never written
-  g.lda = g.ldw = step == CS_STEP_MLP_DOWN ? enc->I_ld : g.K;
+  g.lda = g.ldw = step == CS_STEP_MLP_DOWN ? enc->I_ld : enc->D_ldw;
   if (epi == EPI_RESADD_SCALED_F32) g.col_scale = enc->ptr<float>(enc->layers[0].ls1);
   // (batches small enough for split K run other launches; this names the kernel of the unsplit path)
   return launch_gemm(epi, g, nullptr);
@@ -964,10 +978,10 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     }
     folded = 0;
   };
-  auto gemm_residual = [&](const bf16_t* A, int64_t lda, size_t W, size_t bias, size_t scale, int64_t K, size_t next_gain,
+  auto gemm_residual = [&](const bf16_t* A, int64_t lda, size_t W, int64_t ldw, size_t bias, size_t scale, int64_t K, size_t next_gain,
                            int fold_parts, int S) -> cs_status {
     GemmArgs g = {};
-    g.A = A; g.lda = lda; g.W = e->ptr<bf16_t>(W); g.ldw = lda; g.ldo = D; g.M = (int32_t)N; g.N = (int32_t)D;   // (A and W have one pitch)
+    g.A = A; g.lda = lda; g.W = e->ptr<bf16_t>(W); g.ldw = ldw; g.ldo = D; g.M = (int32_t)N; g.N = (int32_t)D;
     if (S > 1) {
       g.K = (int32_t)K; g.splits = S; g.split_stride = N * D; g.out = parts;
       if (cs_status st = launch_gemm(EPI_F32, g, stream)) return st;
@@ -979,7 +993,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     g.bias = e->ptr<float>(bias); g.out = x; g.K = (int32_t)K;
     if (scale) g.col_scale = e->ptr<float>(scale);
     if (next_gain && fold_parts > 0) {
-      g.norm_gain = e->ptr<float>(next_gain); g.xg = xn; g.ld_xg = D; g.ss_out = ss; g.ss_stride = w.ss_stride;
+      g.norm_gain = e->ptr<float>(next_gain); g.xg = xn; g.ld_xg = e->xn_ld; g.ss_out = ss; g.ss_stride = w.ss_stride;
       if (!vit) g.s1_out = s1;
       folded = fold_parts;
     }
@@ -1019,8 +1033,8 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
   auto norm = [&](size_t gain, size_t bias) -> cs_status {
     if (folded) return CS_OK;      // the residual GEMM in front has written xn and the sums of squares
     StepTimer tm(e, CS_STEP_NORM, stream);
-    if (vit) return launch_rmsnorm(x, e->ptr<float>(gain), c.norm_eps, xn, N, (int32_t)D, stream, take_pending());
-    return launch_layernorm(x, e->ptr<float>(gain), e->ptr<float>(bias), c.norm_eps, xn, N, (int32_t)D, stream, take_pending());
+    if (vit) return launch_rmsnorm(x, e->ptr<float>(gain), c.norm_eps, xn, e->xn_ld, N, (int32_t)D, stream, take_pending());
+    return launch_layernorm(x, e->ptr<float>(gain), e->ptr<float>(bias), c.norm_eps, xn, e->xn_ld, N, (int32_t)D, stream, take_pending());
   };
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& L = e->layers[l];
@@ -1028,7 +1042,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     {
       StepTimer tm(e, CS_STEP_QKV, stream);
       GemmArgs g = {};
-      g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.wqkv); g.bias = e->ptr<float>(L.bqkv);
+      g.A = xn; g.lda = e->xn_ld; g.W = e->ptr<bf16_t>(L.wqkv); g.ldw = e->D_ldw; g.bias = e->ptr<float>(L.bqkv);
       g.out = qk; g.ldo = 2 * D; g.M = (int32_t)N; g.N = (int32_t)(3 * D); g.K = (int32_t)D;
       g.vt = vt; g.ld_vt = w.ld_vt; g.rope_cs = e->rope ? rope_cs : nullptr;
       g.hidden = (int32_t)D; g.head_dim = c.head_dim; g.q_scale = q_scale;
@@ -1053,21 +1067,21 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     }
     {
       StepTimer tm(e, CS_STEP_PROJ, stream);
-      if (cs_status st = gemm_residual(attn, D, L.wo, L.bo, cls ? L.ls1 : 0, D, L.g2, w.fold_proj, w.s_proj)) return st;
+      if (cs_status st = gemm_residual(attn, D, L.wo, e->D_ldw, L.bo, cls ? L.ls1 : 0, D, L.g2, w.fold_proj, w.s_proj)) return st;
     }
     if (cs_status st = norm(L.g2, L.be2)) return st;
     {
       StepTimer tm(e, CS_STEP_MLP_UP, stream);
       if (vit) {
         GemmArgs g = {};
-        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
+        g.A = xn; g.lda = e->xn_ld; g.W = e->ptr<bf16_t>(L.w1); g.ldw = e->D_ldw; g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
         g.M = (int32_t)N; g.N = 2 * e->I_pad; g.K = (int32_t)D;
         consume_norm(g);
         if (cs_status st = launch_gemm(EPI_SWIGLU_BF16, g, stream)) return st;
       }
       else {
         GemmArgs g = {};
-        g.A = xn; g.lda = D; g.W = e->ptr<bf16_t>(L.w1); g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
+        g.A = xn; g.lda = e->xn_ld; g.W = e->ptr<bf16_t>(L.w1); g.ldw = e->D_ldw; g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
         g.M = (int32_t)N; g.N = e->I_pad; g.K = (int32_t)D;
         consume_norm(g, L.c1, L.d1);
         if (cs_status st = launch_gemm(EPI_GELU_BF16, g, stream)) return st;
@@ -1077,7 +1091,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       StepTimer tm(e, CS_STEP_MLP_DOWN, stream);
       // (the norm behind the last block is the merger's, which splits its output: a kernel of its own)
       const size_t next_g1 = l + 1 < c.n_layers ? e->layers[l + 1].g1 : 0;
-      if (cs_status st = gemm_residual(big, e->I_ld, L.w2, L.b2, cls ? L.ls2 : 0, e->I_pad, next_g1, w.fold_down, w.s_down)) return st;
+      if (cs_status st = gemm_residual(big, e->I_ld, L.w2, e->I_ld, L.b2, cls ? L.ls2 : 0, e->I_pad, next_g1, w.fold_down, w.s_down)) return st;
     }
   }
 

@@ -225,12 +225,13 @@ struct PendingSum {
   const float* bias = nullptr;
   const float* scale = nullptr;
 };
-cs_status launch_rmsnorm(float* x, const float* gain, float eps, bf16_t* y, int64_t rows, int32_t dim, hipStream_t s,
+// (ldy: elements between the rows of y)
+cs_status launch_rmsnorm(float* x, const float* gain, float eps, bf16_t* y, int64_t ldy, int64_t rows, int32_t dim, hipStream_t s,
                          const PendingSum& add = PendingSum());
 // y[g, 0:group*dim) = bf16 hi parts of `group` consecutive normalised rows, y[g, group*dim : 2*group*dim) = lo parts
 cs_status launch_rmsnorm_split(float* x, const float* gain, float eps, bf16_t* y, int64_t rows, int32_t dim,
                                int32_t group, hipStream_t s, const PendingSum& add = PendingSum());
-cs_status launch_layernorm(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows,
+cs_status launch_layernorm(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t ldy, int64_t rows,
                            int32_t dim, hipStream_t s, const PendingSum& add = PendingSum());
 // y[r] = layernorm(mean of `pool` consecutive rows of x)
 cs_status launch_pool_layernorm(const float* x, const float* gain, const float* bias, float eps, bf16_t* y,

@@ -36,7 +36,7 @@ typedef float f32x4_n __attribute__((ext_vector_type(4)));
 template <int MODE, int PARTS, int NV, bool WIDE>
 __global__ __launch_bounds__(WIDE ? 64 * NV : 64) void norm_kernel(float* __restrict__ x, const float* __restrict__ gain,
                                                                    const float* __restrict__ bias, float eps,
-                                                                   bf16_t* __restrict__ y, int dim, int pool, int split_group,
+                                                                   bf16_t* __restrict__ y, int64_t ldy, int dim, int pool, int split_group,
                                                                    bool wt, bool wt_x, PendingSum add) {
 #pragma clang fp contract(off)   // (which products are fused with which sums is written out: it is the same in every form)
   constexpr int P = WIDE ? 1 : NV;   // pieces of this lane
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(WIDE ? 64 * NV : 64) void norm_kernel(float* __rest
     pk.x = pack2_e(o[0], o[1]);
     pk.y = pack2_e(o[2], o[3]);
     if (split_group == 0) {
-      store8(reinterpret_cast<uint2*>(y + row * dim) + c[i], __builtin_bit_cast(wt_f32x2, pk), wt);
+      store8(reinterpret_cast<uint2*>(y + row * ldy) + c[i], __builtin_bit_cast(wt_f32x2, pk), wt);
     } else {
       // hi | lo halves of a row of `split_group` tokens: lo = value - hi, again rounded to bf16
       const uint32_t group = (uint32_t)row / (uint32_t)split_group, at = (uint32_t)row % (uint32_t)split_group;
@@ -165,45 +165,46 @@ static cs_status norm_check(int64_t rows, int dim, const PendingSum& add = Pendi
 // 2048 4.7 against 4.9, 3000 6.0 against 5.6, 8192 12.5 against 11.1, 110 940 174 against 146.
 constexpr int64_t NORM_WIDE_MAX_ROWS = 2048;
 template <int MODE, int PARTS, int NV>
-static void norm_launch_one(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+static void norm_launch_one(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t ldy, int64_t rows, int dim, int pool,
                             int split_group, const PendingSum& add, hipStream_t s) {
-  const bool wt = lines_exclusive(y, (int64_t)dim * 2), wt_x = lines_exclusive(x, (int64_t)dim * 4);
+  const bool wt = lines_exclusive(y, ldy * 2) && dim % 64 == 0, wt_x = lines_exclusive(x, (int64_t)dim * 4);
   if constexpr (PARTS == 0) {
     if (rows > NORM_WIDE_MAX_ROWS) {
-      hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, false>), dim3((unsigned)rows), dim3(64), 0, s, x, gain, bias, eps, y, dim, pool, split_group, wt, wt_x, add);
+      hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, false>), dim3((unsigned)rows), dim3(64), 0, s, x, gain, bias, eps, y, ldy, dim, pool, split_group, wt, wt_x, add);
       return;
     }
   }
-  hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, true>), dim3((unsigned)rows), dim3(64 * NV), 0, s, x, gain, bias, eps, y, dim, pool, split_group, wt, wt_x, add);
+  hipLaunchKernelGGL((norm_kernel<MODE, PARTS, NV, true>), dim3((unsigned)rows), dim3(64 * NV), 0, s, x, gain, bias, eps, y, ldy, dim, pool, split_group, wt, wt_x, add);
 }
 template <int MODE, int PARTS>
-static void norm_launch_nv(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+static void norm_launch_nv(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t ldy, int64_t rows, int dim, int pool,
                            int split_group, const PendingSum& add, hipStream_t s) {
-  if (dim <= 256) norm_launch_one<MODE, PARTS, 1>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
-  else if (dim <= 1024) norm_launch_one<MODE, PARTS, 4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
-  else if (dim <= 1280) norm_launch_one<MODE, PARTS, 5>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
-  else norm_launch_one<MODE, PARTS, NORM_MAX_V4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s);
+  if (dim <= 256) norm_launch_one<MODE, PARTS, 1>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s);
+  else if (dim <= 1024) norm_launch_one<MODE, PARTS, 4>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s);
+  else if (dim <= 1280) norm_launch_one<MODE, PARTS, 5>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s);
+  else norm_launch_one<MODE, PARTS, NORM_MAX_V4>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s);
 }
 template <int MODE>
-static cs_status norm_launch(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows, int dim, int pool,
+static cs_status norm_launch(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t ldy, int64_t rows, int dim, int pool,
                              int split_group, const PendingSum& add, hipStream_t s) {
   static_assert(PENDING_MAX_PARTS == 4, "one instantiation per number of pending sums");
   switch (add.parts ? add.n_parts : 0) {
-    case 0: norm_launch_nv<MODE, 0>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
-    case 1: norm_launch_nv<MODE, 1>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
-    case 2: norm_launch_nv<MODE, 2>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
-    case 3: norm_launch_nv<MODE, 3>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
-    default: norm_launch_nv<MODE, 4>(x, gain, bias, eps, y, rows, dim, pool, split_group, add, s); break;
+    case 0: norm_launch_nv<MODE, 0>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s); break;
+    case 1: norm_launch_nv<MODE, 1>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s); break;
+    case 2: norm_launch_nv<MODE, 2>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s); break;
+    case 3: norm_launch_nv<MODE, 3>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s); break;
+    default: norm_launch_nv<MODE, 4>(x, gain, bias, eps, y, ldy, rows, dim, pool, split_group, add, s); break;
   }
   CS_HIP(hipGetLastError());
   return CS_OK;
 }
 
-cs_status launch_rmsnorm(float* x, const float* gain, float eps, bf16_t* y, int64_t rows, int32_t dim, hipStream_t s,
+cs_status launch_rmsnorm(float* x, const float* gain, float eps, bf16_t* y, int64_t ldy, int64_t rows, int32_t dim, hipStream_t s,
                          const PendingSum& add) {
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
-  return norm_launch<0>(x, gain, nullptr, eps, y, rows, dim, 1, 0, add, s);
+  if (ldy < dim || (ldy & 3)) return fail(CS_ERR_INVALID_ARG, "norm: the pitch of y must be at least dim and a multiple of 4");
+  return norm_launch<0>(x, gain, nullptr, eps, y, ldy, rows, dim, 1, 0, add, s);
 }
 
 cs_status launch_rmsnorm_split(float* x, const float* gain, float eps, bf16_t* y, int64_t rows, int32_t dim,
@@ -211,14 +212,15 @@ cs_status launch_rmsnorm_split(float* x, const float* gain, float eps, bf16_t* y
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
   if (group < 1 || rows % group) return fail(CS_ERR_INVALID_ARG, "rmsnorm_split: rows must be a multiple of the group");
-  return norm_launch<0>(x, gain, nullptr, eps, y, rows, dim, 1, group, add, s);
+  return norm_launch<0>(x, gain, nullptr, eps, y, dim, rows, dim, 1, group, add, s);
 }
 
-cs_status launch_layernorm(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t rows,
+cs_status launch_layernorm(float* x, const float* gain, const float* bias, float eps, bf16_t* y, int64_t ldy, int64_t rows,
                            int32_t dim, hipStream_t s, const PendingSum& add) {
   if (rows <= 0) return CS_OK;
   if (cs_status st = norm_check(rows, dim, add)) return st;
-  return norm_launch<1>(x, gain, bias, eps, y, rows, dim, 1, 0, add, s);
+  if (ldy < dim || (ldy & 3)) return fail(CS_ERR_INVALID_ARG, "norm: the pitch of y must be at least dim and a multiple of 4");
+  return norm_launch<1>(x, gain, bias, eps, y, ldy, rows, dim, 1, 0, add, s);
 }
 
 cs_status launch_pool_layernorm(const float* x, const float* gain, const float* bias, float eps, bf16_t* y,
@@ -226,7 +228,7 @@ cs_status launch_pool_layernorm(const float* x, const float* gain, const float* 
   if (out_rows <= 0) return CS_OK;
   if (cs_status st = norm_check(out_rows, dim)) return st;
   if (pool < 1) return fail(CS_ERR_INVALID_ARG, "pool_layernorm: pool < 1");
-  return norm_launch<1>(const_cast<float*>(x), gain, bias, eps, y, out_rows, dim, pool, 0, PendingSum(), s);
+  return norm_launch<1>(const_cast<float*>(x), gain, bias, eps, y, dim, out_rows, dim, pool, 0, PendingSum(), s);
 }
 
 // ---- gather + cast to bf16 with zero padding; 4 elements per thread
