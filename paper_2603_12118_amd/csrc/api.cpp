@@ -264,7 +264,7 @@ static size_t pack_vector(Arena& A, const SrcTensor& t, int64_t n_pad, RowOf idx
 
 // Rows whose pitch is a multiple of 1 KB start on few of the memory channels, and the rows of a tile are read in step:
 // a line of 128 bytes more per row spreads them (pitch 10240 B, 24 000 x 1280 x 5120: 255 -> 245 us; 8192 B,
-// 8224 x 1024 x 4096: 84.1 -> 78.4 us; pitches of 2048 and 2560 B at K = 1024 and 1280: no change).
+// 8224 x 1024 x 4096: 84.1 -> 78.4 us).
 // Not with a rotary table, whose place in the workspace pays for the 128 bytes per token elsewhere: a batch that fits a
 // workspace of a given size, the static scratch for one, must go on fitting it.
 static int activation_pitch(int cols, bool rope) { return !rope && cols >= 2048 && cols % 512 == 0 ? cols + 64 : cols; }
