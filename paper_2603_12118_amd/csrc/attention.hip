@@ -26,6 +26,12 @@ __device__ __forceinline__ uint32_t pack2_a(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_a));
 }
 
+// v as a value the compiler knows nothing about: what is computed from it is not kept in registers from an earlier time
+__device__ __forceinline__ int afresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // Window layers launch thousands of two-wave workgroups, each a short chain load -> stage ->
 // MFMA -> store: latency is hidden only by residency, so the single-tile variant is held to 168 registers
 // (three waves per SIMD, six workgroups per CU, which is also what their LDS tiles allow).
@@ -55,6 +61,11 @@ void attn_kernel(AttnArgs a) {
   // and a second workgroup onto the CU.
   // (Key groups: the groups have the same queries and write the same bytes.)
   constexpr bool Q_IN_LDS = (DH > 64 && NW == 8) || KG > 1;
+  // There the addresses of the batch's last, partly filled tile are computed where that tile is loaded, too: what of them
+  // does not change from tile to tile was kept, and eight registers spilled to scratch by every workgroup (36 bytes a
+  // lane) for a tile that most never load.  110 940 tokens x 16 heads: 389 002 -> 276 621 KiB written a launch, of which
+  // 277 350 are the output; 8 x 1024 tokens 58.4 -> 57.5 us, 2 x 8192 738 -> 733.
+  constexpr bool LAST_TILE_AFRESH = DH > 64 && NW == 8;
   static_assert(KG == 1 || (!SINGLE && QT == 1 && DH % 32 == 0), "key groups: one 32-query block per wave");
   constexpr int K_BYTES = 64 * KSTR, V_BYTES = DT * 32 * VSTR;
   __shared__ __align__(16) unsigned char tiles[KG * (K_BYTES + V_BYTES)];
@@ -190,9 +201,10 @@ void attn_kernel(AttnArgs a) {
       }
       return;
     }
+    const int t = LAST_TILE_AFRESH ? afresh(tid) : tid;
 #pragma unroll
     for (int u = 0; u < K_PT; ++u) {
-      int c = tid + u * NT;
+      int c = t + u * NT;
       c = c < 64 * KCH ? c : 64 * KCH - 1;
       const int r = c / KCH, ch = c % KCH;
       int row = kv + r;
@@ -201,7 +213,7 @@ void attn_kernel(AttnArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < V_PT; ++u) {
-      int c = tid + u * NT;
+      int c = t + u * NT;
       c = c < DH * 16 ? c : DH * 16 - 1;
       const int d = c >> 4, ch = c & 15;
       int tok = kv + ch * 4;

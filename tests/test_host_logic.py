@@ -332,3 +332,12 @@ def test_key_groups_refuse_keys_beyond_32_bit_offsets(seg, heads, ld_vt, groups)
     args = (16, 16, ld_vt, 16, s.ctypes.data_as(C.POINTER(C.c_int32)), len(seg) - 1, heads, 64, groups, None)
     assert B.lib().cs_attention_varlen_groups(*args) == 5            # CS_ERR_UNSUPPORTED
     assert B.lib().cs_attention_varlen_groups(*args[:8], 3, None) == 1
+
+
+def test_no_kernel_uses_scratch_memory():
+    """Registers that do not fit go to scratch, which is HBM: the code objects inside the built library say of every kernel
+    how many bytes of it a lane takes (the metadata's map has its keys in order, so the size follows the name)."""
+    blob = open(B.LIB_PATH, "rb").read()
+    found = re.findall(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_Z\w+)\xbb\.private_segment_fixed_size(.)", blob, re.S)
+    assert len(found) == blob.count(b".private_segment_fixed_size") > 0
+    assert [name.decode() for name, size in found if size != b"\0"] == []
