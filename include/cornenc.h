@@ -352,7 +352,8 @@ cs_status cs_plan_tokens(const cs_encoder_config* config, const int32_t* cu_seql
                          int32_t win_cu_capacity, int32_t* n_windows);
 /* The same for the work lists of the full-attention layers (audio: of every layer): `work` [n_full + n_tail, 4]
  * (or NULL) receives query range and key range (q0, q1, kv0, kv1) of each item, internal token order, the items of
- * the main launch first, then those of the launch for short last blocks (items of at most 64 queries). */
+ * the main list first, then the short last blocks (items of at most 64 queries), which have a launch of their own
+ * unless cs_plan_attention_queries says that the batch runs as workgroups of 64 queries. */
 typedef struct {
   int32_t n_full, n_tail;
   int32_t q_per_block;     /* queries an item of the main list has at most: 64, 128 or 256 */
@@ -361,6 +362,10 @@ typedef struct {
 } cs_attention_plan;
 cs_status cs_plan_attention(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
                             int32_t n_items, int32_t* work, int32_t work_capacity, cs_attention_plan* out);
+/* The queries a workgroup of the main launch takes: q_per_block, or 64 where that is 256 and the batch is so small that
+ * every item runs as four workgroups of 64 queries (no key groups; the short items are then part of that launch). */
+cs_status cs_plan_attention_queries(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
+                                    int32_t n_items, int32_t* queries);
 
 /* Component calls: the two contraction kernels on their own, for parity tests and
  * micro-benchmarks.  All pointers dev.

@@ -73,6 +73,7 @@ def lib() -> C.CDLL:
         L.cs_forward_embeddings.argtypes = [vp, vp, vp, i64, i64, C.c_int32, C.c_int32, vp, vp]
         L.cs_plan_tokens.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p, i32p, i32p, C.c_int32, i32p]
         L.cs_plan_attention.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p, C.c_int32, C.POINTER(cs_attention_plan)]
+        L.cs_plan_attention_queries.argtypes = [C.POINTER(cs_encoder_config), i32p, i32p, C.c_int32, i32p]
         L.cs_linear_bf16.argtypes = [vp, i64, vp, vp, vp, C.c_int32, i64, C.c_int32, C.c_int32, vp]
         L.cs_linear_kernel.argtypes = [i64, C.c_int32, i64, C.c_int32, C.c_int32, C.c_char_p, C.c_size_t]
         L.cs_attention_varlen.argtypes = [vp, vp, i64, vp, i32p, C.c_int32, C.c_int32, C.c_int32, vp]
@@ -108,7 +109,7 @@ def lib() -> C.CDLL:
         L.cs_last_error.restype = C.c_char_p
         for f in ("cs_encoder_create", "cs_encoder_query", "cs_encode", "cs_encode_static", "cs_encoder_plan_cache_stats", "cs_encode_graph_create",
                   "cs_encode_graph_launch",
-                  "cs_forward_embeddings", "cs_plan_tokens", "cs_plan_attention",
+                  "cs_forward_embeddings", "cs_plan_tokens", "cs_plan_attention", "cs_plan_attention_queries",
                   "cs_linear_bf16", "cs_linear_kernel", "cs_attention_varlen", "cs_attention_varlen_groups", "cs_encoder_time_step", "cs_encoder_step_kernel", "cs_encoder_time_every",
                   "cs_encoder_read_timing", "cs_patchify", "cs_mfma_ceiling", "cs_pack_batch", "cs_channel_create",
                   "cs_channel_acquire", "cs_channel_publish", "cs_channel_forward", "cs_channel_release",
@@ -303,6 +304,14 @@ def cs_plan_attention(cfg, cu_seqlens, grid_thw):
     work = np.empty((p.n_full + p.n_tail, 4), np.int32)
     _check(lib().cs_plan_attention(C.byref(cc), _i32p(cu), _i32p(g), g.shape[0], _i32p(work), len(work), C.byref(p)))
     return p, work[:p.n_full], work[p.n_full:]
+
+
+def cs_plan_attention_queries(cfg, cu_seqlens, grid_thw) -> int:
+    """Host-only: queries a workgroup of the full-attention layers takes."""
+    cu, g = _i32(cu_seqlens), _i32(grid_thw)
+    cc, n = make_config(cfg), C.c_int32()
+    _check(lib().cs_plan_attention_queries(C.byref(cc), _i32p(cu), _i32p(g), g.shape[0], C.byref(n)))
+    return n.value
 
 
 def cs_forward_embeddings(src, placeholder_index, dst_seq, err_flag=None, stream=None) -> None:

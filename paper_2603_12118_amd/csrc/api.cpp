@@ -854,21 +854,22 @@ cs_status cs_plan_tokens(const cs_encoder_config* config, const int32_t* cu_seql
   });
 }
 
+static cs_status build_plan_of_config(const cs_encoder_config& config, const int32_t* cu_seqlens, const int32_t* grid_thw,
+                                      int32_t n_items, BatchPlan& p) {
+  if (cs_status st = check_config(config)) return st;
+  if (config.arch == CS_ARCH_VIT) return build_vit_plan(config, cu_seqlens, grid_thw, n_items, p);
+  if (config.arch == CS_ARCH_AUDIO) return build_audio_plan(config, cu_seqlens, grid_thw, n_items, p);
+  if (!grid_thw || n_items <= 0) return fail(CS_ERR_INVALID_ARG, "cs_plan_attention: no items");
+  const int64_t n_pos = 1 + (int64_t)grid_thw[1] * grid_thw[2];   // as cs_plan_tokens
+  if (n_pos < 5 || n_pos > (1 << 20)) return fail(CS_ERR_SHAPE, "cs_plan_attention: tile size");
+  return build_cls_plan(config, (int32_t)n_pos, cu_seqlens, grid_thw, n_items, p);
+}
+
 static cs_status plan_attention(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
                                 int32_t n_items, int32_t* work, int32_t work_capacity, cs_attention_plan* out) {
   if (!config || !out || (!work && work_capacity > 0)) return fail(CS_ERR_INVALID_ARG, "cs_plan_attention: NULL argument");
-  if (cs_status st = check_config(*config)) return st;
   BatchPlan p;
-  if (config->arch == CS_ARCH_VIT) {
-    if (cs_status st = build_vit_plan(*config, cu_seqlens, grid_thw, n_items, p)) return st;
-  } else if (config->arch == CS_ARCH_AUDIO) {
-    if (cs_status st = build_audio_plan(*config, cu_seqlens, grid_thw, n_items, p)) return st;
-  } else {
-    if (!grid_thw || n_items <= 0) return fail(CS_ERR_INVALID_ARG, "cs_plan_attention: no items");
-    const int64_t n_pos = 1 + (int64_t)grid_thw[1] * grid_thw[2];   // as cs_plan_tokens
-    if (n_pos < 5 || n_pos > (1 << 20)) return fail(CS_ERR_SHAPE, "cs_plan_attention: tile size");
-    if (cs_status st = build_cls_plan(*config, (int32_t)n_pos, cu_seqlens, grid_thw, n_items, p)) return st;
-  }
+  if (cs_status st = build_plan_of_config(*config, cu_seqlens, grid_thw, n_items, p)) return st;
   out->n_full = p.n_full_work;
   out->n_tail = p.n_tail_work;
   out->q_per_block = p.full_q_per_block;
@@ -885,6 +886,17 @@ static cs_status plan_attention(const cs_encoder_config* config, const int32_t* 
 cs_status cs_plan_attention(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
                             int32_t n_items, int32_t* work, int32_t work_capacity, cs_attention_plan* out) {
   return guarded("cs_plan_attention", [&] { return plan_attention(config, cu_seqlens, grid_thw, n_items, work, work_capacity, out); });
+}
+
+cs_status cs_plan_attention_queries(const cs_encoder_config* config, const int32_t* cu_seqlens, const int32_t* grid_thw,
+                                    int32_t n_items, int32_t* queries) {
+  return guarded("cs_plan_attention_queries", [&]() -> cs_status {
+    if (!config || !queries) return fail(CS_ERR_INVALID_ARG, "cs_plan_attention_queries: NULL argument");
+    BatchPlan p;
+    if (cs_status st = build_plan_of_config(*config, cu_seqlens, grid_thw, n_items, p)) return st;
+    *queries = p.full_q_split ? 64 : p.full_q_per_block;
+    return CS_OK;
+  });
 }
 
 // The encoder task.  may_grow: the pinned staging slots may be re-allocated for a batch whose index

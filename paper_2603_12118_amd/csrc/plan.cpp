@@ -74,9 +74,14 @@ static bool share_keys(const cs_encoder_config& cfg, int64_t items_256, int64_t 
 // Without groups, items of up to 256 queries run as four workgroups of 64 (two waves each) while that makes at most two
 // per CU.  A workgroup of eight waves walks its key tiles at two waves per SIMD, 1.9 us a tile, one of two waves at 1 us,
 // and the short last blocks join the same launch.  Queries keep their waves of 32, so the results are the same bits, and
-// the lists stay as they are (a batch's workspace must not grow).  us a layer, 256 -> 64 queries a workgroup, heads x
-// tokens: 16 x 256 11.5 -> 7.3 (64 workgroups), 576 31.4 -> 12.9 (144), 1024 30.3 -> 21.5 (256), two items of 1024 32.3 ->
-// 30.5 (512); beyond that 2116 60.7 -> 60.5 (544), three of 1024 34.4 -> 36.5 (768), 20 x 8 x 500 25.0 -> 28.3 (1280).
+// the lists stay as they are (a batch's workspace must not grow).  us a layer, 256 -> 64 queries a workgroup:
+//   16 heads of 80: 256 tokens 11.8 -> 8.4 (64 workgroups), 576 31.8 -> 12.8 (144), 1024 29.1 -> 20.7 (256), 1536 43.0 ->
+//     41.2 (384), two items of 1024 30.8 -> 29.7 (512), 2048 56.0 -> 55.7 (512); beyond 2116 60.7 -> 60.5 (544), three of
+//     1024 34.4 -> 36.5 (768)
+//   heads of 64: 16 x 256 9.4 -> 7.0 (64), 20 x 256 9.9 -> 7.5 (80), 16 x 576 25.8 -> 11.6 (144), 1024 21.8 -> 18.2 (256),
+//     20 x 1024 21.7 -> 21.2 (320), 12 x 2048 39.1 -> 38.2 (384), 16 x 2 x 1024 23.1 -> 22.9 (512), 2048 40.5 -> 40.4 (512);
+//     beyond 16 x 5 x 400 13.4 -> 14.1 (560), 12 x 3 x 1024 22.9 -> 25.8 (576), 20 x 2048 42.0 -> 48.6 (640); items of which
+//     a short last block would be a launch of its own gain there too: 20 x 3 x 576 26.5 -> 17.0 (540)
 static void split_queries(const cs_encoder_config& cfg, BatchPlan& p) {
   if (p.full_q_per_block != 256 || p.full_key_groups != 1 || (p.n_tail_work > 0 && (p.tail_key_groups != 1 || p.off_tail_work != p.off_full_work + 4 * (size_t)p.n_full_work))) return;
   int64_t blocks = 0;

@@ -341,3 +341,35 @@ def test_no_kernel_uses_scratch_memory():
     found = re.findall(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_Z\w+)\xbb\.private_segment_fixed_size(.)", blob, re.S)
     assert len(found) == blob.count(b".private_segment_fixed_size") > 0
     assert [name.decode() for name, size in found if size != b"\0"] == []
+
+
+# ---- 256-query items as workgroups of 64 queries
+def workgroup_queries(cfg, grid):
+    g = np.asarray(grid, np.int32)
+    cu = np.concatenate([[0], np.cumsum(g.astype(np.int64).prod(1))]).astype(np.int32)
+    return B.cs_plan_attention_queries(cfg, cu, g)
+
+
+@pytest.mark.parametrize("cfg", [wl.vit_7b_config(), replace(wl.vit_7b_config(), hidden=512, n_heads=8, head_dim=64, rope_sections=(0, 16, 16))])
+def test_few_queries_run_as_workgroups_of_64(cfg):
+    """While the batch's blocks of 64 queries, each item's last one counted whole, make at most two workgroups per CU."""
+    rng = np.random.default_rng(3)
+    for _ in range(200):
+        grid = [(1, 2 * int(rng.integers(1, 24)), 2 * int(rng.integers(1, 24))) for _ in range(int(rng.integers(1, 8)))]
+        blocks = sum(-(-h * w // 64) for _, h, w in grid)
+        assert workgroup_queries(cfg, grid) == (64 if blocks * cfg.n_heads <= 512 else 256), grid
+
+
+def test_query_split_on_both_sides_of_its_line():
+    vit, cls, audio = wl.vit_7b_config(), wl.vit_cls_config(), wl.audio_config()
+    for cfg, grid, queries in [
+            (vit, [(1, 32, 64)], 64), (vit, [(1, 38, 54)], 256),                   # 16 heads: 32 blocks of 64, and 2052 tokens
+            (vit, [(1, 4, 4)] * 32, 64), (vit, [(1, 4, 4)] * 33, 256),
+            (cls, [(1, 18, 18)] * 5, 64), (cls, [(1, 18, 18)] * 6, 256),           # 328 tokens: six blocks a tile
+            (cls, [(1, 32, 32)], 128), (cls, [(1, 32, 32)] * 6, 256),              # key groups; tail items in four of them
+            (audio, [(1, 1, 1024)] * 3, 64), (audio, [(1, 1, 1024)] * 4, 256),     # 20 heads: 24 and 32 blocks
+            (audio, [(1, 1, 3000)], 128),                                          # key groups
+            (replace(audio, attn_chunk=200), [(1, 1, 2400)], 64), (replace(audio, attn_chunk=200), [(1, 1, 2800)], 256),
+            (replace(audio, attn_chunk=100), [(1, 1, 400)], 64)]:                  # (64-query items already)
+        assert workgroup_queries(cfg, grid) == queries, grid
+    assert B.lib().cs_plan_attention_queries(None, None, None, 1, None) == B.CS_ERR_INVALID_ARG
