@@ -375,7 +375,8 @@ cs_status cs_plan_attention_queries(const cs_encoder_config* config, const int32
 cs_status cs_linear_bf16(const void* A, int64_t lda, const void* W, const float* bias, void* C,
                          int32_t c_dtype, int64_t M, int32_t N, int32_t K, void* stream);
 /* Host-only: the name of the kernel instantiation (as cs_encoder_step_kernel writes it; ", far rows" behind it where the
- * rows lie too far apart for 32-bit offsets) that cs_linear_bf16 runs for these sizes, to `out` (capacity >= 96). */
+ * rows lie too far apart for 32-bit offsets, ", <n> half tiles" where so many workgroups of the last round run half a
+ * tile each) that cs_linear_bf16 runs for these sizes, to `out` (capacity >= 96). */
 cs_status cs_linear_kernel(int64_t lda, int32_t c_dtype, int64_t M, int32_t N, int32_t K, char* out, size_t capacity);
 
 /* cs_attention_varlen: softmax(q k^T) v per head inside each segment; q already carries the

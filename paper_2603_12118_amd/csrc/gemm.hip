@@ -947,7 +947,7 @@ constexpr bool tail_splits() { return TAIL == TAIL_SPLIT || (TAIL == TAIL_LIGHT 
 // of A and 8 slices of W per k-step (an L2 miss on every W byte otherwise: measured 427 clocks average
 // L2 read latency and the L1 miss queue full 58 % of the time).
 // A workgroup's way to its first load is a chain of scalar work that nothing hides, a tenth of a small launch, so no
-// division is left in it: x / d = high 64 bits of x * reciprocal(d), exact for all x < 2^32, 2 <= d < 2^32 (the reciprocal
+// division is left in that of a whole or a half tile (the 64-row tiles of a light tail divide by their number): x / d = high 64 bits of x * reciprocal(d), exact for all x < 2^32, 2 <= d < 2^32 (the reciprocal
 // exceeds 2^64 / d by at most one, which adds less than x / 2^64 < 1 / d to the quotient).  With the launch's tile counts in
 // the arguments and the arguments in two lines: 256 x 3840 x 1280 10.8 -> 10.4 us, 256 x 1280 x 3456 in three parts 8.4 ->
 // 8.1, a lone 64 x 64 x 64 tile 3.4 -> 3.0.
@@ -1049,16 +1049,6 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   constexpr int LDS = launch_lds_bytes<BM, BN, WGM * WGN, EPI, TAIL, STAGES>();
   static_assert(LDS <= 160 * 1024, "LDS of a CU");
   auto kern = gemm_kernel<BM, BN, WGM, WGN, EPI, TAIL, STAGES, FAR>;
-  if (g.describe) {
-    snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32%s", BM, BN, WGM, WGN, EPI, TAIL, FAR ? ", far rows" : "");
-    return CS_OK;
-  }
-  // one attribute call per instantiation (two threads that both see `false` repeat a harmless call)
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set.load(std::memory_order_acquire)) {
-    CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
-    attr_set.store(true, std::memory_order_release);
-  }
   GemmArgs ga = g;
   const int tiles_n = (g.N + BN - 1) / BN;
   // the tiles that are run whole or in halves: with a light tail those of the full tile rows
@@ -1075,6 +1065,17 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
       ga.half_tiles = 2 * rest;
       tiles += rest;
     }
+  }
+  if (g.describe) {
+    const int n = snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32%s", BM, BN, WGM, WGN, EPI, TAIL, FAR ? ", far rows" : "");
+    if (ga.half_tiles > 0) snprintf(g.describe + n, 96 - n, ", %d half tiles", ga.half_tiles);
+    return CS_OK;
+  }
+  // one attribute call per instantiation (two threads that both see `false` repeat a harmless call)
+  static std::atomic<bool> attr_set{false};
+  if (!attr_set.load(std::memory_order_acquire)) {
+    CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
+    attr_set.store(true, std::memory_order_release);
   }
   ga.grid_tiles = whole - ga.half_tiles / 2;
   ga.band_recip = reciprocal((uint32_t)(GROUP_M * tiles_n));

@@ -373,3 +373,25 @@ def test_query_split_on_both_sides_of_its_line():
             (replace(audio, attn_chunk=100), [(1, 1, 400)], 64)]:                  # (64-query items already)
         assert workgroup_queries(cfg, grid) == queries, grid
     assert B.lib().cs_plan_attention_queries(None, None, None, 1, None) == B.CS_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("full_rows,N,rest,halves", [
+    (17, 4096, 1, 32), (17, 4096, 255, 32), (23, 4096, 65, 224), (23, 4096, 129, 0), (24, 4096, 1, 0),   # 256 of both, 272; 256 and 16
+    (16, 4096, 64, 0), (32, 4096, 64, 0),                                                                # exactly full rounds
+    (13, 5120, 72, 8), (33, 4096, 0, 32), (24, 4096, 0, 256), (25, 4096, 0, 0)])                         # (without a light tail, half a round at most)
+def test_half_tiles_by_what_the_last_round_holds(full_rows, N, rest, halves):
+    if any(k.startswith("CS_GEMM_") for k in os.environ):
+        pytest.skip("a measurement switch in the environment changes the choice")
+    name = B.cs_linear_kernel(256 * full_rows + rest, N, 1280)
+    assert name.startswith("gemm_kernel<256, 256, 2, 4, 1, ") and name.endswith(f"16x16x32, {halves} half tiles" if halves else "16x16x32")
+
+
+def test_one_round_launches_by_tile():
+    if any(k.startswith("CS_GEMM_") for k in os.environ):
+        pytest.skip("a measurement switch in the environment changes the choice")
+    # the launches of the towers that take 128 x 160 tiles: rows and columns of the convolutions, the patch embedding, fc1,
+    # the merger (whose epilogues take the tile that these plain ones take), and the sizes beside them
+    for M, N, tile in [(3400, 1280, "128, 160"), (3900, 1280, "128, 160"), (4096, 1280, "128, 160"), (4097, 1280, "128, 256"),
+                       (804, 5120, "128, 160"), (975, 5120, "128, 160"), (1024, 5120, "128, 160"), (1028, 5120, "128, 256"),
+                       (1028, 4096, "128, 160"), (768, 5120, "128, 128"), (3200, 1280, "128, 128")]:
+        assert B.cs_linear_kernel(M, N, 1280).startswith(f"gemm_kernel<{tile}, "), (M, N)
