@@ -45,7 +45,7 @@ def test_tile_ends(dh, segs):
 
 
 # the pitch up to which 32-bit offsets reach (rows of the head and one step of a 512-thread workgroup), and the next one;
-# 2.3 GB of v^T, of which the columns of the batch are touched
+# 1.4 GB (head dimension 64) and 1.5 GB (80) of v^T, of which the columns of the batch are touched
 @pytest.mark.parametrize("dh", [64, 80])
 @pytest.mark.parametrize("beyond", [False, True])
 def test_far_pitch(dh, beyond):

@@ -17,9 +17,9 @@ def vit(hidden):
                             rope_sections=(0, 16, 16))
 
 
-# 192, 256: one piece per lane (48 and 64 of its lanes at work); 320: two of four waves, 1024: all four; 1088: a fifth for
+# 768: rows of 1536 bytes, the normalised ones and the weights that read them 1664 apart; 192, 256: one piece per lane (48 and 64 of its lanes at work); 320: two of four waves, 1024: all four; 1088: a fifth for
 # 16 lanes; 1344: six of eight, 2048: all
-@pytest.mark.parametrize("hidden", [192, 256, 320, 1024, 1088, 1344, 2048])
+@pytest.mark.parametrize("hidden", [192, 256, 320, 768, 1024, 1088, 1344, 2048])
 def test_rms_rows(hidden):
     w = wl.images_workload(f"rows_{hidden}", vit(hidden), [(140, 84), (28, 56)], seq_len=512, data_seed=hidden)
     check_items(f"vision tower, hidden {hidden}", w, w.weights, [0, 1])
@@ -30,6 +30,15 @@ def test_layer_norm_rows(hidden):
     cfg = replace(wl.audio_config(2), hidden=hidden, n_heads=hidden // 64, head_dim=64, mlp_dim=512, out_hidden=256)
     w = wl.audio_workload(f"clip_{hidden}", cfg, 2, 136, seq_len=512, data_seed=hidden)
     check_items(f"audio tower, hidden {hidden}", w, w.weights, [0, 1])
+
+
+# a LayerNorm tower whose rows are set apart: one tile (split sums, the normalisation kernel writes the rows) and three
+# (3084 tokens: the residual GEMMs write them, scaled by the gain, and QKV and fc1 normalise)
+@pytest.mark.parametrize("n_tiles", [1, 3])
+def test_layer_norm_rows_apart(n_tiles):
+    cfg = replace(wl.vit_cls_config(2), hidden=768, n_heads=12, mlp_dim=1536, merger_hidden=512, out_hidden=512)
+    w = wl.images_workload(f"tiles_768_{n_tiles}", cfg, [(448, 448)] * n_tiles, seq_len=2048, data_seed=n_tiles)
+    check_items(f"class-token tower, hidden 768, {n_tiles} tiles", w, w.weights, sorted({0, n_tiles - 1}))
 
 
 @pytest.mark.parametrize("size", [(896, 448), (532, 756)])       # 2048 rows, 2052 rows
