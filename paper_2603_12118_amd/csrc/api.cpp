@@ -274,6 +274,7 @@ static int activation_pitch(int cols, bool rope) { return !rope && cols >= 2048 
 // weights, then weights and xn: 256 x 6912 x 1280 12.9 -> 12.2 -> 11.8 us, 1024 x 3840 17.6 -> 16.9 -> 16.1, 1024 x 6912
 // 28.3 -> 27.5 -> 26.7, 1500 x 3840 25.7 -> 23.8 -> 22.9, 5128 x 3840 63 -> 61 -> 60, 8192 x 6912 126 -> 123.5 -> 124.4,
 // 110 940 rows the same; pitches of 1536, 3072 and 5120 B gain alike, 2048 B loses (1028 x 4096 x 1024 19.4 -> 19.9).
+// The price is 128 bytes of device memory per weight row: 49 MB on 32 layers of 12 032 rows of 1280.
 static int row_pitch(int cols) {
   const int bytes = 2 * cols;
   return bytes % 512 == 0 && (bytes & (bytes - 1)) != 0 ? cols + 64 : cols;
@@ -470,8 +471,10 @@ struct Workspace {
 constexpr int MAX_K_PARTS = PENDING_MAX_PARTS;
 constexpr int64_t SPLIT_K_MAX_TOKENS = 2560;
 
-// Parts for x += A W^T with M rows, N columns, K deep on 128 x 128 tiles: as many (at most MAX_K_PARTS)
-// as divide the K slices evenly, leave four slices or more per part and keep the launch within 640 workgroups.
+// Parts for x += A W^T with M rows, N columns, K deep: as many (at most MAX_K_PARTS) as divide the K slices evenly, leave
+// four slices or more per part and keep the launch within 640 workgroups, counted in tiles of 128 x 128.  (That was the
+// tile of all split launches when the limits were measured.  A launch now takes the tile that makes one round, 64 x 64
+// to 128 x 256, and the limits have not been measured on those.)
 static int k_parts(int64_t M, int64_t N, int64_t K) {
   const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128);
   if (wgs > 160) return 1;
@@ -531,8 +534,9 @@ static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   w.s_proj = w.split_k ? k_parts(N, D, D) : 1;
   w.s_down = w.split_k ? k_parts(N, D, e->I_pad) : 1;
   // The out projection's short K loop is not split once 128 x 160 tiles fill half the chip: unsplit, the launch
-  // folds the next RMSNorm into its epilogue, which saves more than the split gains (2048 tokens: 5.33 -> 5.19 ms
-  // per step; 1024 tokens: 3.95 -> 4.00 ms, so those stay split).
+  // folds the next RMSNorm into its epilogue, which saves more than the split gains.  us a layer, split -> unsplit: 64
+  // workgroups (1024 tokens) +6.1, 96 (1520) +1.5, 112 (1680) -5.2, 128 (1936, 2024) -7.9 and -7.1, 136 -0.3.  (A line
+  // at 104, and the same for the LayerNorm towers, which always split: 96 +2.3, 104 -2.9, 128 -8.8, is not yet drawn.)
   if (w.s_proj > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
       gemm_norm_fold_parts(N, D, D, e->D_ldw, scaled, ln) > 0)
     w.s_proj = 1;

@@ -26,10 +26,10 @@ typedef float f32x4_n __attribute__((ext_vector_type(4)));
 // PARTS: the number of pending split-K sums, which join the residual stream here (pool == 1), in part order.
 // NV: 16-byte pieces of a row per lane of a wave, the smallest instantiation that covers dim.
 // A row is a dozen kilobytes and the work on it a few hundred instructions, so a launch over few rows (a small batch,
-// whose pending sums join here) lasts as long as its loads' latency: every load of a row, of its pending sums and of
-// gain and bias is issued before the first is used, and WIDE gives each piece a wave of its own (a workgroup of NV waves
-// per row; the waves exchange their lanes' sums through LDS and add them piece by piece, in the order in which one wave
-// adds its own, so both forms give the same bits).  Rows of 1280 with four pending sums, before (a wave per row, guarded
+// whose pending sums join here) lasts as long as its loads' latency: WIDE gives each piece a wave of its own and issues
+// every load of a row, of its pending sums and of gain and bias before the first is used (a workgroup of NV waves per
+// row; the waves exchange their lanes' sums through LDS and add them piece by piece, in the order in which one wave adds
+// its own, so both forms give the same bits).  A wave alone loads gain and bias behind the statistics.  Rows of 1280 with four pending sums, before (a wave per row, guarded
 // loads that compiled to single words through the flat path, gain behind the statistics) -> now: 256 rows 5.4 -> 2.8 us,
 // 1024 9.1 -> 4.1, 1500 (LayerNorm) 12.0 -> 6.9, 2560 16.6 -> 13.1 (5.1 TB/s); x is stored write-through where its rows
 // are whole lines (1500 rows 8.4 -> 6.9: no write-back at the kernel's end).
