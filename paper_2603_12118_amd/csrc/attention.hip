@@ -2,7 +2,7 @@
 //
 // A work item names a block of queries [q0,q1) and the keys [kv0,kv1) they attend to (both in
 // token indices of the packed batch); a window layer has one item per window, a full layer
-// cuts every sequence into query blocks.  Inside a workgroup every wave owns 64 queries and
+// cuts every sequence into query blocks.  Inside a workgroup every wave owns 32 queries and
 // all waves walk the same 64-key tiles, which are staged in LDS once per workgroup.
 //
 // Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: a lane then holds
