@@ -204,7 +204,7 @@ def main() -> int:
         n_tokens //= 2
     elif w.cfg.arch == "vit_cls":
         n_tokens += 4 * w.n_items
-    kernel = enc.cs_encoder_step_kernel(B.STEPS[dominant], n_tokens)
+    kernel = enc.cs_encoder_batch_kernel(B.STEPS[dominant], n_tokens)
     traffic, traffic_src = measured_traffic(w.name, kernel, args.items <= 0)
     res = {
         "metric": "encoder_patches_per_s" if w.cfg.arch != "audio" else "encoder_mel_frames_per_s",

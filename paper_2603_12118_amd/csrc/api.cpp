@@ -2,6 +2,7 @@
 // host), batch query, the encoder task itself (a fixed sequence of kernel launches on the
 // caller's stream) and the embedding hand-off.
 #include <math.h>
+#include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
@@ -494,6 +495,22 @@ static bool fold_off() {
   return off;
 }
 
+// Parts over K that a residual GEMM of a batch of N tokens runs in: the out projection, or the down projection.
+static int residual_parts(const cs_encoder* e, int64_t N, bool down) {
+  if (N > SPLIT_K_MAX_TOKENS) return 1;
+  const cs_encoder_config& c = e->cfg;
+  const int64_t D = c.hidden;
+  const int parts = k_parts(N, D, down ? e->I_pad : D);
+  // The out projection's short K loop is not split once 128 x 160 tiles fill half the chip: unsplit, the launch
+  // folds the next RMSNorm into its epilogue, which saves more than the split gains.  us a layer, split -> unsplit: 64
+  // workgroups (1024 tokens) +6.1, 96 (1520) +1.5, 112 (1680) -5.2, 128 (1936, 2024) -7.9 and -7.1, 136 -0.3.  (A line
+  // at 104, and the same for the LayerNorm towers, which always split: 96 +2.3, 104 -2.9, 128 -8.8, is not yet drawn.)
+  if (!down && parts > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
+      gemm_norm_fold_parts(N, D, D, e->D_ldw, false, false) > 0)
+    return 1;
+  return parts;
+}
+
 static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   const cs_encoder_config& c = e->cfg;
   const int64_t N = p.n_tok, D = c.hidden;
@@ -531,15 +548,8 @@ static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   w.ss_stride = round_up(N, 64);
   // (a residual GEMM that runs split over K leaves its partial sums to the normalisation kernel: no fold)
   const bool ln = c.arch != CS_ARCH_VIT, scaled = c.arch == CS_ARCH_VIT_CLS;
-  w.s_proj = w.split_k ? k_parts(N, D, D) : 1;
-  w.s_down = w.split_k ? k_parts(N, D, e->I_pad) : 1;
-  // The out projection's short K loop is not split once 128 x 160 tiles fill half the chip: unsplit, the launch
-  // folds the next RMSNorm into its epilogue, which saves more than the split gains.  us a layer, split -> unsplit: 64
-  // workgroups (1024 tokens) +6.1, 96 (1520) +1.5, 112 (1680) -5.2, 128 (1936, 2024) -7.9 and -7.1, 136 -0.3.  (A line
-  // at 104, and the same for the LayerNorm towers, which always split: 96 +2.3, 104 -2.9, 128 -8.8, is not yet drawn.)
-  if (w.s_proj > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
-      gemm_norm_fold_parts(N, D, D, e->D_ldw, scaled, ln) > 0)
-    w.s_proj = 1;
+  w.s_proj = residual_parts(e, N, false);
+  w.s_down = residual_parts(e, N, true);
   w.fold_proj = w.s_proj == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, D, e->D_ldw, scaled, ln) : 0;
   w.fold_down = w.s_down == 1 && !fold_off() ? gemm_norm_fold_parts(N, D, e->I_pad, e->I_ld, scaled, ln) : 0;
   w.ss = take((w.fold_proj || w.fold_down) ? (size_t)8 * w.ss_stride * 4 : 0);
@@ -640,6 +650,56 @@ static cs_status guarded(const char* who, F&& body) {
 constexpr size_t STAGE_BYTES_AT_CREATE = (size_t)1 << 20;
 
 }  // namespace cs
+
+// as_run: with the parts over K and the tiles that small batches have for themselves
+static cs_status step_kernel(const char* who, const cs_encoder* enc, int32_t step, int64_t n_tokens, bool as_run, char* out, size_t capacity) {
+  if (!enc || !out || capacity < 96 || n_tokens <= 0 || n_tokens > 0x7fffffff)
+    return fail(CS_ERR_INVALID_ARG, std::string(who) + ": NULL argument, capacity below 96 or bad token count");
+  const cs_encoder_config& c = enc->cfg;
+  const int64_t D = c.hidden;
+  GemmArgs g = {};
+  g.small_batch = as_run && n_tokens <= SPLIT_K_MAX_TOKENS;
+  g.describe = out;
+  g.M = (int32_t)n_tokens;
+  int epi = EPI_BF16;
+  switch (step) {
+    case CS_STEP_QKV:
+      g.N = (int32_t)(3 * D); g.K = (int32_t)D; g.ldo = 2 * D; g.hidden = (int32_t)D; g.head_dim = c.head_dim; g.ld_vt = round_up(n_tokens, 64);
+      g.M = (int32_t)round_up(n_tokens, 4);
+      epi = EPI_QKV;
+      break;
+    case CS_STEP_PROJ:
+      g.N = (int32_t)D; g.K = (int32_t)D; g.ldo = D;
+      epi = c.arch == CS_ARCH_VIT_CLS ? EPI_RESADD_SCALED_F32 : EPI_RESADD_F32;
+      break;
+    case CS_STEP_MLP_UP:
+      g.N = c.arch == CS_ARCH_VIT ? 2 * enc->I_pad : enc->I_pad; g.K = (int32_t)D; g.ldo = enc->I_pad;
+      epi = c.arch == CS_ARCH_VIT ? EPI_SWIGLU_BF16 : EPI_GELU_BF16;
+      break;
+    case CS_STEP_MLP_DOWN:
+      g.N = (int32_t)D; g.K = enc->I_pad; g.ldo = D;
+      epi = c.arch == CS_ARCH_VIT_CLS ? EPI_RESADD_SCALED_F32 : EPI_RESADD_F32;
+      break;
+    default: return fail(CS_ERR_INVALID_ARG, std::string(who) + ": step must be one of the four GEMM steps of a block");
+  }
+  // (an audio tower's residual GEMMs run the instantiation that also writes the plain sums of a folded LayerNorm)
+  if (epi == EPI_RESADD_F32 && c.arch == CS_ARCH_AUDIO && !fold_off() &&
+      (n_tokens > SPLIT_K_MAX_TOKENS || k_parts(n_tokens, D, g.K) == 1))
+    g.s1_out = reinterpret_cast<float*>(uintptr_t(16));   // describe mode: only looked at, never written
+  g.lda = g.ldw = step == CS_STEP_MLP_DOWN ? enc->I_ld : enc->D_ldw;
+  if (epi == EPI_RESADD_SCALED_F32) g.col_scale = enc->ptr<float>(enc->layers[0].ls1);
+  if (as_run && (step == CS_STEP_PROJ || step == CS_STEP_MLP_DOWN)) {
+    const int parts = residual_parts(enc, n_tokens, step == CS_STEP_MLP_DOWN);
+    if (parts > 1) {
+      g.splits = parts; g.split_stride = n_tokens * D;
+      if (cs_status st = launch_gemm(EPI_F32, g, nullptr)) return st;
+      const size_t n = strlen(out);
+      snprintf(out + n, capacity - n, ", K in %d parts", parts);
+      return CS_OK;
+    }
+  }
+  return launch_gemm(epi, g, nullptr);
+}
 
 extern "C" {
 
@@ -765,42 +825,11 @@ cs_status cs_encoder_read_timing(cs_encoder* enc, double* total_ms, int64_t* lau
 }
 
 cs_status cs_encoder_step_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity) {
-  if (!enc || !out || capacity < 96 || n_tokens <= 0 || n_tokens > 0x7fffffff)
-    return fail(CS_ERR_INVALID_ARG, "cs_encoder_step_kernel: NULL argument, capacity below 96 or bad token count");
-  const cs_encoder_config& c = enc->cfg;
-  const int64_t D = c.hidden;
-  GemmArgs g = {};
-  g.describe = out;
-  g.M = (int32_t)n_tokens;
-  int epi = EPI_BF16;
-  switch (step) {
-    case CS_STEP_QKV:
-      g.N = (int32_t)(3 * D); g.K = (int32_t)D; g.ldo = 2 * D; g.hidden = (int32_t)D; g.head_dim = c.head_dim; g.ld_vt = round_up(n_tokens, 64);
-      g.M = (int32_t)round_up(n_tokens, 4);
-      epi = EPI_QKV;
-      break;
-    case CS_STEP_PROJ:
-      g.N = (int32_t)D; g.K = (int32_t)D; g.ldo = D;
-      epi = c.arch == CS_ARCH_VIT_CLS ? EPI_RESADD_SCALED_F32 : EPI_RESADD_F32;
-      break;
-    case CS_STEP_MLP_UP:
-      g.N = c.arch == CS_ARCH_VIT ? 2 * enc->I_pad : enc->I_pad; g.K = (int32_t)D; g.ldo = enc->I_pad;
-      epi = c.arch == CS_ARCH_VIT ? EPI_SWIGLU_BF16 : EPI_GELU_BF16;
-      break;
-    case CS_STEP_MLP_DOWN:
-      g.N = (int32_t)D; g.K = enc->I_pad; g.ldo = D;
-      epi = c.arch == CS_ARCH_VIT_CLS ? EPI_RESADD_SCALED_F32 : EPI_RESADD_F32;
-      break;
-    default: return fail(CS_ERR_INVALID_ARG, "cs_encoder_step_kernel: step must be one of the four GEMM steps of a block");
-  }
-  // (an audio tower's residual GEMMs run the instantiation that also writes the plain sums of a folded LayerNorm)
-  if (epi == EPI_RESADD_F32 && c.arch == CS_ARCH_AUDIO && !fold_off() &&
-      (n_tokens > SPLIT_K_MAX_TOKENS || k_parts(n_tokens, D, g.K) == 1))
-    g.s1_out = reinterpret_cast<float*>(uintptr_t(16));   // describe mode: only looked at, never written
-  g.lda = g.ldw = step == CS_STEP_MLP_DOWN ? enc->I_ld : enc->D_ldw;
-  if (epi == EPI_RESADD_SCALED_F32) g.col_scale = enc->ptr<float>(enc->layers[0].ls1);
-  // (batches small enough for split K run other launches; this names the kernel of the unsplit path)
-  return launch_gemm(epi, g, nullptr);
+  return guarded("cs_encoder_step_kernel", [&] { return step_kernel("cs_encoder_step_kernel", enc, step, n_tokens, false, out, capacity); });
+}
+
+cs_status cs_encoder_batch_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity) {
+  return guarded("cs_encoder_batch_kernel", [&] { return step_kernel("cs_encoder_batch_kernel", enc, step, n_tokens, true, out, capacity); });
 }
 
 cs_status cs_encoder_query(const cs_encoder* enc, const int32_t* cu_seqlens, const int32_t* grid_thw, int32_t n_items,
@@ -1092,6 +1121,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
         GemmArgs g = {};
         g.A = xn; g.lda = e->xn_ld; g.W = e->ptr<bf16_t>(L.w1); g.ldw = e->D_ldw; g.bias = e->ptr<float>(L.b1); g.out = big; g.ldo = e->I_ld;
         g.M = (int32_t)N; g.N = 2 * e->I_pad; g.K = (int32_t)D;
+        g.small_batch = w.split_k;
         consume_norm(g);
         if (cs_status st = launch_gemm(EPI_SWIGLU_BF16, g, stream)) return st;
       }

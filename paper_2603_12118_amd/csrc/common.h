@@ -112,6 +112,8 @@ struct GemmArgs {
   // measurement aid: when set (host buffer of at least 96 bytes), launch_gemm writes the name of the kernel
   // instantiation it would run for these arguments there and launches nothing
   char* describe;
+  // nonzero: a launch of a small batch (the encoder's, up to SPLIT_K_MAX_TOKENS tokens), which may take tiles of its own
+  int32_t small_batch;
   // set by the launcher: the residual epilogue stores plainly (through the L2's write-back) instead of write-through
   int32_t plain_stores;
 };
