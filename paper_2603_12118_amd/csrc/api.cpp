@@ -91,6 +91,8 @@ struct cs_encoder {
   size_t w_pe = 0, g_m = 0, w_m1 = 0, b_m1 = 0, w_m2 = 0, b_m2 = 0;          // vit
   size_t w_c1 = 0, b_c1 = 0, w_c2 = 0, b_c2 = 0, g_p = 0, be_p = 0, w_p = 0, b_p = 0, pe_tab = 0;  // audio
   size_t inv_freq = 0, axis = 0;
+  size_t rope_tab = 0, rope_freq = 0;        // (cos, sin) by position (RopeTable), if the sections allow it, and its frequencies
+  int rope_pitch = 0, rope_n_freq = 0, rope_first[3] = {0, 0, 0};
   int pe_positions = 0;
   size_t b_pe = 0, be_m = 0, pos_tab = 0;    // class-token tower: patch-embed bias, projector norm bias, position table
   int n_positions = 0;                       // rows of its position table (1 + patches per tile); row n_positions = class token + row 0
@@ -281,6 +283,8 @@ static int row_pitch(int cols) {
   return bytes % 512 == 0 && (bytes & (bytes - 1)) != 0 ? cols + 64 : cols;
 }
 
+constexpr int ROPE_POSITIONS = 128;   // rows of the rotary table by position (176 bytes each in the 7B-style tower; 22 KB behind a 256 x 256 tile)
+
 static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
   const cs_encoder_config& c = e->cfg;
   const int64_t D = c.hidden, I = c.mlp_dim, dh = c.head_dim;
@@ -406,6 +410,28 @@ static cs_status build_weights(cs_encoder* e, const WeightBook& wb, Arena& A) {
       for (int rep = 0; rep < 2; ++rep)
         for (int64_t k = 0; k < MH; ++k) A.bf(e->w_m2)[(r * 2 + rep) * e->MH_pad + k] = t.bits(r * MH + k);
     e->b_m2 = pack_vector(A, b, H, ident);
+    // rotary angles by position: the QKV epilogue reads them 16 bytes at a time, two pairs of one section
+    const int32_t* sec = c.rope_sections;
+    if (e->rope && !(sec[0] & 1) && !(sec[1] & 1) && !(sec[2] & 1)) {
+      std::vector<float> freq;
+      for (int a = 0, start = 0; a < 3; start += sec[a++]) {
+        int same = 0;
+        while (sec[same] != sec[a]) ++same;
+        if (same == a) {
+          e->rope_first[a] = (int)freq.size() - start;
+          for (int i = 0; i < sec[a]; ++i) freq.push_back((float)pow((double)c.rope_theta, -(double)i / sec[a]));
+        } else {   // the entries of the equal section before it
+          int start_same = 0;
+          for (int b = 0; b < same; ++b) start_same += sec[b];
+          e->rope_first[a] = e->rope_first[same] + start_same - start;
+        }
+      }
+      e->rope_n_freq = (int)freq.size();
+      e->rope_pitch = ((e->rope_n_freq / 2) | 1) * 16;
+      e->rope_freq = A.alloc(freq.size() * 4);
+      std::copy(freq.begin(), freq.end(), A.f32(e->rope_freq));
+      e->rope_tab = A.alloc((size_t)ROPE_POSITIONS * e->rope_pitch + 1024);   // filled on the device at create
+    }
     // rotary: per pair j the axis it follows and its inverse frequency
     e->inv_freq = A.alloc((size_t)std::max(e->half, 1) * 4);
     e->axis = A.alloc((size_t)std::max(e->half, 1) * 4);
@@ -758,6 +784,10 @@ static cs_status encoder_create(const cs_encoder_config* config, const cs_tensor
     hipError_t he = hipGetDevice(&e->device);
     if (he == hipSuccess) he = hipMalloc(reinterpret_cast<void**>(&e->dev), A.host.size());
     if (he == hipSuccess) he = hipMemcpy(e->dev, A.host.data(), A.host.size(), hipMemcpyHostToDevice);
+    if (he == hipSuccess && e->rope_tab) {   // by the device's sine and cosine, as the table by token
+      st = launch_rope_positions(e->ptr<float>(e->rope_freq), e->rope_n_freq, e->rope_pitch, ROPE_POSITIONS, e->dev + e->rope_tab, nullptr);
+      if (st == CS_OK) he = hipStreamSynchronize(nullptr);
+    }
     for (int s = 0; s < 2 && he == hipSuccess; ++s) he = hipEventCreateWithFlags(&e->stage_ev[s], hipEventDisableTiming);
     for (int s = 0; s < 2 && he == hipSuccess; ++s) {
       he = hipHostMalloc(&e->stage[s], STAGE_BYTES_AT_CREATE, hipHostMallocDefault);
@@ -1045,12 +1075,23 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
     return launch_gemm(scale ? EPI_RESADD_SCALED_F32 : EPI_RESADD_F32, g, stream);
   };
 
+  // rotary angles by position where the batch's positions fit behind the QKV tile, by token otherwise
+  RopeTable rope = {};
+  if (e->rope_tab && p.n_positions <= ROPE_POSITIONS) {
+    const int64_t bytes = round_up((int64_t)p.n_positions * e->rope_pitch, 1024);
+    if (bytes <= gemm_rope_room(N, (int32_t)D, c.head_dim, D, e->xn_ld, e->D_ldw)) {
+      rope.tab = e->dev + e->rope_tab; rope.pos = plan + p.off_pos; rope.bytes = (int32_t)bytes; rope.pitch = e->rope_pitch;
+      rope.end[0] = c.rope_sections[0]; rope.end[1] = c.rope_sections[0] + c.rope_sections[1];
+      for (int a = 0; a < 3; ++a) rope.first[a] = e->rope_first[a];
+    }
+  }
+
   // ---- front end: tokens into the fp32 residual stream x [N, D]
   {
     StepTimer tm(e, CS_STEP_FRONT, stream);
     if (vit) {
       if (cs_status st = launch_gather_cast(patches, c.dtype == CS_BF16, c.patch_dim, plan + p.off_src_row, big, e->P_pad, N, stream)) return st;
-      if (e->rope)
+      if (e->rope && !rope.tab)
         if (cs_status st = launch_rope_table(plan + p.off_pos, e->ptr<int32_t>(e->axis), e->ptr<float>(e->inv_freq), e->half, rope_cs, N, stream)) return st;
       if (cs_status st = gemm(EPI_F32, big, e->P_pad, e->w_pe, 0, x, D, N, D, e->P_pad, nullptr)) return st;
     } else if (cls) {
@@ -1089,7 +1130,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       GemmArgs g = {};
       g.A = xn; g.lda = e->xn_ld; g.W = e->ptr<bf16_t>(L.wqkv); g.ldw = e->D_ldw; g.bias = e->ptr<float>(L.bqkv);
       g.out = qk; g.ldo = 2 * D; g.M = (int32_t)N; g.N = (int32_t)(3 * D); g.K = (int32_t)D;
-      g.vt = vt; g.ld_vt = w.ld_vt; g.rope_cs = e->rope ? rope_cs : nullptr;
+      g.vt = vt; g.ld_vt = w.ld_vt; g.rope_cs = e->rope && !rope.tab ? rope_cs : nullptr; g.rope = rope;
       g.hidden = (int32_t)D; g.head_dim = c.head_dim; g.q_scale = q_scale;
       consume_norm(g, L.cqkv, L.dqkv);
       if (cs_status st = launch_gemm(EPI_QKV, g, stream)) return st;

@@ -55,6 +55,19 @@ enum GemmEpilogue {
                              // launch_gemm picks it for EPI_RESADD_F32 with s1_out set
 };
 
+// (cos, sin) of the rotary pairs by position: row p of `pitch` bytes holds the pairs' (cos, sin) at position p, section by
+// section, equal sections once.  Pair j of a token follows axis a, the first with j < end[a] (the last one's end is
+// head_dim/2), and is entry first[a] + j of the row at the token's position along a.
+// (A few KB for a batch instead of head_dim/2 pairs for each of its tokens: no launch in front of the first layer, and nothing
+// to wait for behind the K loop.  One 224 x 224 image 1656 -> 1640 us; 8192 x 3840 x 1280 79.5 -> 78.4, of which the rotation
+// itself is 2.5 and the stores, 63 MB from all CUs at once, 9.)
+struct RopeTable {
+  const unsigned char* tab;   // nullptr: none; readable up to `bytes`
+  const int32_t* pos;         // [M, 3] positions (t, row, col), below 256 along an axis that some pair follows
+  int32_t bytes, pitch;       // bytes to load, a multiple of 1024; the pitch an odd multiple of 16
+  int32_t end[2], first[3];   // even
+};
+
 struct GemmArgs {
   // (what a workgroup needs before its first load comes first, in one 64-byte line of the kernel's arguments and the next)
   const bf16_t* A;   // [M, lda]
@@ -78,7 +91,8 @@ struct GemmArgs {
   // EPI_QKV only
   bf16_t* vt;        // [hidden, ld_vt]
   int64_t ld_vt;
-  const float* rope_cs;    // [M, head_dim/2, 2] = (cos, sin) per rotary pair, or nullptr (no rotary)
+  const float* rope_cs;    // [M, head_dim/2, 2] = (cos, sin) per rotary pair, or nullptr (no rotary, or rope.tab)
+  RopeTable rope;          // rope.tab set: the rotary angles by position instead (no larger than gemm_rope_room says)
   int32_t hidden;    // q columns [0,hidden), k [hidden,2 hidden), v [2 hidden, 3 hidden)
   int32_t head_dim;
   float q_scale;
@@ -112,6 +126,7 @@ struct GemmArgs {
   // measurement aid: when set (host buffer of at least 96 bytes), launch_gemm writes the name of the kernel
   // instantiation it would run for these arguments there and launches nothing
   char* describe;
+  int32_t* rope_room;   // beside describe: the LDS left for a RopeTable by the kernel that a QKV launch runs, bytes
   // nonzero: a launch of a small batch (the encoder's, up to SPLIT_K_MAX_TOKENS tokens), which may take tiles of its own
   int32_t small_batch;
   // set by the launcher: the residual epilogue stores plainly (through the L2's write-back) instead of write-through
@@ -125,6 +140,8 @@ inline bool gemm_rows_addressable(int64_t rows, int64_t pitch) {
   return n <= 0 || (pitch >= 0 && pitch <= (0xFFFFFF00ll / 2 - 64) / n);
 }
 cs_status launch_gemm(int epilogue, const GemmArgs& g, hipStream_t stream);
+// The largest RopeTable::bytes that the QKV launch of M rows takes (0: none).
+int32_t gemm_rope_room(int64_t M, int32_t hidden, int32_t head_dim, int64_t K, int64_t lda, int64_t ldw);
 // Column tiles (= partial sums of squares per row) of a residual GEMM that can fold the next RMSNorm into its
 // epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.  pitch: elements
 // between the rows of its operands.
@@ -251,6 +268,8 @@ cs_status launch_pool_layernorm(const float* x, const float* gain, const float* 
 cs_status launch_gather_cast(const void* src, int src_is_bf16, int32_t src_cols, const int32_t* src_row,
                              bf16_t* dst, int32_t dst_cols, int64_t rows, hipStream_t s);
 // out[n, j] = (cos, sin) of pos[n, axis[j]] * inv_freq[j]
+// rows 0 .. of a RopeTable: entry u of row p = (cos, sin) of p * inv_freq[u]
+cs_status launch_rope_positions(const float* inv_freq, int32_t n_freq, int32_t pitch, int32_t rows, unsigned char* tab, hipStream_t s);
 cs_status launch_rope_table(const int32_t* pos, const int32_t* axis, const float* inv_freq, int32_t half,
                             float* cos_sin_out, int64_t n_tok, hipStream_t s);
 // class-token towers: pos[r] >= 0: x[r] += table[pos[r]];  -1: x[r] = table[class_row];  -2: x[r] = 0

@@ -297,6 +297,21 @@ cs_status launch_rope_table(const int32_t* pos, const int32_t* axis, const float
   return CS_OK;
 }
 
+__global__ __launch_bounds__(256) void rope_positions_kernel(const float* __restrict__ inv_freq, int n_freq, int pitch, int rows, unsigned char* __restrict__ tab) {
+  const int t = (int)blockIdx.x * 256 + threadIdx.x, p = t / n_freq, u = t - p * n_freq;
+  if (p >= rows) return;
+  const float ang = (float)p * inv_freq[u];
+  float sn, cs_;
+  sincosf(ang, &sn, &cs_);
+  *reinterpret_cast<float2*>(tab + (int64_t)p * pitch + u * 8) = make_float2(cs_, sn);
+}
+
+cs_status launch_rope_positions(const float* inv_freq, int32_t n_freq, int32_t pitch, int32_t rows, unsigned char* tab, hipStream_t s) {
+  hipLaunchKernelGGL(rope_positions_kernel, dim3((unsigned)((rows * n_freq + 255) / 256)), dim3(256), 0, s, inv_freq, n_freq, pitch, rows, tab);
+  CS_HIP(hipGetLastError());
+  return CS_OK;
+}
+
 // ---- split-K sums into the residual stream: x += scale * (sum of parts + bias), parts added in index order
 __global__ __launch_bounds__(256) void add_partials_kernel(float* __restrict__ x, const float* __restrict__ parts, int n_parts,
                                                            int64_t stride, const float* __restrict__ bias,

@@ -653,6 +653,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   // (groups q and q + 2 hold the same columns: two distinct column groups per block)
   constexpr int CQ = 2;
   f32x4 bias_r[TN][CQ];
+  [[maybe_unused]] unsigned char* const rope_lds = smem + LDS_ALLOC;   // the rotary table by position, and the rows' positions
+  [[maybe_unused]] uint32_t row_pos = 0;
   [[maybe_unused]] f32x4 scale_r[EPI == EPI_RESADD_SCALED_F32 ? TN : 1][CQ];
   main_loop<BM, BN, WGM, WGN, true, STAGES, FAR>(g, smem, m0, n0, acc, [&] {
 #pragma unroll
@@ -672,12 +674,28 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
       for (int j = 0; j < TN; ++j) fetch_old(0, j, held[0][j]);
     }
     if constexpr (CONSUMES_NORM) gather_scale();
+    if constexpr (EPI == EPI_QKV) {
+      if (g.rope.tab) {
+        for (int u = wave; u < g.rope.bytes >> 10; u += NWAVES)
+          load_lds16<0>(reinterpret_cast<const bf16_t*>(g.rope.tab), (uint32_t)(u * 1024 + lane * 16), rope_lds + u * 1024);
+        int m = m0 + (int)threadIdx.x;
+        m = m < M ? m : M - 1;
+        if (threadIdx.x < BM) row_pos = (g.rope.pos[3 * (int64_t)m] & 255) | (g.rope.pos[3 * (int64_t)m + 1] & 255) << 8 | (g.rope.pos[3 * (int64_t)m + 2] & 255) << 16;
+      }
+    }
   }, [&] {
     if constexpr (HELD_LATE) {
 #pragma unroll
       for (int j = 0; j < TN; ++j) fetch_old(0, j, held[0][j]);
     }
   });
+  if constexpr (EPI == EPI_QKV) {
+    if (g.rope.tab) {
+      if (threadIdx.x < BM) *reinterpret_cast<uint32_t*>(rope_lds + g.rope.bytes + 4 * threadIdx.x) = row_pos;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of the table
+      if (!g.ss_in) __syncthreads();                     // (publish_scale ends with one)
+    }
+  }
   if constexpr (CONSUMES_NORM) publish_scale();
   if constexpr (HOLD_TWO) {
     if (m0 + wm * WM + 32 < M) {   // wave-uniform
@@ -703,13 +721,15 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
     }
   }
 
-  // QKV: the (cos, sin) rows of this tile's BM tokens are staged in LDS (free after the K loop)
+  // QKV.  With the angles by position the table (some 6 - 22 KB) has a place behind everything else that a tile keeps in
+  // LDS and lands under the last K slice; a row of the tile is then one word, its positions.
+  // Otherwise the (cos, sin) rows of this tile's BM tokens are staged in LDS (free after the K loop)
   // with coalesced 16-byte loads; read per lane from global they are 16-byte pieces of 32 different
   // rows per instruction, which cost 18 us of a 110 us launch.  The table sits at the bottom of
   // LDS and the epilogue chunks move to the top.
-  [[maybe_unused]] int rope_stride = 0;
+  [[maybe_unused]] int rope_stride = g.rope.pitch;
   if constexpr (EPI == EPI_QKV) {
-    if (g.rope_cs) {
+    if (!g.rope.tab && g.rope_cs) {
       const int half = g.head_dim >> 1;
       const int cpr = half >> 1;                       // 16-byte pieces per token row (two pairs each)
       const int upr = (cpr + 1) | 1;                   // ... per padded LDS row: odd, so rows spread over the banks
@@ -744,14 +764,23 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   const bool wt = TILE_OUT_BYTES % 128 == 0 && lines_exclusive(g.out, g.ldo * OUT_ES);
   // QKV: byte offset of the first (cos, sin) pair of every 4-column group, once per lane (the
   // divisions by run-time sizes must not be redone for every row block)
-  [[maybe_unused]] int rope_off[TN][CQ];
+  // (and by position: the place of the axis among the row's positions)
+  [[maybe_unused]] int rope_off[TN][CQ], rope_axis[TN][CQ];
+  [[maybe_unused]] const unsigned char* rope_base = g.rope.tab ? rope_lds : smem;
   if constexpr (EPI == EPI_QKV) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int q = 0; q < CQ; ++q) {
         const int n = nw + j * 32 + blk_col(q, lane);
-        rope_off[j][q] = ((((n < g.hidden ? n : n - g.hidden)) % g.head_dim) >> 1) * 8;
+        const int pair = (((n < g.hidden ? n : n - g.hidden)) % g.head_dim) >> 1;
+        rope_off[j][q] = pair * 8;
+        rope_axis[j][q] = 0;
+        if (g.rope.tab) {
+          const int axis = pair < g.rope.end[0] ? 0 : pair < g.rope.end[1] ? 1 : 2;
+          rope_off[j][q] = (pair + (axis == 0 ? g.rope.first[0] : axis == 1 ? g.rope.first[1] : g.rope.first[2])) * 8;
+          rope_axis[j][q] = 8 * axis;
+        }
       }
   }
 #pragma unroll
@@ -771,6 +800,15 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
       if (layer_norm) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) msq[q] = extra_lds[BM + mrow - m0 + blk_row(q, lane)];
+      }
+    }
+    // rotary: the positions of the two rows of a lane, or their numbers in the tile
+    [[maybe_unused]] uint32_t rope_row[2];
+    if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = mrow - m0 + blk_row(2 * h, lane);
+        rope_row[h] = g.rope.tab ? *reinterpret_cast<const uint32_t*>(rope_lds + g.rope.bytes + 4 * r) : (uint32_t)r;
       }
     }
     // ... producer side: sums of squares of the updated rows, gathered by the residual store
@@ -829,8 +867,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
             }
             if constexpr (EPI == EPI_QKV) {
               // q and k columns: rotary on neighbouring columns (2p, 2p+1), both held by this lane
-              if (g.rope_cs) {
-                const f32x4 cs = *reinterpret_cast<const f32x4*>(smem + (mrow - m0 + blk_row(q, lane)) * rope_stride + rope_off[j][q % CQ]);  // cos,sin,cos,sin
+              if (g.rope.tab || g.rope_cs) {
+                const uint32_t at = __umul24((rope_row[q >> 1] >> rope_axis[j][q % CQ]) & 255, rope_stride) + rope_off[j][q % CQ];
+                const f32x4 cs = *reinterpret_cast<const f32x4*>(rope_base + at);  // cos,sin,cos,sin
                 const float r0 = t[0] * cs[0] - t[1] * cs[1], r1 = t[1] * cs[0] + t[0] * cs[1];
                 const float r2 = t[2] * cs[2] - t[3] * cs[3], r3 = t[3] * cs[2] + t[2] * cs[3];
                 t[0] = r0; t[1] = r1; t[2] = r2; t[3] = r3;
@@ -1072,6 +1111,13 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
       tiles += rest;
     }
   }
+  // LDS for a rotary table by position behind the launch's own: what a CU has left, for two workgroups where two fit
+  constexpr int POS_BYTES = 256 * 4, PER_CU = NT == 256 && STAGES == 2 && 2 * LDS <= 160 * 1024 ? 2 : 1;
+  constexpr int ROPE_ROOM = EPI == EPI_QKV && 160 * 1024 / PER_CU >= LDS + POS_BYTES ? (160 * 1024 / PER_CU - LDS - POS_BYTES) / 1024 * 1024 : 0;
+  const int lds = LDS + (g.rope.tab ? g.rope.bytes + POS_BYTES : 0);
+  if (g.rope.tab && (g.rope.bytes > ROPE_ROOM || (g.rope.bytes & 1023) || g.rope.pitch % 32 != 16))
+    return fail(CS_ERR_INVALID_ARG, "gemm: no room for the rotary table");
+  if (g.rope_room) *g.rope_room = ROPE_ROOM;
   if (g.describe) {
     const int n = snprintf(g.describe, 96, "gemm_kernel<%d, %d, %d, %d, %d, %d> 16x16x32%s", BM, BN, WGM, WGN, EPI, TAIL, FAR ? ", far rows" : "");
     if (ga.half_tiles > 0) snprintf(g.describe + n, 96 - n, ", %d half tiles", ga.half_tiles);
@@ -1080,7 +1126,7 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
   // one attribute call per instantiation (two threads that both see `false` repeat a harmless call)
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load(std::memory_order_acquire)) {
-    CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
+    CS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, EPI == EPI_QKV ? 160 * 1024 : LDS));
     attr_set.store(true, std::memory_order_release);
   }
   ga.grid_tiles = whole - ga.half_tiles / 2;
@@ -1095,7 +1141,7 @@ static cs_status launch_one(const GemmArgs& g, hipStream_t stream) {
     static const int mode = [] { const char* v = getenv("CS_GEMM_RESADD_PLAIN"); return v && *v >= '0' && *v <= '1' ? *v - '0' : 2; }();
     ga.plain_stores = mode == 1 || (mode == 2 && BN < 256 && tiles > CHIP_CUS);
   }
-  hipLaunchKernelGGL(kern, dim3(tiles, g.splits > 1 ? g.splits : 1), dim3(NT), LDS, stream, ga);
+  hipLaunchKernelGGL(kern, dim3(tiles, g.splits > 1 ? g.splits : 1), dim3(NT), lds, stream, ga);
   CS_HIP(hipGetLastError());
   return CS_OK;
 }
@@ -1256,6 +1302,17 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   return launch_cfg<128, 128, 2, 2, EPI>(g, stream);
 }
 
+int32_t gemm_rope_room(int64_t M, int32_t hidden, int32_t head_dim, int64_t K, int64_t lda, int64_t ldw) {
+  // (the launcher says so itself)
+  if (M <= 0 || M > 0x7fffffff) return 0;
+  char name[96] = {0};
+  int32_t room = 0;
+  GemmArgs g = {};
+  g.M = (int32_t)M; g.N = 3 * hidden; g.K = (int32_t)K; g.lda = lda; g.ldw = ldw; g.ldo = 2 * (int64_t)hidden; g.hidden = hidden; g.head_dim = head_dim;
+  g.ld_vt = round_up(M, 64); g.describe = name; g.rope_room = &room;
+  return launch_gemm(EPI_QKV, g, nullptr) == CS_OK ? room : 0;
+}
+
 int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, int64_t pitch, bool scaled, bool sums) {
   // ask the launcher itself which tile such a residual GEMM runs on: one partial sum per column tile
   if (M <= 0 || M > 0x7fffffff || N <= 0 || K <= 0 || (N & 3) || (K & 63)) return 0;
@@ -1306,7 +1363,7 @@ cs_status launch_gemm(int epilogue, const GemmArgs& g_in, hipStream_t stream) {
           (reinterpret_cast<uintptr_t>(g.vt) & 7))
         return fail(CS_ERR_UNSUPPORTED, "gemm: qkv epilogue needs M % 4 == 0, hidden % 64 == 0, head_dim % 4 == 0, N == 3 hidden");
       // the (cos, sin) table of a tile's tokens and the epilogue chunks share LDS behind the K loop
-      if (g.rope_cs && g.head_dim > 80) return fail(CS_ERR_UNSUPPORTED, "gemm: rotary epilogue needs head_dim <= 80");
+      if ((g.rope_cs || g.rope.tab) && g.head_dim > 80) return fail(CS_ERR_UNSUPPORTED, "gemm: rotary epilogue needs head_dim <= 80");
       return launch_epi<EPI_QKV>(g, stream);
     default: return fail(CS_ERR_INVALID_ARG, "gemm: unknown epilogue");
   }

@@ -110,6 +110,8 @@ cs_status build_vit_plan(const cs_encoder_config& cfg, const int32_t* cu, const 
   int64_t out_base = 0;
   for (int i = 0; i < n_items; ++i) {
     const int T = grid[3 * i], h = grid[3 * i + 1], w = grid[3 * i + 2];
+    for (int axis = 0; axis < 3; ++axis)
+      if (cfg.rope_sections[axis] > 0) p.n_positions = std::max(p.n_positions, grid[3 * i + axis]);
     const int win = cfg.window > 0 ? cfg.window : std::max(h, w);
     const int item_start = (int)src_row.size();
     for (int t = 0; t < T; ++t)

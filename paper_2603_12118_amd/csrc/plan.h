@@ -17,6 +17,7 @@ struct BatchPlan {
   // vit
   size_t off_src_row = 0;   // [n_tok]   raster patch row of internal token i
   size_t off_pos = 0;       // [n_tok*3] (t,row,col) of internal token i      (audio: [n_tok] frame position)
+  int32_t n_positions = 0;  // one more than the largest position along an axis that the rotary embedding follows
   size_t off_out_row = 0;   // [n_out]   output row of internal merged token j
   size_t off_win_work = 0;  // [n_win_work*4] AttnWork, one window (or 64-query slice of it) each
   size_t off_full_work = 0; // [n_full_work*4] AttnWork, 256-query blocks of whole items
