@@ -1266,20 +1266,31 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
     constexpr bool RES = EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SUMS_F32;
     if (big >= (RES ? 384 : big_tile_min()) && big_ok && !narrow_first) return launch_cfg<256, 256, 2, 4, EPI>(g, stream);
   }
+  // 192 x 256 (eight waves of 96 x 64; two stages, three do not fit) where 128 x 256 need more than a round of the chip and
+  // these make one: K loops of one-round launches go at the pace of a CU's operand loads, 1147 KB at K = 1280 instead of 1311
+  // for 256 x 256, with three quarters of the products behind each slice, and of 256 x 256 there are fewer than 200.  Where
+  // those did not fill 5/8 of a round the launch ran on 128 x 128, two per CU, and N = 5120 or 4096 beyond a round on 256 x 160
+  // or 256 x 128.  A step, before -> with these: 7B-style tower, gate|up of 1280 tokens 3642 -> 3433 us, 1428 3702 -> 3577, QKV of
+  // 2392 5802 -> 5513, of 3072 5670 -> 5546; audio tower, QKV and fc1 of 2200 6219 -> 5247, QKV of 2512 6809 -> 6439;
+  // class-token tower, QKV of 3084 3914 -> 3647.  (256 x 160 in one round are as fast: fc1 of 1600 - 2048 audio tokens within 1 %.)
+  const bool one_192 = !RESADD && big_ok && g.splits <= 1 && !one_round(g.M, g.N, 1, 128, 256) && one_round(g.M, g.N, 1, 192, 256);
   if constexpr (EPI != EPI_QKV && EPI != EPI_SWIGLU_BF16) {
     // narrow outputs (N = hidden = 1280): 256 x 160 tiles, eight waves of 64 x 80 (a wave's third 32-column block
     // half used), give M/256 * 8 workgroups, one round of the chip at M = 8192
     if constexpr (EIGHT_WAVES_OK) {
-      if (g.N % 160 == 0 && tm * (g.N / 160) >= 192) {
+      if (g.N % 160 == 0 && tm * (g.N / 160) >= 192 && !(one_192 && tm * (g.N / 160) > CHIP_CUS)) {
         return launch_cfg<256, 160, 4, 2, EPI>(g, stream);
       }
     }
     // the same for N = 1024: 256 x 128 tiles (eight waves of 64 x 64 leave room for the scaled residual epilogue too)
     // (not for N = 1280, which it would cut into ten column tiles, too many for the next normalisation to fold:
     // 5120 tokens, 9.73 -> 9.35 ms per step on the 128 x 160 tiles below)
-    if (g.N % 128 == 0 && g.N % 160 != 0 && tm * (g.N / 128) >= 192) {
+    if (g.N % 128 == 0 && g.N % 160 != 0 && tm * (g.N / 128) >= 192 && !(one_192 && tm * (g.N / 128) > CHIP_CUS)) {
       return launch_cfg<256, 128, 4, 2, EPI>(g, stream);
     }
+  }
+  if constexpr (!RESADD) {
+    if (one_192) return launch_one<192, 256, 2, 4, EPI, TAIL_NONE, 2>(g, stream);
   }
   if constexpr (EIGHT_WAVES_OK) {
     // 256 x 256 also when it fills one round to 5/8 or more (batches of 2 - 4 images: 2 - 7 % faster than

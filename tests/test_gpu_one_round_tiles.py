@@ -1,0 +1,69 @@
+"""Launches on 192 x 256 tiles: where 128 x 256 need more than one round of the chip and these make one.  Both ends of the range,
+ragged last tiles of either direction, and K loops as short as one slice."""
+import os
+from dataclasses import replace
+
+import pytest
+import torch
+
+from paper_2603_12118_amd import binding as B
+from paper_2603_12118_amd import workloads as wl
+from tests.test_gpu_batch_sizes import check_items, shared_weights
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def runs(cfg, W, n_tokens, **kernels):
+    if any(k.startswith("CS_") for k in os.environ):
+        return
+    enc = B.Encoder(cfg, W)
+    for step, kernel in kernels.items():
+        assert enc.cs_encoder_batch_kernel(B.STEPS[step], n_tokens) == kernel, (step, n_tokens)
+
+
+# 27 column tiles, the last of 256 or 244 columns: 1153 rows (seven tile rows, the last of one row) to 1728 (nine full ones), and
+# one more; 15 column tiles, the last of 4 columns: 3264 rows are seventeen full tile rows and 255 tiles; and fewer
+@pytest.mark.parametrize("M,N,tile", [(1153, 6912, "192, 256"), (1728, 6900, "192, 256"), (1729, 6900, "256, 256"), (2177, 3588, "192, 256"),
+                                      (3264, 3588, "192, 256"), (2561, 3840, "192, 256"), (2560, 3840, "256, 160")])
+@pytest.mark.parametrize("K", [64, 128, 192, 1280])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_linear(M, N, tile, K, dtype):
+    if not any(k.startswith("CS_") for k in os.environ):
+        assert B.cs_linear_kernel(M, N, K, 0, "bf16" if dtype == torch.bfloat16 else "f32").startswith(f"gemm_kernel<{tile}, ")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M * 7 + N * 3 + K)
+    A = torch.randn(M, K, generator=g, device=DEV).bfloat16()
+    W = torch.randn(N, K, generator=g, device=DEV).bfloat16()
+    bias = torch.randn(N, generator=g, device=DEV)
+    C = torch.full((M + 1, N), 7.0, device=DEV, dtype=dtype)
+    B.cs_linear_bf16(A, W, bias, C[:M])
+    ref = A.double() @ W.double().T + bias.double()
+    # bf16 products are exact in fp32; the sums of K unit-variance products and the bias round at 2^-24 relative to the
+    # partial sums, which stay below 8 sqrt(K): K steps at most; a bf16 result rounds once more, 2^-9 of itself
+    bound = K * 2.0 ** -24 * 8 * (K ** 0.5 + 1) + (ref.abs() * 2.0 ** -8 if dtype == torch.bfloat16 else 0)
+    assert ((C[:M].double() - ref).abs() <= bound).all()
+    assert (C[M] == 7.0).all()
+
+
+SWIGLU_192, QKV_192, GELU_192 = (f"gemm_kernel<192, 256, 2, 4, {epi}, 0> 16x16x32" for epi in (5, 6, 2))
+
+
+# gate|up: 1156 tokens (a last tile row of four) and 1728, and 1216 of two images; QKV: 2392 tokens are thirteen tile rows
+@pytest.mark.parametrize("sizes,kernels", [([(476, 476)], dict(mlp_up=SWIGLU_192)), ([(504, 672)], dict(mlp_up=SWIGLU_192)),
+                                           ([(448, 504), (56, 224)], dict(mlp_up=SWIGLU_192)), ([(644, 728)], dict(qkv=QKV_192))])
+def test_images(sizes, kernels):
+    cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,))
+    w = wl.images_workload(f"one_round_{len(sizes)}_{sizes[0][1]}", cfg, sizes, seq_len=2048, data_seed=sizes[0][1])
+    W = shared_weights("vit", w)
+    runs(cfg, W, int(w.cu_seqlens[-1]), **kernels)
+    check_items(f"{int(w.cu_seqlens[-1])} tokens", w, W, sorted({0, len(sizes) - 1}))
+
+
+# fc1 and QKV of two clips (2200 tokens)
+def test_two_clips():
+    cfg = replace(wl.audio_config(2), attn_chunk=200)
+    w = wl.audio_workload("one_round_2x2200", cfg, 2, 2200, seq_len=2048, data_seed=2)
+    W = shared_weights("audio", w)
+    runs(cfg, W, 2200, mlp_up=GELU_192, qkv=QKV_192)
+    check_items("two clips of 1100 tokens", w, W, [1])
