@@ -178,26 +178,17 @@ __host__ __device__ inline bool lines_exclusive(const void* base, int64_t pitch_
   return ((reinterpret_cast<uintptr_t>(base) | static_cast<uintptr_t>(pitch_bytes)) & 127) == 0;
 }
 
-// GELU(z) = z Phi(z) = max(z, 0) - |z| h(|z|) with h(x) = erfc(x / sqrt 2) / 2 as a power of two whose exponent, log2 h, is a
-// polynomial of degree 8 in x on [0, 6.5] (weighted minimax fit, constant term -1 so that h(0) is 1/2; beyond 6.5, where
-// x h is 2.6e-10, x stays there).  The epilogue of the audio and class-token towers' widest GEMM is vector arithmetic, a
-// quarter of a tile's time: 15 issue slots an element where the rational approximation of Abramowitz & Stegun 7.1.26 that was
-// here before took 23.  Error in fp32 against fp64, this / that: rms over N(0, 1) 2.9e-8 / 5.6e-8, largest over
-// |z| <= 12 2.5e-7 / 4.2e-7 (half a unit in the last place of the result alone: 2.4e-7), largest relative to a result of
-// -1 <= z < 0 4.6e-7 / 7.1e-7, of -4 <= z < -3 9e-5 / 4.7e-4, of -6 <= z < -5 2.3e-3 / 3.6e-3.  NaN stays NaN (minimum and maximum
-// are IEEE 754-2019's); -inf gives -0.0, its limit, up to 2.6e-10.
+// GELU(z) = z Phi(z) with erfc from the five-term rational approximation of Abramowitz & Stegun
+// 7.1.26 (absolute error below 1.5e-7): erfc(x) = t (a1 + t (a2 + ... t a5)) exp(-x^2), t = 1 / (1 + p x),
+// x >= 0.  Phi(z) = erfc(|z| / sqrt 2) / 2 for z < 0 and one minus that otherwise, so the negative side
+// has no cancellation.  A dozen instructions with the hardware reciprocal and exp2 where the library
+// erff takes several times that, for every element of the audio MLP's widest epilogue.
 __device__ __forceinline__ float gelu_erf(float z) {
-  const float x = __builtin_elementwise_minimum(__builtin_fabsf(z), 6.5f);
-  float p = -8.181963266906678e-07f;
-  p = __builtin_fmaf(p, x, 1.4059400200494565e-05f);
-  p = __builtin_fmaf(p, x, -6.03367698204238e-05f);
-  p = __builtin_fmaf(p, x, -0.0004545917036011815f);
-  p = __builtin_fmaf(p, x, 0.007496895734220743f);
-  p = __builtin_fmaf(p, x, -0.052809398621320724f);
-  p = __builtin_fmaf(p, x, -0.45910075306892395f);
-  p = __builtin_fmaf(p, x, -1.1511179208755493f);
-  p = __builtin_fmaf(p, x, -1.0f);
-  return __builtin_fmaf(-x, __builtin_amdgcn_exp2f(p), __builtin_elementwise_maximum(z, 0.0f));
+  const float x = fabsf(z) * 0.70710678118654752f;
+  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
+  const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
+  const float half_erfc = 0.5f * poly * __builtin_amdgcn_exp2f(-1.4426950408889634f * x * x);
+  return z * (z < 0.f ? half_erfc : 1.0f - half_erfc);
 }
 
 // pixels -> patch rows (elementwise.hip): up to PATCHIFY_ITEMS items [F,3,H,W] per launch, described by value

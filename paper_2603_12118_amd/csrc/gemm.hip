@@ -849,17 +849,11 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
             f32x4 t;
 #pragma unroll
             for (int e = 0; e < 4; ++e) t[e] = acc[i][j][q][e];
-            if constexpr (EPI == EPI_GELU_BF16) {   // (two fused operations an element; vector arithmetic bounds this epilogue)
-              f32x4 b = bias_r[j][q % CQ];
-              if (layer_norm) b -= msq[q] * *reinterpret_cast<const f32x4*>(extra_lds + 2 * BM + (n - n0));
-              t = t * rsq[q] + b;
-            } else {
-              if constexpr (CONSUMES_NORM && EPI != EPI_SWIGLU_BF16) t *= rsq[q];
-              if constexpr (CONSUMES_LAYERNORM) {
-                if (layer_norm) t -= msq[q] * *reinterpret_cast<const f32x4*>(extra_lds + 2 * BM + (n - n0));
-              }
-              t += bias_r[j][q % CQ];
+            if constexpr (CONSUMES_NORM && EPI != EPI_SWIGLU_BF16) t *= rsq[q];
+            if constexpr (CONSUMES_LAYERNORM) {
+              if (layer_norm) t -= msq[q] * *reinterpret_cast<const f32x4*>(extra_lds + 2 * BM + (n - n0));
             }
+            t += bias_r[j][q % CQ];
             if constexpr (EPI == EPI_RESADD_SCALED_F32) t *= scale_r[j][q % CQ];
             if constexpr (EPI == EPI_GELU_BF16 || EPI == EPI_GELU_F32 || EPI == EPI_GELU_SPLIT) {
 #pragma unroll
