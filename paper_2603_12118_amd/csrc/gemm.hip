@@ -1299,6 +1299,13 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   // 1 takes four waves at any size.
   if constexpr (EPI == EPI_RESADD_F32 || EPI == EPI_RESADD_SUMS_F32) {
     if (g.N % 160 == 0 && g.splits <= 1 && small_resadd_pair() > 0) {
+      // 64 x 160, four waves of 32 x 80 and three K slices in flight, from half a chip of them to a whole one (N = 1280: 961 -
+      // 2048 rows): such a launch goes at the pace of its operand loads, of which a CU then pulls 573 KB at K = 1280 instead of
+      // 737, and twice as many CUs work.  A step of the 7B-style tower, out projections on 64 x 160 against 128 x 160: 2048 tokens
+      // 4172 / 4297 us (1520 3791 / 3921 and 1760 4052 / 4198, unsplit for the measurement).
+      // (Fewer of them lie in batches whose residual GEMMs run split over K, or in narrow towers.)
+      if (one_round(g.M, g.N, 1, 64, 160) && (int64_t)((g.M + 63) / 64) * (g.N / 160) >= CHIP_CUS / 2)
+        return launch_one<64, 160, 2, 2, EPI, TAIL_NONE, 4>(g, stream);
       const int64_t tiles = ((g.M + 127) / 128) * (g.N / 160);
       if (small_resadd_pair() == 2 && tiles <= CHIP_CUS) return launch_cfg<128, 160, 4, 2, EPI>(g, stream);
       return launch_cfg<128, 160, 2, 2, EPI>(g, stream);

@@ -1,5 +1,6 @@
-"""Launches on 192 x 256 tiles: where 128 x 256 need more than one round of the chip and these make one.  Both ends of the range,
-ragged last tiles of either direction, and K loops as short as one slice."""
+"""Launches that the chip holds in one round: 192 x 256 tiles, where 128 x 256 need more than one, and residual GEMMs on 64 x
+160 tiles.  Both ends of each range, ragged last tiles of either
+direction, and K loops as short as one slice."""
 import os
 from dataclasses import replace
 
@@ -47,11 +48,14 @@ def test_linear(M, N, tile, K, dtype):
 
 
 SWIGLU_192, QKV_192, GELU_192 = (f"gemm_kernel<192, 256, 2, 4, {epi}, 0> 16x16x32" for epi in (5, 6, 2))
+PROJ_64 = "gemm_kernel<64, 160, 2, 2, 4, 0> 16x16x32"
 
 
-# gate|up: 1156 tokens (a last tile row of four) and 1728, and 1216 of two images; QKV: 2392 tokens are thirteen tile rows
+# gate|up: 1156 tokens (a last tile row of four) and 1728; the out projection: 1924 tokens, not
+# split any more, and 2048, the most that 64 x 160 tiles take; QKV: 2392 tokens are thirteen tile rows of 192 x 256
 @pytest.mark.parametrize("sizes,kernels", [([(476, 476)], dict(mlp_up=SWIGLU_192)), ([(504, 672)], dict(mlp_up=SWIGLU_192)),
-                                           ([(448, 504), (56, 224)], dict(mlp_up=SWIGLU_192)), ([(644, 728)], dict(qkv=QKV_192))])
+                                           ([(448, 840), (28, 28)], dict(proj=PROJ_64)),
+                                           ([(448, 896)], dict(proj=PROJ_64)), ([(644, 728)], dict(qkv=QKV_192))])
 def test_images(sizes, kernels):
     cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,))
     w = wl.images_workload(f"one_round_{len(sizes)}_{sizes[0][1]}", cfg, sizes, seq_len=2048, data_seed=sizes[0][1])
