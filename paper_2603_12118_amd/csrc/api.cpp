@@ -512,6 +512,30 @@ static int k_parts(int64_t M, int64_t N, int64_t K) {
   return best;
 }
 
+// ... and for the residual GEMMs of the class-token tower the number that costs least.  A split launch is one round of the chip and
+// takes as long as a CU takes for its operands (1.54 ns for the 128 bytes of a row or column of the tile in a K slice, 0.75 us
+// more for 128 x 160 tiles and 0.5 for 128 x 256), and every part's sums are written and read back (0.89 ps an element).  Fitted over 46
+// shapes (64 - 2056 rows of N = 1280 or 1024, K = 1280 - 5120, two to four parts each), where it picks the fastest or one within
+// 0.2 us but for three, 1.0 us a launch behind at most.  A step of one tile 2112 -> 2050 us, of two 3292 -> 3019.
+// The vision and audio towers keep the parts above, although these would save them 1 - 9 % up to 2048 tokens: other parts
+// are other orders of the sums, hence another draw of the bf16 rounding in every layer, and where an item's rows fill less than
+// 4 % of a sequence that is more than 0.09 of the sequence's rms in single elements, the bound for two evaluations.
+static int cheapest_parts(int64_t M, int64_t N, int64_t K) {
+  const int64_t kt = K / 64;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int s = 2; s <= MAX_K_PARTS && kt / s >= 4; ++s) {
+    int32_t bm, bn;
+    if (!gemm_split_tile(M, N, s, &bm, &bn)) continue;
+    const int64_t cost = 1540 * (bm + bn) * ((kt + s - 1) / s) + 89 * s * M * N / 100 + (bn == 160 ? 750000 : bn > 160 ? 500000 : 0);   // ps
+    if (cost < least) {
+      least = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
 // Measurement switch: CS_NO_NORM_FOLD=1 in the environment keeps every RMSNorm a kernel of its own (read once).
 static bool fold_off() {
   static const bool off = [] {
@@ -527,10 +551,11 @@ static int residual_parts(const cs_encoder* e, int64_t N, bool down) {
   const cs_encoder_config& c = e->cfg;
   const int64_t D = c.hidden;
   const int parts = k_parts(N, D, down ? e->I_pad : D);
+  if (parts > 1 && c.arch == CS_ARCH_VIT_CLS) return cheapest_parts(N, D, down ? e->I_pad : D);
   // The out projection's short K loop is not split once 128 x 160 tiles fill half the chip: unsplit, the launch
   // folds the next RMSNorm into its epilogue, which saves more than the split gains.  us a layer, split -> unsplit: 64
-  // workgroups (1024 tokens) +6.1, 96 (1520) +1.5, 112 (1680) -5.2, 128 (1936, 2024) -7.9 and -7.1, 136 -0.3.  (A line
-  // at 104, and the same for the LayerNorm towers, which always split: 96 +2.3, 104 -2.9, 128 -8.8, is not yet drawn.)
+  // workgroups (1024 tokens) +6.1, 96 (1520) +1.5, 112 (1680) -5.2, 128 (1936, 2024) -7.9 and -7.1, 136 -0.3.  (On
+  // 64 x 160 tiles it would pay from 1412 tokens on: 1428 3574 us a step in the best number of parts -> 3555, 1760 4024 -> 3972.)
   if (!down && parts > 1 && c.arch == CS_ARCH_VIT && D % 160 == 0 && ((N + 127) / 128) * (D / 160) >= 128 && !fold_off() &&
       gemm_norm_fold_parts(N, D, D, e->D_ldw, false, false) > 0)
     return 1;

@@ -145,6 +145,8 @@ int32_t gemm_rope_room(int64_t M, int32_t hidden, int32_t head_dim, int64_t K, i
 // Column tiles (= partial sums of squares per row) of a residual GEMM that can fold the next RMSNorm into its
 // epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.  pitch: elements
 // between the rows of its operands.
+// The tile of a launch of partial sums in `parts` parts over K, where one round of the chip holds it; false where none does.
+bool gemm_split_tile(int64_t M, int64_t N, int64_t parts, int32_t* bm, int32_t* bn);
 int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, int64_t pitch, bool scaled = false, bool sums = false);
 
 // ---- write-through global stores -----------------------------------------------------------

@@ -1211,6 +1211,15 @@ static int small_tile(int64_t M, int64_t N, int64_t parts, int first) {
   return t;
 }
 
+// (as launch_epi takes it for EPI_F32)
+bool gemm_split_tile(int64_t M, int64_t N, int64_t parts, int32_t* bm, int32_t* bn) {
+  const int t = small_tile(M, N, parts, TILE_64);
+  if (t == N_SMALL_TILES) return false;
+  *bm = SMALL_TILES[t].bm;
+  *bn = t == TILE_128x256 && N % 32 == 0 && one_round(M, N, parts, 128, 160) ? 160 : SMALL_TILES[t].bn;
+  return true;
+}
+
 template <int EPI>
 static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   // rows whose offsets inside a tile do not fit 32 bits

@@ -1,5 +1,5 @@
-"""Launches that the chip holds in one round: 192 x 256 tiles, where 128 x 256 need more than one, and residual GEMMs on 64 x
-160 tiles.  Both ends of each range, ragged last tiles of either
+"""Launches that the chip holds in one round: 192 x 256 tiles, where 128 x 256 need more than one, residual GEMMs on 64 x 160
+tiles, and the class-token tower's in parts over K.  Both ends of each range, ragged last tiles of either
 direction, and K loops as short as one slice."""
 import os
 from dataclasses import replace
@@ -71,3 +71,15 @@ def test_two_clips():
     W = shared_weights("audio", w)
     runs(cfg, W, 2200, mlp_up=GELU_192, qkv=QKV_192)
     check_items("two clips of 1100 tokens", w, W, [1])
+
+
+# 16 slices in two parts and 64 in three (22, 21 and 21) or two
+@pytest.mark.parametrize("tiles,proj,down", [(1, 2, 3), (2, 2, 2)])
+def test_class_token_tiles(tiles, proj, down):
+    w = wl.images_workload(f"one_round_tiles_{tiles}", wl.vit_cls_config(2), [(448, 448)] * tiles, seq_len=2048, data_seed=tiles)
+    W = shared_weights("cls", w)
+    if not any(k.startswith("CS_") for k in os.environ):
+        enc = B.Encoder(w.cfg, W)
+        for step, parts in (("proj", proj), ("mlp_down", down)):
+            assert enc.cs_encoder_batch_kernel(B.STEPS[step], 1028 * tiles).endswith(f", K in {parts} parts")
+    check_items(f"{tiles} tiles", w, W, [tiles - 1])
