@@ -709,7 +709,7 @@ static cs_status step_kernel(const char* who, const cs_encoder* enc, int32_t ste
   const cs_encoder_config& c = enc->cfg;
   const int64_t D = c.hidden;
   GemmArgs g = {};
-  g.small_batch = as_run && n_tokens <= SPLIT_K_MAX_TOKENS;
+  g.small_batch = as_run && (n_tokens <= SPLIT_K_MAX_TOKENS || step == CS_STEP_PROJ || step == CS_STEP_MLP_DOWN);
   g.describe = out;
   g.M = (int32_t)n_tokens;
   int epi = EPI_BF16;
@@ -1091,6 +1091,7 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
       return CS_OK;
     }
     g.bias = e->ptr<float>(bias); g.out = x; g.K = (int32_t)K;
+    g.small_batch = 1;
     if (scale) g.col_scale = e->ptr<float>(scale);
     if (next_gain && fold_parts > 0) {
       g.norm_gain = e->ptr<float>(next_gain); g.xg = xn; g.ld_xg = e->xn_ld; g.ss_out = ss; g.ss_stride = w.ss_stride;

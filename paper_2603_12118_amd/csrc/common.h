@@ -127,7 +127,7 @@ struct GemmArgs {
   // instantiation it would run for these arguments there and launches nothing
   char* describe;
   int32_t* rope_room;   // beside describe: the LDS left for a RopeTable by the kernel that a QKV launch runs, bytes
-  // nonzero: a launch of a small batch (the encoder's, up to SPLIT_K_MAX_TOKENS tokens), which may take tiles of its own
+  // nonzero: a launch of the encoder's that may take tiles of its own (gate|up up to SPLIT_K_MAX_TOKENS tokens, the residual GEMMs)
   int32_t small_batch;
   // set by the launcher: the residual epilogue stores plainly (through the L2's write-back) instead of write-through
   int32_t plain_stores;

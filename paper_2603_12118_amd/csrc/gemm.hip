@@ -1316,6 +1316,12 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
       if (one_round(g.M, g.N, 1, 64, 160) && (int64_t)((g.M + 63) / 64) * (g.N / 160) >= CHIP_CUS / 2)
         return launch_one<64, 160, 2, 2, EPI, TAIL_NONE, 4>(g, stream);
       const int64_t tiles = ((g.M + 127) / 128) * (g.N / 160);
+      // Beyond one round of 128 x 160, up to where 256 x 160 fill the chip (N = 1280: 4097 - 5888 rows): one round of 192 x 160, six
+      // waves of 64 x 80, three stages, 901 KB of operands a CU at K = 1280.  As 128 x 160, two workgroups on some CUs and one on
+      // others, those with two pulled 1475 KB.  A step of the 7B-style tower: 4100 tokens 7064 -> 6787 us, 4232 7571 -> 7335, 5120
+      // 8632 -> 8420, 5888 8987 -> 8732; of the audio tower: 4500 9519 -> 9084, 5128 9165 -> 8780.
+      if (g.small_batch && tiles > CHIP_CUS && one_round(g.M, g.N, 1, 192, 160))
+        return launch_one<192, 160, 3, 2, EPI, TAIL_NONE, 3>(g, stream);
       if (small_resadd_pair() == 2 && tiles <= CHIP_CUS) return launch_cfg<128, 160, 4, 2, EPI>(g, stream);
       return launch_cfg<128, 160, 2, 2, EPI>(g, stream);
     }

@@ -64,6 +64,36 @@ def test_images(sizes, kernels):
     check_items(f"{int(w.cu_seqlens[-1])} tokens", w, W, sorted({0, len(sizes) - 1}))
 
 
+# residual GEMMs on 192 x 160 tiles, six waves: 4100 tokens (the last tile row of 68), 5760, 30 full tile rows,
+# and clips of 5140
+RES_192 = "gemm_kernel<192, 160, 3, 2, 4, 0> 16x16x32"
+
+
+@pytest.mark.parametrize("sizes", [[(448, 448)] * 4 + [(28, 28)], [(448, 448)] * 5 + [(448, 280)]])
+def test_images_on_192_rows(sizes):
+    cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,))
+    w = wl.images_workload(f"rows_192_{len(sizes)}_{sizes[-1][0]}", cfg, sizes, seq_len=2048, data_seed=len(sizes))
+    W = shared_weights("vit", w)
+    runs(cfg, W, int(w.cu_seqlens[-1]), proj=RES_192, mlp_down=RES_192)
+    check_items(f"{int(w.cu_seqlens[-1])} tokens", w, W, [0, len(sizes) - 1])
+
+
+def test_clips_on_192_rows():
+    w = wl.audio_workload("rows_192", replace(wl.audio_config(2), attn_chunk=100), 5, 2048 + 8, seq_len=2048, data_seed=6)
+    W = shared_weights("audio", w)
+    runs(w.cfg, W, 5140, proj=RES_192.replace("4, 0>", "9, 0>"), mlp_down=RES_192.replace("4, 0>", "9, 0>"))
+    check_items("five clips of 1028 tokens", w, W, [0, 4])
+
+
+# down projections of one to ten slices: K loops about as long as the pipeline of three
+@pytest.mark.parametrize("mlp_dim", [64, 128, 192, 640])
+def test_short_k_on_192_rows(mlp_dim):
+    cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(), hidden=1280, n_heads=16, mlp_dim=mlp_dim, merger_hidden=512, out_hidden=512)
+    w = wl.images_workload(f"short_192_{mlp_dim}", cfg, [(448, 448)] * 4 + [(28, 56)], seq_len=2048, data_seed=mlp_dim)
+    runs(cfg, w.weights, int(w.cu_seqlens[-1]), mlp_down=RES_192)
+    check_items(f"mlp {mlp_dim}", w, w.weights, [0, 4])
+
+
 # fc1 and QKV of two clips (2200 tokens)
 def test_two_clips():
     cfg = replace(wl.audio_config(2), attn_chunk=200)
