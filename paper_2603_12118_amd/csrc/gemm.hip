@@ -654,7 +654,7 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   constexpr int CQ = 2;
   f32x4 bias_r[TN][CQ];
   [[maybe_unused]] unsigned char* const rope_lds = smem + LDS_ALLOC;   // the rotary table by position, and the rows' positions
-  [[maybe_unused]] uint32_t row_pos = 0;
+  [[maybe_unused]] int32_t row_pos[3] = {0, 0, 0};   // of row m0 + threadIdx.x, as loaded: to pack them here would wait for every load
   [[maybe_unused]] f32x4 scale_r[EPI == EPI_RESADD_SCALED_F32 ? TN : 1][CQ];
   main_loop<BM, BN, WGM, WGN, true, STAGES, FAR>(g, smem, m0, n0, acc, [&] {
 #pragma unroll
@@ -680,7 +680,8 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
           load_lds16<0>(reinterpret_cast<const bf16_t*>(g.rope.tab), (uint32_t)(u * 1024 + lane * 16), rope_lds + u * 1024);
         int m = m0 + (int)threadIdx.x;
         m = m < M ? m : M - 1;
-        if (threadIdx.x < BM) row_pos = (g.rope.pos[3 * (int64_t)m] & 255) | (g.rope.pos[3 * (int64_t)m + 1] & 255) << 8 | (g.rope.pos[3 * (int64_t)m + 2] & 255) << 16;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) row_pos[a] = g.rope.pos[3 * (int64_t)m + a];
       }
     }
   }, [&] {
@@ -691,7 +692,9 @@ __device__ __forceinline__ void tile_body(const GemmArgs& g, unsigned char* smem
   });
   if constexpr (EPI == EPI_QKV) {
     if (g.rope.tab) {
-      if (threadIdx.x < BM) *reinterpret_cast<uint32_t*>(rope_lds + g.rope.bytes + 4 * threadIdx.x) = row_pos;
+      asm volatile("" : "+v"(row_pos[0]), "+v"(row_pos[1]), "+v"(row_pos[2]));   // (keeps the packing from moving up to the loads)
+      if (threadIdx.x < BM)
+        *reinterpret_cast<uint32_t*>(rope_lds + g.rope.bytes + 4 * threadIdx.x) = (row_pos[0] & 255) | (row_pos[1] & 255) << 8 | (row_pos[2] & 255) << 16;
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of the table
       if (!g.ss_in) __syncthreads();                     // (publish_scale ends with one)
     }

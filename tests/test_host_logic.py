@@ -4,6 +4,8 @@ with brute-force enumeration written here.  No compute call is made (no GPU need
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 from dataclasses import replace
 
 import numpy as np
@@ -341,6 +343,32 @@ def test_no_kernel_uses_scratch_memory():
     found = re.findall(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_Z\w+)\xbb\.private_segment_fixed_size(.)", blob, re.S)
     assert len(found) == blob.count(b".private_segment_fixed_size") > 0
     assert [name.decode() for name, size in found if size != b"\0"] == []
+
+
+def test_qkv_tiles_run_their_last_slice_over_the_loads_of_the_epilogue(tmp_path):
+    """The rotary table, the rows' positions, the bias and the partial sums are requested ahead of the last K slice: in the
+    built QKV kernels no wait for loads stands between the positions' load and the slice's products."""
+    objdump = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin:" + os.environ.get("PATH", ""))
+    if objdump is None:
+        pytest.skip("no disassembler")
+    blob, at, seen = open(B.LIB_PATH, "rb").read(), -1, 0
+    while (at := blob.find(b"__CLANG_OFFLOAD_BUNDLE__", at + 1)) >= 0:
+        entry = at + 32
+        for _ in range(int.from_bytes(blob[at + 24:at + 32], "little")):
+            offset, size, length = (int.from_bytes(blob[entry + 8 * i:entry + 8 * i + 8], "little") for i in range(3))
+            entry += 24 + length
+            code = blob[at + offset:at + offset + size]
+            kernels = sorted(set(re.findall(rb"_ZN2cs11gemm_kernelI(?:Li\d+E){4}Li6E\w+", code)))
+            if not kernels:
+                continue
+            (tmp_path / "code").write_bytes(code)
+            text = subprocess.run([objdump, "-d", "--disassemble-symbols=" + b",".join(kernels).decode(), str(tmp_path / "code")],
+                                  capture_output=True, text=True, check=True).stdout
+            for part in text.split("\tglobal_load_dwordx3 ")[1:]:
+                ahead = part.split("\tv_mfma", 8)   # (up to the eighth product)
+                assert len(ahead) == 9 and "vmcnt" not in "".join(ahead[:8]), part[:2000]
+                seen += 1
+    assert seen >= 11   # one a tile body
 
 
 # ---- 256-query items as workgroups of 64 queries
