@@ -419,8 +419,8 @@ cs_status cs_encoder_time_step(cs_encoder* enc, int32_t step);
  * MFMA shape) that `step` (CS_STEP_QKV, CS_STEP_PROJ, CS_STEP_MLP_UP or CS_STEP_MLP_DOWN) runs for a batch of
  * n_tokens tokens when it is not split over K, written as a C string to `out` (capacity >= 96). */
 cs_status cs_encoder_step_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity);
-/* The same for what a batch of n_tokens tokens runs in fact: with the tiles that gate|up of up to 2560 tokens and the
- * residual GEMMs have for themselves, and ", K in <n> parts" behind the name of a GEMM that is split over K. */
+/* The same for what a batch of n_tokens tokens runs in fact: a GEMM that is split over K by the name of its launch, with
+ * ", K in <n> parts" behind it. */
 cs_status cs_encoder_batch_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity);
 /* An event pair costs the stream about 5 us of idle time on either side of the launch it brackets
  * (measured: 0.36 ms per step when all 32 launches of one step are timed).  cs_encoder_time_every(enc, n)

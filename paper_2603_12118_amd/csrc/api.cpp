@@ -702,14 +702,14 @@ constexpr size_t STAGE_BYTES_AT_CREATE = (size_t)1 << 20;
 
 }  // namespace cs
 
-// as_run: with the parts over K and the tiles that small batches have for themselves
+// as_run: with the parts over K
 static cs_status step_kernel(const char* who, const cs_encoder* enc, int32_t step, int64_t n_tokens, bool as_run, char* out, size_t capacity) {
   if (!enc || !out || capacity < 96 || n_tokens <= 0 || n_tokens > 0x7fffffff)
     return fail(CS_ERR_INVALID_ARG, std::string(who) + ": NULL argument, capacity below 96 or bad token count");
   const cs_encoder_config& c = enc->cfg;
   const int64_t D = c.hidden;
   GemmArgs g = {};
-  g.small_batch = as_run && (n_tokens <= SPLIT_K_MAX_TOKENS || step == CS_STEP_PROJ || step == CS_STEP_MLP_DOWN);
+  g.small_batch = n_tokens <= SPLIT_K_MAX_TOKENS || step == CS_STEP_PROJ || step == CS_STEP_MLP_DOWN;   // (as the encode sets it)
   g.describe = out;
   g.M = (int32_t)n_tokens;
   int epi = EPI_BF16;

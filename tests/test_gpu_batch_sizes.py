@@ -89,17 +89,25 @@ def test_tile_choice_by_batch_size():
     w = wl.images_workload("tiles_by_size", replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,)),
                            [(56, 56)], seq_len=8192, data_seed=1)
     enc = B.Encoder(w.cfg, shared_weights("vit", w))
-    name = lambda step, n: enc.cs_encoder_step_kernel(B.STEPS[step], n).split(">")[0] + ">"
-    # gate|up: 128 x 128 below a round of 256 x 256 tiles (short of 5/8 of it), 256 x 256 from 160 tiles on, with half
+
+    def name(step, n):
+        run = enc.cs_encoder_batch_kernel(B.STEPS[step], n)
+        # the same without its parts over K, of which these have none
+        assert enc.cs_encoder_step_kernel(B.STEPS[step], n) == run, (step, n)
+        return run.split(">")[0] + ">"
+
+    # gate|up: 128 x 256 while they make one round, 192 x 256 where only these do, 256 x 256 from there on, with half
     # tiles in a last round that is at most half full
-    assert name("mlp_up", 1024) == "gemm_kernel<128, 128, 2, 2, 5, 0>"
+    assert name("mlp_up", 1024) == "gemm_kernel<128, 256, 2, 4, 5, 0>"
+    assert name("mlp_up", 1280) == "gemm_kernel<192, 256, 2, 4, 5, 0>"
     assert name("mlp_up", 2048) == "gemm_kernel<256, 256, 2, 4, 5, 0>"      # 216 tiles: one round
     assert name("mlp_up", 3072) == "gemm_kernel<256, 256, 2, 4, 5, 2>"      # 324 tiles: a round and 68
     assert name("mlp_up", 8192) == "gemm_kernel<256, 256, 2, 4, 5, 2>"      # 864 tiles: three rounds and 96
-    # residual GEMMs with N = 1280: 128 x 160 (eight waves up to one tile per CU, then two four-wave workgroups per
-    # CU), 256 x 160 from 192 of those on, 256 x 256 from a round and a half on
+    # residual GEMMs with N = 1280: 64 x 160 and 128 x 160 (eight waves) up to one tile per CU, then one round of 192 x 160,
+    # 256 x 160 from 192 of those on, 256 x 256 from a round and a half on
+    assert name("proj", 2048) == "gemm_kernel<64, 160, 2, 2, 4, 0>"
     assert name("proj", 3072) == "gemm_kernel<128, 160, 4, 2, 4, 0>"
-    assert name("proj", 5120) == "gemm_kernel<128, 160, 2, 2, 4, 0>"
+    assert name("proj", 5120) == "gemm_kernel<192, 160, 3, 2, 4, 0>"
     assert name("proj", 8192) == "gemm_kernel<256, 160, 4, 2, 4, 0>"
     assert name("mlp_down", 8192) == "gemm_kernel<256, 160, 4, 2, 4, 0>"
     assert name("proj", 24576) == "gemm_kernel<256, 256, 2, 4, 4, 0>"        # 480 tiles: a round and 224
