@@ -420,7 +420,8 @@ cs_status cs_encoder_time_step(cs_encoder* enc, int32_t step);
  * n_tokens tokens when it is not split over K, written as a C string to `out` (capacity >= 96). */
 cs_status cs_encoder_step_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity);
 /* The same for what a batch of n_tokens tokens runs in fact: a GEMM that is split over K by the name of its launch, with
- * ", K in <n> parts" behind it. */
+ * ", K in <n> parts" behind it; QKV with a rotary embedding with ", <n> positions", those up to which it takes the angles by
+ * position (larger items: by token). */
 cs_status cs_encoder_batch_kernel(const cs_encoder* enc, int32_t step, int64_t n_tokens, char* out, size_t capacity);
 /* An event pair costs the stream about 5 us of idle time on either side of the launch it brackets
  * (measured: 0.36 ms per step when all 32 launches of one step are timed).  cs_encoder_time_every(enc, n)

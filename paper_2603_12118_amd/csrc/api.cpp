@@ -562,6 +562,14 @@ static int residual_parts(const cs_encoder* e, int64_t N, bool down) {
   return parts;
 }
 
+// Positions along an axis up to which a batch of N tokens takes its rotary angles by position: those that fit behind the tile
+// that its QKV launch runs.  0: by token (no rotary embedding, or sections that do not allow the table).
+static int64_t rope_positions(const cs_encoder* e, int64_t N) {
+  if (!e->rope_tab) return 0;
+  const int64_t room = gemm_rope_room(N, e->cfg.hidden, e->cfg.head_dim, e->cfg.hidden, e->xn_ld, e->D_ldw);   // whole KB
+  return std::min<int64_t>(ROPE_POSITIONS, room / e->rope_pitch);
+}
+
 static Workspace layout_workspace(const cs_encoder* e, const BatchPlan& p) {
   const cs_encoder_config& c = e->cfg;
   const int64_t N = p.n_tok, D = c.hidden;
@@ -702,7 +710,7 @@ constexpr size_t STAGE_BYTES_AT_CREATE = (size_t)1 << 20;
 
 }  // namespace cs
 
-// as_run: with the parts over K
+// as_run: with the parts over K and the positions of a rotary table
 static cs_status step_kernel(const char* who, const cs_encoder* enc, int32_t step, int64_t n_tokens, bool as_run, char* out, size_t capacity) {
   if (!enc || !out || capacity < 96 || n_tokens <= 0 || n_tokens > 0x7fffffff)
     return fail(CS_ERR_INVALID_ARG, std::string(who) + ": NULL argument, capacity below 96 or bad token count");
@@ -749,7 +757,12 @@ static cs_status step_kernel(const char* who, const cs_encoder* enc, int32_t ste
       return CS_OK;
     }
   }
-  return launch_gemm(epi, g, nullptr);
+  if (cs_status st = launch_gemm(epi, g, nullptr)) return st;
+  if (as_run && step == CS_STEP_QKV && enc->rope) {
+    const size_t n = strlen(out);
+    snprintf(out + n, capacity - n, ", %d positions", (int)rope_positions(enc, g.M));
+  }
+  return CS_OK;
 }
 
 extern "C" {
@@ -1103,13 +1116,11 @@ static cs_status encode_impl(cs_encoder* e, const void* patches, const int32_t* 
 
   // rotary angles by position where the batch's positions fit behind the QKV tile, by token otherwise
   RopeTable rope = {};
-  if (e->rope_tab && p.n_positions <= ROPE_POSITIONS) {
-    const int64_t bytes = round_up((int64_t)p.n_positions * e->rope_pitch, 1024);
-    if (bytes <= gemm_rope_room(N, (int32_t)D, c.head_dim, D, e->xn_ld, e->D_ldw)) {
-      rope.tab = e->dev + e->rope_tab; rope.pos = plan + p.off_pos; rope.bytes = (int32_t)bytes; rope.pitch = e->rope_pitch;
-      rope.end[0] = c.rope_sections[0]; rope.end[1] = c.rope_sections[0] + c.rope_sections[1];
-      for (int a = 0; a < 3; ++a) rope.first[a] = e->rope_first[a];
-    }
+  if (e->rope_tab && p.n_positions <= rope_positions(e, N)) {
+    rope.tab = e->dev + e->rope_tab; rope.pos = plan + p.off_pos; rope.pitch = e->rope_pitch;
+    rope.bytes = (int32_t)round_up((int64_t)p.n_positions * e->rope_pitch, 1024);
+    rope.end[0] = c.rope_sections[0]; rope.end[1] = c.rope_sections[0] + c.rope_sections[1];
+    for (int a = 0; a < 3; ++a) rope.first[a] = e->rope_first[a];
   }
 
   // ---- front end: tokens into the fp32 residual stream x [N, D]

@@ -47,7 +47,7 @@ def test_linear(M, N, tile, K, dtype):
     assert (C[M] == 7.0).all()
 
 
-SWIGLU_192, QKV_192, GELU_192 = (f"gemm_kernel<192, 256, 2, 4, {epi}, 0> 16x16x32" for epi in (5, 6, 2))
+SWIGLU_192, QKV_192, GELU_192 = (f"gemm_kernel<192, 256, 2, 4, {epi}, 0> 16x16x32" for epi in (5, 6, 2))   # (QKV: of a tower without a rotary embedding)
 PROJ_64 = "gemm_kernel<64, 160, 2, 2, 4, 0> 16x16x32"
 
 
@@ -55,7 +55,7 @@ PROJ_64 = "gemm_kernel<64, 160, 2, 2, 4, 0> 16x16x32"
 # split any more, and 2048, the most that 64 x 160 tiles take; QKV: 2392 tokens are thirteen tile rows of 192 x 256
 @pytest.mark.parametrize("sizes,kernels", [([(476, 476)], dict(mlp_up=SWIGLU_192)), ([(504, 672)], dict(mlp_up=SWIGLU_192)),
                                            ([(448, 840), (28, 28)], dict(proj=PROJ_64)),
-                                           ([(448, 896)], dict(proj=PROJ_64)), ([(644, 728)], dict(qkv=QKV_192))])
+                                           ([(448, 896)], dict(proj=PROJ_64)), ([(644, 728)], dict(qkv=QKV_192 + ", 128 positions"))])
 def test_images(sizes, kernels):
     cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(1,))
     w = wl.images_workload(f"one_round_{len(sizes)}_{sizes[0][1]}", cfg, sizes, seq_len=2048, data_seed=sizes[0][1])
