@@ -64,6 +64,57 @@ def test_images(sizes, kernels):
     check_items(f"{int(w.cu_seqlens[-1])} tokens", w, W, sorted({0, len(sizes) - 1}))
 
 
+# down projections of one to four slices (the pipeline holds four) at both ends of the rows that take 64 x 160 tiles
+@pytest.mark.parametrize("mlp_dim", [64, 128, 192, 256])
+@pytest.mark.parametrize("sizes", [[(420, 420), (112, 112)], [(448, 868), (84, 140)]])
+def test_short_k_on_64_rows(sizes, mlp_dim):
+    cfg = replace(wl.vit_7b_config(2), dtype="bf16", full_attn_layers=(), hidden=1280, n_heads=16, mlp_dim=mlp_dim, merger_hidden=512, out_hidden=512)
+    w = wl.images_workload(f"short_64_{sizes[0][1]}_{mlp_dim}", cfg, sizes, seq_len=2048, data_seed=mlp_dim)
+    runs(cfg, w.weights, int(w.cu_seqlens[-1]), mlp_down=PROJ_64)
+    check_items(f"{int(w.cu_seqlens[-1])} tokens, mlp {mlp_dim}", w, w.weights, [0, 1])
+
+
+# a narrow tower's, which also write the plain sums of the folded LayerNorm: two column tiles of 65 tile rows, and one and
+# five slices
+@pytest.mark.parametrize("mlp_dim", [64, 320])
+def test_narrow_clips_on_64_rows(mlp_dim):
+    cfg = replace(wl.audio_config(2), attn_chunk=100, hidden=320, n_heads=5, mlp_dim=mlp_dim, out_hidden=512)
+    w = wl.audio_workload(f"narrow_64_{mlp_dim}", cfg, 5, 1640, seq_len=2048, data_seed=mlp_dim)
+    runs(cfg, w.weights, 4100, proj=PROJ_64.replace("4, 0>", "9, 0>"), mlp_down=PROJ_64.replace("4, 0>", "9, 0>"))
+    check_items(f"five clips of 820 tokens, mlp {mlp_dim}", w, w.weights, [0, 4])
+
+
+# The launches in front of the blocks and behind them, on 192 x 256 tiles as the plain ones of their sizes: the first
+# convolution (GELU, a row map) and the second (fp32 GELU, rows between the clips that belong to neither), the patch embeddings, and
+# the merger's first product (GELU into a high and a low half)
+def plain_192(*shapes):
+    if not any(k.startswith("CS_") for k in os.environ):
+        for shape in shapes:
+            assert B.cs_linear_kernel(*shape) == "gemm_kernel<192, 256, 2, 4, 1, 0> 16x16x32", shape
+
+
+@pytest.mark.parametrize("n_clips,frames", [(3, 2800), (7, 2400)])   # 8400 frames; 8400 tokens
+def test_convolutions_on_192_rows(n_clips, frames):
+    plain_192((8400, 1280, 384), (8406, 1280, 3840))
+    w = wl.audio_workload(f"convolutions_192_{n_clips}", replace(wl.audio_config(1), attn_chunk=100), n_clips, frames, seq_len=2048, data_seed=n_clips)
+    check_items(f"{n_clips} clips of {frames} frames", w, shared_weights("audio_1", w), [0, n_clips - 1])
+
+
+# (at 2305 merge groups it is the merger's second product, whose rows go to their places through a map)
+@pytest.mark.parametrize("n,merger", [(8, (2049, 5120, 2 * 5120)), (9, (2305, 3584, 2 * 5120))])
+def test_patches_and_merger_on_192_rows(n, merger):
+    plain_192((1024 * n + 4, 1280, 1216), merger)
+    cfg = replace(wl.vit_7b_config(1), dtype="bf16", full_attn_layers=())
+    w = wl.images_workload(f"merger_192_{n}", cfg, [(448, 448)] * n + [(28, 28)], seq_len=2048, data_seed=n)
+    check_items(f"{1024 * n + 4} patches", w, shared_weights("vit_1", w), [0, n])
+
+
+def test_nine_class_token_tiles():
+    plain_192((9 * 1028, 1024, 640), (9 * 256, 4096, 4096))
+    w = wl.images_workload("nine_tiles", wl.vit_cls_config(1), [(448, 448)] * 9, seq_len=2048, data_seed=9)
+    check_items("nine tiles", w, shared_weights("cls_1", w), [0, 8])
+
+
 # residual GEMMs on 192 x 160 tiles, six waves: 4100 tokens (the last tile row of 68), 5760, 30 full tile rows,
 # and clips of 5140
 RES_192 = "gemm_kernel<192, 160, 3, 2, 4, 0> 16x16x32"
@@ -103,7 +154,7 @@ def test_two_clips():
     check_items("two clips of 1100 tokens", w, W, [1])
 
 
-# 16 slices in two parts and 64 in three (22, 21 and 21) or two
+# 16 slices in two parts and 64 in three (21, 21 and 22) or two
 @pytest.mark.parametrize("tiles,proj,down", [(1, 2, 3), (2, 2, 2)])
 def test_class_token_tiles(tiles, proj, down):
     w = wl.images_workload(f"one_round_tiles_{tiles}", wl.vit_cls_config(2), [(448, 448)] * tiles, seq_len=2048, data_seed=tiles)

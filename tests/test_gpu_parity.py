@@ -98,10 +98,11 @@ def test_forward_embeddings_workload_spans():
 # ------------------------------------------------------------------ contraction kernels on their own
 # one K slice; one row; N a multiple of 4 only; ragged tails of every tile shape; the layer shapes; 256 x 256
 # tiles that fill one round of the chip (180 of them), with and without 64-row tail tiles behind the full
-# tile rows (3000 = 11 x 256 + 184); 256 x 128 tiles with one tail tile row (8224 = 32 x 256 + 32)
+# tile rows (3000 = 11 x 256 + 184); one round of 192 x 256 tiles (8224 x 1024); 256 x 128 tiles with one tail tile row
+# (12 320 = 48 x 256 + 32)
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 64), (100, 36, 192), (300, 200, 128), (1000, 520, 1216),
                                    (257, 3840, 1280), (2048, 1280, 3456), (3000, 1280, 256), (3072, 3840, 128),
-                                   (3000, 3840, 192), (8224, 1024, 256),
+                                   (3000, 3840, 192), (8224, 1024, 256), (12320, 1024, 256),
                                    (4096, 4352, 128),      # 272 tiles of 256 x 256: the last 16 run as half tiles
                                    (16500, 2048, 64)])     # 520 tiles, a ragged last tile row among the 8 split ones
 def test_linear_matches_oracle(M, N, K):
