@@ -404,7 +404,7 @@ cs_status cs_attention_varlen_groups(const void* qk, const void* vt, int64_t ld_
  * since the last read, and clears them.  step = CS_STEP_NONE switches recording off. */
 typedef enum {
   CS_STEP_NONE = 0,
-  CS_STEP_FRONT = 1,       /* gather/cast, rotary table, patch embed / convolutions */
+  CS_STEP_FRONT = 1,       /* gather/cast, patch embed / convolutions; rotary angles by token where they are not read by position */
   CS_STEP_NORM = 2,        /* RMSNorm / LayerNorm launches inside the blocks        */
   CS_STEP_QKV = 3,         /* QKV projection with rotary epilogue                   */
   CS_STEP_ATTN_WINDOW = 4,

@@ -142,11 +142,11 @@ inline bool gemm_rows_addressable(int64_t rows, int64_t pitch) {
 cs_status launch_gemm(int epilogue, const GemmArgs& g, hipStream_t stream);
 // The largest RopeTable::bytes that the QKV launch of M rows takes (0: none).
 int32_t gemm_rope_room(int64_t M, int32_t hidden, int32_t head_dim, int64_t K, int64_t lda, int64_t ldw);
+// The tile of a launch of partial sums in `parts` parts over K, where one round of the chip holds it; false where none does.
+bool gemm_split_tile(int64_t M, int64_t N, int64_t parts, int32_t* bm, int32_t* bn);
 // Column tiles (= partial sums of squares per row) of a residual GEMM that can fold the next RMSNorm into its
 // epilogue for M rows and N columns, or 0 if that launch would not run on the tile that supports it.  pitch: elements
 // between the rows of its operands.
-// The tile of a launch of partial sums in `parts` parts over K, where one round of the chip holds it; false where none does.
-bool gemm_split_tile(int64_t M, int64_t N, int64_t parts, int32_t* bm, int32_t* bn);
 int32_t gemm_norm_fold_parts(int64_t M, int64_t N, int64_t K, int64_t pitch, bool scaled = false, bool sums = false);
 
 // ---- write-through global stores -----------------------------------------------------------
@@ -260,9 +260,9 @@ cs_status launch_pool_layernorm(const float* x, const float* gain, const float* 
 // dst[r, 0:dst_cols) = bf16(src[src_row[r], 0:src_cols)) padded with zeros; src_row < 0 gives a zero row
 cs_status launch_gather_cast(const void* src, int src_is_bf16, int32_t src_cols, const int32_t* src_row,
                              bf16_t* dst, int32_t dst_cols, int64_t rows, hipStream_t s);
-// out[n, j] = (cos, sin) of pos[n, axis[j]] * inv_freq[j]
 // rows 0 .. of a RopeTable: entry u of row p = (cos, sin) of p * inv_freq[u]
 cs_status launch_rope_positions(const float* inv_freq, int32_t n_freq, int32_t pitch, int32_t rows, unsigned char* tab, hipStream_t s);
+// out[n, j] = (cos, sin) of pos[n, axis[j]] * inv_freq[j]
 cs_status launch_rope_table(const int32_t* pos, const int32_t* axis, const float* inv_freq, int32_t half,
                             float* cos_sin_out, int64_t n_tok, hipStream_t s);
 // class-token towers: pos[r] >= 0: x[r] += table[pos[r]];  -1: x[r] = table[class_row];  -2: x[r] = 0

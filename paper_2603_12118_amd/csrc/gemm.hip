@@ -1274,11 +1274,16 @@ static cs_status launch_epi(const GemmArgs& g, hipStream_t stream) {
   }
   // 192 x 256 (eight waves of 96 x 64; two stages, three do not fit) where 128 x 256 need more than a round of the chip and
   // these make one: K loops of one-round launches go at the pace of a CU's operand loads, 1147 KB at K = 1280 instead of 1311
-  // for 256 x 256, with three quarters of the products behind each slice, and of 256 x 256 there are fewer than 200.  Where
-  // those did not fill 5/8 of a round the launch ran on 128 x 128, two per CU, and N = 5120 or 4096 beyond a round on 256 x 160
-  // or 256 x 128.  A step, before -> with these: 7B-style tower, gate|up of 1280 tokens 3642 -> 3433 us, 1428 3702 -> 3577, QKV of
-  // 2392 5802 -> 5513, of 3072 5670 -> 5546; audio tower, QKV and fc1 of 2200 6219 -> 5247, QKV of 2512 6809 -> 6439;
-  // class-token tower, QKV of 3084 3914 -> 3647.  (256 x 160 in one round are as fast: fc1 of 1600 - 2048 audio tokens within 1 %.)
+  // for 256 x 256, with three quarters of the products behind each slice and, at most widths, more CUs at work.  Without them such
+  // a launch runs on 256 x 256 where those fill 5/8 of a round, on 128 x 128, two per CU, where they do not, or in more than a round
+  // of 256 x 160 or 256 x 128: N = 5120 and 4096, and from 8193 rows on N = 1280 (to 9792: first convolution, patch embedding)
+  // and 1024 (to 12 288).  us, those -> 192 x 256: 8196 x 1280 x 1280 50.1 -> 32.3, 9792 rows 48.2 -> 30.8, 8224 x 1280 x 3840 115
+  // -> 74, 8224 x 1024 x 640 18.3 -> 16.2, 12 288 rows 24.9 -> 19.2, 2052 x 5120 x 5120 154 -> 101, 3072 x 4096 x 4096 112 -> 81, 1300 x
+  // 9216 x 1280 44.6 -> 31.4, 3264 x 3840 x 1280 46 -> 30, the least 2310 x 3584 x 5120 106 -> 102.  A step: 7B-style tower, gate|up of
+  // 1280 tokens 3715 -> 3547 us, 1428 3875 -> 3740, QKV of 2392 5955 -> 5590, of 3072 5790 -> 5661, patches and merger of 8196 13.82 ->
+  // 13.65 ms; audio tower, QKV and fc1 of 2200 6367 -> 5404 us, QKV of 2512 6928 -> 6646; class-token tower, QKV of 3084 3983 -> 3780,
+  // both ends of 9252 10.55 -> 10.35 ms.  Also where 256 x 256 make as many tiles (255 of 576 x 21 760, gate|up: eight layers 1002 -> 970).
+  // (256 x 160 in one round are as fast: fc1 of 1600 - 2048 audio tokens within 1 %.)
   const bool one_192 = !RESADD && big_ok && g.splits <= 1 && !one_round(g.M, g.N, 1, 128, 256) && one_round(g.M, g.N, 1, 192, 256);
   if constexpr (EPI != EPI_QKV && EPI != EPI_SWIGLU_BF16) {
     // narrow outputs (N = hidden = 1280): 256 x 160 tiles, eight waves of 64 x 80 (a wave's third 32-column block
