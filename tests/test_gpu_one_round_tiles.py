@@ -110,7 +110,7 @@ def test_patches_and_merger_on_192_rows(n, merger):
 
 
 def test_nine_class_token_tiles():
-    plain_192((9 * 1028, 1024, 640), (9 * 256, 4096, 4096))
+    plain_192((9 * 1028, 1024, 640), (9 * 257, 4096, 2 * 4096))
     w = wl.images_workload("nine_tiles", wl.vit_cls_config(1), [(448, 448)] * 9, seq_len=2048, data_seed=9)
     check_items("nine tiles", w, shared_weights("cls_1", w), [0, 8])
 
