@@ -1,5 +1,5 @@
 """Launches that the chip holds in one round: 192 x 256 tiles, where 128 x 256 need more than one, residual GEMMs on 64 x 160
-tiles, and the class-token tower's in parts over K.  Both ends of each range, ragged last tiles of either
+and 192 x 160 tiles, and the class-token tower's in parts over K.  Both ends of each range, ragged last tiles of either
 direction, and K loops as short as one slice."""
 import os
 from dataclasses import replace
